@@ -8,7 +8,9 @@
 // the input ever exists.  The compression functions are fully unrolled with the state
 // and message schedule in VGPRs, using v_alignbit_b32 rotates, v_bitop3_b32 for every
 // three-input boolean function (including three-way xor) and v_add3_u32 / v_xad_u32 for
-// the sums.
+// the sums.  Each exists in two forms of the same arithmetic: compress<A>, in the compiler's
+// order with the fewest instructions, for a wave that has its SIMD to itself, and
+// compress_many<A> (hb_issue.hpp), ordered for a SIMD that several waves share.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -217,9 +219,14 @@ template <int A> __device__ __forceinline__ void init_state(uint32_t s[8])
     else sm3_init(s);
 }
 
-template <int A> __device__ __forceinline__ void compress(uint32_t s[8], const uint32_t w[16])
+// MANY: the form for a SIMD shared by several waves (hb_issue.hpp) rather than for one
+// wave alone on its SIMD.
+template <int A> __device__ __forceinline__ void compress_many(uint32_t s[8], const uint32_t w[16]);
+
+template <int A, bool MANY = false> __device__ __forceinline__ void compress(uint32_t s[8], const uint32_t w[16])
 {
-    if constexpr (A == MD5) md5_compress(s, w);
+    if constexpr (MANY) compress_many<A>(s, w);
+    else if constexpr (A == MD5) md5_compress(s, w);
     else if constexpr (A == SHA1) sha1_compress(s, w);
     else sm3_compress(s, w);
 }
@@ -377,7 +384,7 @@ template <int A> constexpr int kDefaultBurst = A == MD5 ? 4 : 2;
 // nb = floor((L + 8) / 64) + 1 -- tail bytes, 0x80, zeros and the length field m.bits --
 // are assembled in registers.  When every lane of a wave has the same length the loop and
 // its branch are wave-uniform.
-template <int A, bool PAD, int BURST = kDefaultBurst<A>>
+template <int A, bool PAD, int BURST = kDefaultBurst<A>, bool MANY = false>
 __device__ __forceinline__ void absorb(const Msg &m, uint32_t s[8])
 {
     static_assert(BURST == 1 || BURST == 2 || BURST == 4, "blocks per burst");
@@ -404,36 +411,36 @@ __device__ __forceinline__ void absorb(const Msg &m, uint32_t s[8])
         for (; blk + 4 <= nburst; blk += 4) {
             uint32_t w[4][16];
             load_full_quad<kBE>(m, blk, aligned, w);
-            compress<A>(s, w[0]);
-            compress<A>(s, w[1]);
-            compress<A>(s, w[2]);
-            compress<A>(s, w[3]);
+            compress<A, MANY>(s, w[0]);
+            compress<A, MANY>(s, w[1]);
+            compress<A, MANY>(s, w[2]);
+            compress<A, MANY>(s, w[3]);
         }
     }
     if constexpr (BURST >= 2) {
         for (; blk + 2 <= nburst; blk += 2) {
             uint32_t w0[16], w1[16];
             load_full_pair<kBE>(m, blk, aligned, w0, w1);
-            compress<A>(s, w0);
-            compress<A>(s, w1);
+            compress<A, MANY>(s, w0);
+            compress<A, MANY>(s, w1);
         }
     }
     for (; blk < nb; ++blk) {
         uint32_t w[16];
         if (blk < nfast) load_full_block(m, blk, w);
         else load_any_block<Traits<A>::kBE>(m, blk, blk + 1 == nb, w);
-        compress<A>(s, w);
+        compress<A, MANY>(s, w);
     }
 }
 
 // Digest state of one whole message: the initial value, then every block including the
 // padding.
-template <int A, int BURST = kDefaultBurst<A>>
+template <int A, int BURST = kDefaultBurst<A>, bool MANY = false>
 __device__ __forceinline__ void hash_message(const uint8_t *base, uint64_t len, uint32_t s[8])
 {
     const Msg m = make_msg<A>(base, len);
     init_state<A>(s);
-    absorb<A, true, BURST>(m, s);
+    absorb<A, true, BURST, MANY>(m, s);
 }
 
 // As hash_message, with the next whole block's loads issued before the current block is
@@ -486,3 +493,5 @@ __device__ __forceinline__ void store_digest(uint8_t *out, const uint32_t s[8], 
 }
 
 }  // namespace hb
+
+#include "hb_issue.hpp"  // compress_many

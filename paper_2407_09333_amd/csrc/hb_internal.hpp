@@ -22,6 +22,11 @@ hipError_t launch_plain(int algo, const uint8_t *msgs, const uint64_t *offs, con
 
 int digest_size(int algo);
 
+// One lane per message for n messages makes at most one wave per SIMD of the current
+// device: every wave runs alone, so the compression with the fewest instructions is the
+// faster one; from two waves on a SIMD the one ordered for sharing is (hb_issue.hpp).
+bool few_waves(uint64_t n);
+
 // Hash messages [i0, i1) on host threads (the CPU share of a CPU + GPU split); message i's
 // digest goes to out + (i - i0) * stride.  threads <= 0: all hardware threads.
 void cpu_hash_range(const uint8_t *algos, int algo, const uint8_t *msgs, const uint64_t *offs, const uint64_t *lens,

@@ -1,5 +1,6 @@
 // hb_kernels.hip -- plain batch-hashing kernels: one lane per message, in index order.
 #include <algorithm>
+#include <atomic>
 #include <cstdlib>
 
 #include "hb_device.hpp"
@@ -25,13 +26,11 @@ __device__ __forceinline__ uint32_t xcd_contiguous_block()
 // Lane i hashes message i.  FIXED: message i starts at i * fixed_len and is fixed_len
 // bytes long (no metadata reads).  With `filter`, messages whose id differs from A are
 // skipped, so one launch per algorithm covers a mixed batch.
-template <int A, bool FIXED>
-__global__ __launch_bounds__(kPlainBlock) void k_plain(const uint8_t *__restrict__ msgs,
-                                                       const uint64_t *__restrict__ offs,
-                                                       const uint64_t *__restrict__ lens, uint64_t n,
-                                                       uint64_t fixed_len, uint8_t *__restrict__ out,
-                                                       uint32_t stride,
-                                                       const uint8_t *__restrict__ filter)
+template <int A, bool FIXED, bool MANY>
+__device__ __forceinline__ void plain_lane(const uint8_t *__restrict__ msgs, const uint64_t *__restrict__ offs,
+                                           const uint64_t *__restrict__ lens, uint64_t n, uint64_t fixed_len,
+                                           uint8_t *__restrict__ out, uint32_t stride,
+                                           const uint8_t *__restrict__ filter)
 {
     const uint64_t i = uint64_t(xcd_contiguous_block()) * kPlainBlock + threadIdx.x;
     if (i >= n) return;
@@ -49,8 +48,31 @@ __global__ __launch_bounds__(kPlainBlock) void k_plain(const uint8_t *__restrict
     if constexpr (FIXED) { off = i * fixed_len; len = fixed_len; }
     else { off = offs[i]; len = lens[i]; }
     uint32_t s[8];
-    hash_message<A>(msgs + off, len, s);
+    hash_message<A, kDefaultBurst<A>, MANY>(msgs + off, len, s);
     store_digest<A>(out + i * stride, s, stride);
+}
+
+// For launches with more than one wave per SIMD, and (k_plain_few) for smaller ones.
+template <int A, bool FIXED>
+__global__ __launch_bounds__(kPlainBlock) void k_plain(const uint8_t *__restrict__ msgs,
+                                                       const uint64_t *__restrict__ offs,
+                                                       const uint64_t *__restrict__ lens, uint64_t n,
+                                                       uint64_t fixed_len, uint8_t *__restrict__ out,
+                                                       uint32_t stride,
+                                                       const uint8_t *__restrict__ filter)
+{
+    plain_lane<A, FIXED, true>(msgs, offs, lens, n, fixed_len, out, stride, filter);
+}
+
+template <int A, bool FIXED>
+__global__ __launch_bounds__(kPlainBlock) void k_plain_few(const uint8_t *__restrict__ msgs,
+                                                           const uint64_t *__restrict__ offs,
+                                                           const uint64_t *__restrict__ lens, uint64_t n,
+                                                           uint64_t fixed_len, uint8_t *__restrict__ out,
+                                                           uint32_t stride,
+                                                           const uint8_t *__restrict__ filter)
+{
+    plain_lane<A, FIXED, false>(msgs, offs, lens, n, fixed_len, out, stride, filter);
 }
 
 // Buffer resource word 3 for raw (unswizzled, unformatted) dword access on gfx9-family
@@ -69,14 +91,14 @@ constexpr int kCpolNonTemporal = 2;
 // the per-lane path.  The loads are buffer loads off one wave-uniform base, so they take no
 // vector address arithmetic (MD5 issues its compression instructions and almost nothing
 // more) and few registers.  Each wave keeps the next burst in flight while it compresses the
-// current one.  MD5, whose reads and compression take about as long as each other, streams
-// with non-temporal loads (every line is read once, whole, by one instruction) at five waves
-// per SIMD, the most the LDS holds (8 KiB per wave); SHA-1 and SM3, bound by their
-// compression, use cached loads at five and four.  In interleaved runs on 2^20 x 1 KiB
-// against the per-lane kernel: MD5 0.92, SHA-1 0.98, SM3 0.98 of its time.
-template <int A>
-__global__ __launch_bounds__(kPlainBlock) __attribute__((amdgpu_waves_per_eu(A == MD5 ? 5 : 4))) void k_plain_lds(const uint8_t *__restrict__ msgs, uint64_t n,
-                                                           uint64_t len, uint8_t *__restrict__ out)
+// current one.  MD5, bound by its reads, streams with non-temporal loads (every line is read
+// once, whole, by one instruction); SHA-1 and SM3, bound by their compression, use cached
+// loads.  All three run five waves per SIMD, the most the LDS holds (8 KiB per wave).  On
+// 2^20 x 1 KiB the three launches took 1,132 us with the compiler's order of the
+// compressions and take 998 us with the shared-SIMD order (hb_issue.hpp).
+template <int A, bool MANY>
+__device__ __forceinline__ void plain_lds_wave(const uint8_t *__restrict__ msgs, uint64_t n, uint64_t len,
+                                               uint8_t *__restrict__ out)
 {
     constexpr bool kStream = A == MD5;  // non-temporal loads
     __shared__ u32x4 slice[kPlainBlock / 64][512];  // per wave: 64 messages x 128 bytes
@@ -134,14 +156,14 @@ __global__ __launch_bounds__(kPlainBlock) __attribute__((amdgpu_waves_per_eu(A =
             __builtin_amdgcn_sched_barrier(0);
             words(1, w1);
             __builtin_amdgcn_sched_barrier(0);
-            compress<A>(s, w0);
-            compress<A>(s, w1);
+            compress<A, MANY>(s, w0);
+            compress<A, MANY>(s, w1);
         } else {
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
                 uint32_t w[16];
                 words(h, w);
-                compress<A>(s, w);
+                compress<A, MANY>(s, w);
             }
         }
     };
@@ -161,7 +183,7 @@ __global__ __launch_bounds__(kPlainBlock) __attribute__((amdgpu_waves_per_eu(A =
     for (; blk < nfast; ++blk) {
         uint32_t w[16];
         load_full_block(m, blk, w);
-        compress<A>(s, w);
+        compress<A, MANY>(s, w);
     }
     if (len % 64u == 0) {
         // the last block is padding only -- 0x80, zeros, the bit length -- and the same for
@@ -174,21 +196,36 @@ __global__ __launch_bounds__(kPlainBlock) __attribute__((amdgpu_waves_per_eu(A =
         const uint64_t bits = len << 3;
         w[14] = kBE ? uint32_t(bits >> 32) : uint32_t(bits);
         w[15] = kBE ? uint32_t(bits) : uint32_t(bits >> 32);
-        compress<A>(s, w);
+        compress<A, MANY>(s, w);
     } else {
         for (; blk < nb; ++blk) {
             uint32_t w[16];
             load_any_block<Traits<A>::kBE>(m, blk, blk + 1 == nb, w);
-            compress<A>(s, w);
+            compress<A, MANY>(s, w);
         }
     }
     store_digest<A>(out + mi * Traits<A>::kDigest, s, Traits<A>::kDigest);
 }
 
+// For launches with more than one wave per SIMD, and (k_plain_lds_few) for smaller ones.
+template <int A>
+__global__ __launch_bounds__(kPlainBlock) __attribute__((amdgpu_waves_per_eu(A == MD5 ? 5 : 4))) void
+k_plain_lds(const uint8_t *__restrict__ msgs, uint64_t n, uint64_t len, uint8_t *__restrict__ out)
+{
+    plain_lds_wave<A, true>(msgs, n, len, out);
+}
+
+template <int A>
+__global__ __launch_bounds__(kPlainBlock) __attribute__((amdgpu_waves_per_eu(A == MD5 ? 5 : 4))) void
+k_plain_lds_few(const uint8_t *__restrict__ msgs, uint64_t n, uint64_t len, uint8_t *__restrict__ out)
+{
+    plain_lds_wave<A, false>(msgs, n, len, out);
+}
+
 // The paper's workload (Sec. V-A.2): message i is the 9-character decimal text of
 // start + i, zero-padded ("000000000" .. "999999999").  The text is produced in registers,
 // so a 9-byte message is one padded block: 9 bytes, 0x80, zeros, bit length 72.
-template <int A>
+template <int A, bool MANY>
 __global__ __launch_bounds__(kPlainBlock) void k_digits9(uint64_t start, uint64_t n, uint8_t *__restrict__ out)
 {
     const uint64_t i = uint64_t(blockIdx.x) * kPlainBlock + threadIdx.x;
@@ -217,7 +254,7 @@ __global__ __launch_bounds__(kPlainBlock) void k_digits9(uint64_t start, uint64_
     }
     uint32_t s[8];
     init_state<A>(s);
-    compress<A>(s, w);
+    compress<A, MANY>(s, w);
     store_digest<A>(out + i * Traits<A>::kDigest, s, Traits<A>::kDigest);
 }
 
@@ -257,14 +294,31 @@ hipError_t launch_digits9(int algo, uint64_t start, uint64_t n, uint8_t *out, hi
     const uint64_t blocks = (n + kPlainBlock - 1) / kPlainBlock;
     if (blocks > 0x7fffffffull) return hipErrorInvalidConfiguration;
     const dim3 grid{uint32_t(blocks), 1, 1}, block{kPlainBlock, 1, 1};
+    const bool few = few_waves(n);
     switch (algo) {
-    case MD5: hipLaunchKernelGGL(k_digits9<MD5>, grid, block, 0, stream, start, n, out); break;
-    case SHA1: hipLaunchKernelGGL(k_digits9<SHA1>, grid, block, 0, stream, start, n, out); break;
-    case SM3: hipLaunchKernelGGL(k_digits9<SM3>, grid, block, 0, stream, start, n, out); break;
+    case MD5: hipLaunchKernelGGL((few ? k_digits9<MD5, false> : k_digits9<MD5, true>), grid, block, 0, stream, start, n, out); break;
+    case SHA1: hipLaunchKernelGGL((few ? k_digits9<SHA1, false> : k_digits9<SHA1, true>), grid, block, 0, stream, start, n, out); break;
+    case SM3: hipLaunchKernelGGL((few ? k_digits9<SM3, false> : k_digits9<SM3, true>), grid, block, 0, stream, start, n, out); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
 }
+
+// SIMDs of the current device (four per CU), looked up once per device.
+static uint32_t device_simds()
+{
+    static std::atomic<uint32_t> cached[64];
+    int dev = 0, cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 1024;
+    uint32_t simds = cached[dev].load(std::memory_order_relaxed);
+    if (simds) return simds;
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0) return 1024;
+    simds = uint32_t(cus) * 4u;
+    cached[dev].store(simds, std::memory_order_relaxed);
+    return simds;
+}
+
+bool few_waves(uint64_t n) { return (n + 63u) / 64u <= device_simds(); }
 
 template <int A>
 static hipError_t launch_a(const uint8_t *msgs, const uint64_t *offs, const uint64_t *lens, uint64_t n,
@@ -274,12 +328,10 @@ static hipError_t launch_a(const uint8_t *msgs, const uint64_t *offs, const uint
     const uint64_t blocks = (n + kPlainBlock - 1) / kPlainBlock;
     if (blocks > 0x7fffffffull) return hipErrorInvalidConfiguration;
     const dim3 grid{uint32_t(blocks), 1, 1}, block{kPlainBlock, 1, 1};
-    if (fixed)
-        hipLaunchKernelGGL((k_plain<A, true>), grid, block, 0, stream, msgs, offs, lens, n, fixed_len, out,
-                           stride, filter);
-    else
-        hipLaunchKernelGGL((k_plain<A, false>), grid, block, 0, stream, msgs, offs, lens, n, fixed_len, out,
-                           stride, filter);
+    const bool few = few_waves(n);
+    const auto kernel = fixed ? (few ? k_plain_few<A, true> : k_plain<A, true>)
+                              : (few ? k_plain_few<A, false> : k_plain<A, false>);
+    hipLaunchKernelGGL(kernel, grid, block, 0, stream, msgs, offs, lens, n, fixed_len, out, stride, filter);
     return hipGetLastError();
 }
 
@@ -288,7 +340,8 @@ static hipError_t launch_lds_a(const uint8_t *msgs, uint64_t n, uint64_t len, ui
 {
     const uint64_t blocks = (n + kPlainBlock - 1) / kPlainBlock;
     if (blocks > 0x7fffffffull) return hipErrorInvalidConfiguration;
-    hipLaunchKernelGGL(k_plain_lds<A>, dim3(uint32_t(blocks)), dim3(kPlainBlock), 0, stream, msgs, n, len, out);
+    hipLaunchKernelGGL(few_waves(n) ? k_plain_lds_few<A> : k_plain_lds<A>, dim3(uint32_t(blocks)), dim3(kPlainBlock), 0,
+                       stream, msgs, n, len, out);
     return hipGetLastError();
 }
 

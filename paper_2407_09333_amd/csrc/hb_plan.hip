@@ -651,24 +651,20 @@ __device__ __forceinline__ void hash_lane(const PlanDesc &d, uint32_t idx)
     const uint64_t off = reinterpret_cast<const HB_GLOBAL uint64_t *>(reinterpret_cast<uintptr_t>(d.offs))[idx];
     const uint64_t len = reinterpret_cast<const HB_GLOBAL uint64_t *>(reinterpret_cast<uintptr_t>(d.lens))[idx];
     if constexpr (V == 1 && A != MD5) hash_message_prefetch<A>(d.msgs + off, len, s);
-    else hash_message<A, scheme_burst<V, A>()>(d.msgs + off, len, s);
+    else hash_message<A, scheme_burst<V, A>(), true>(d.msgs + off, len, s);
     store_digest<A>(d.out + uint64_t(idx) * d.stride, s, d.stride);
 }
 
 // Persistent fused kernel: each wave takes items from the queue until none are left.
 // An item is 64 * mpl sorted positions of one algorithm; lane l hashes positions
-// l, l + 64, ... of it.  Items whose cost exceeds the average per-wave share run at raised
-// wave priority so the longest chains keep their issue slots.  PF is the load scheme (see
-// kLoadSchemes).
+// l, l + 64, ... of it.  PF is the load scheme (see kLoadSchemes).
 template <int PF>
-__device__ __forceinline__ void persistent_wave(const PlanWs &ws, uint32_t block, uint32_t nblocks)
+__device__ __forceinline__ void persistent_wave(const PlanWs &ws, uint32_t block)
 {
     const PlanDesc d = *ws.desc;
     const PlanMeta *mp = ws.meta;
     const uint32_t total = mp->seg_item[3];
     const uint32_t per_item = 64u * uint32_t(d.mpl);
-    const uint64_t waves = uint64_t(nblocks) * (kThreads / 64);
-    const uint64_t share = mp->total_cost / (waves ? waves : 1);
     const uint32_t lane = __lane_id();
     uint32_t bulk = mp->bulk_waves;
     if (bulk == 0xffffffffu && d.bulk_margin && total) {
@@ -694,10 +690,6 @@ __device__ __forceinline__ void persistent_wave(const PlanWs &ws, uint32_t block
         int a = 0;
         while (a < 2 && item >= mp->seg_item[a + 1]) ++a;
         const uint32_t pos0 = mp->seg_pos[a] + (item - mp->seg_item[a]) * per_item;
-        const uint32_t first = ws.sorted[pos0];
-        const uint64_t cost = first == kInvalid ? 0 : uint64_t(msg_key(d.lens[first], d.sort)) * algo_cost(a) * d.mpl;
-        if (cost > share) __builtin_amdgcn_s_setprio(2);
-        else __builtin_amdgcn_s_setprio(0);
         const uint32_t long_end = mp->seg_pos[a] + mp->long_n[a] + mp->direct_n[a];  // k_hash_long's
         if (pos0 + per_item <= long_end) continue;
         for (int j = 0; j < d.mpl; ++j) {
@@ -710,13 +702,12 @@ __device__ __forceinline__ void persistent_wave(const PlanWs &ws, uint32_t block
             else hash_lane<SM3, PF>(d, idx);
         }
     }
-    __builtin_amdgcn_s_setprio(0);
 }
 
 template <int PF>
 __global__ __launch_bounds__(kThreads) void k_hash_persistent(PlanWs ws)
 {
-    persistent_wave<PF>(ws, blockIdx.x, gridDim.x);
+    persistent_wave<PF>(ws, blockIdx.x);
 }
 
 // The long-chain kernel and the persistent kernel in one launch: workgroups below
@@ -726,7 +717,7 @@ template <int SCHED, int PF>
 __global__ __launch_bounds__(kThreads) void k_hash_fused(PlanWs ws, uint32_t long_blocks)
 {
     if (blockIdx.x < long_blocks) long_lane<SCHED>(ws, blockIdx.x * kThreads + threadIdx.x);
-    else persistent_wave<PF>(ws, blockIdx.x - long_blocks, gridDim.x - long_blocks);
+    else persistent_wave<PF>(ws, blockIdx.x - long_blocks);
 }
 
 // ---------------------------------------------------------------------------------------

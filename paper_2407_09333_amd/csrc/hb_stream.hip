@@ -29,7 +29,7 @@ __global__ __launch_bounds__(kStreamBlock) void k_init(hb_state *__restrict__ st
     st[i].flags = 0;
 }
 
-template <int A>
+template <int A, bool MANY>
 __global__ __launch_bounds__(kStreamBlock) void k_update(hb_state *__restrict__ st, const uint8_t *__restrict__ msgs,
                                                          const uint64_t *__restrict__ offs,
                                                          const uint64_t *__restrict__ lens, uint64_t n)
@@ -45,12 +45,12 @@ __global__ __launch_bounds__(kStreamBlock) void k_update(hb_state *__restrict__ 
     uint32_t s[8];
     for (int q = 0; q < 8; ++q) s[q] = st[i].h[q];
     const Msg m = make_msg<A>(msgs + offs[i], len);
-    absorb<A, false>(m, s);
+    absorb<A, false, kDefaultBurst<A>, MANY>(m, s);
     for (int q = 0; q < Traits<A>::kWords; ++q) st[i].h[q] = s[q];
     st[i].bytes += len;
 }
 
-template <int A>
+template <int A, bool MANY>
 __global__ __launch_bounds__(kStreamBlock) void k_final(const hb_state *__restrict__ st, const uint8_t *__restrict__ msgs,
                                                         const uint64_t *__restrict__ offs,
                                                         const uint64_t *__restrict__ lens, uint64_t n,
@@ -69,7 +69,7 @@ __global__ __launch_bounds__(kStreamBlock) void k_final(const hb_state *__restri
     const uint64_t len = lens[i];
     Msg m = make_msg<A>(msgs + offs[i], len);
     m.bits = (st[i].bytes + len) << 3;
-    absorb<A, true>(m, s);
+    absorb<A, true, kDefaultBurst<A>, MANY>(m, s);
     store_digest<A>(o, s, Traits<A>::kDigest);
 }
 
@@ -114,9 +114,10 @@ int hash_update_batch(int algo, hb_state *states, const uint8_t *messages, const
     if (rc != HB_OK || n == 0) return rc;
     if (!messages || !offsets || !lengths) return set_error(HB_EINVAL, "hash_update_batch: null device pointer");
     hipStream_t s = static_cast<hipStream_t>(stream);
-    hipError_t e = algo == HB_MD5 ? launch_n(k_update<MD5>, n, s, states, messages, offsets, lengths, n)
-                 : algo == HB_SHA1 ? launch_n(k_update<SHA1>, n, s, states, messages, offsets, lengths, n)
-                                   : launch_n(k_update<SM3>, n, s, states, messages, offsets, lengths, n);
+    const bool few = few_waves(n);
+    hipError_t e = algo == HB_MD5 ? launch_n(few ? k_update<MD5, false> : k_update<MD5, true>, n, s, states, messages, offsets, lengths, n)
+                 : algo == HB_SHA1 ? launch_n(few ? k_update<SHA1, false> : k_update<SHA1, true>, n, s, states, messages, offsets, lengths, n)
+                                   : launch_n(few ? k_update<SM3, false> : k_update<SM3, true>, n, s, states, messages, offsets, lengths, n);
     return e == hipSuccess ? HB_OK : hip_error(e, "hash_update_batch: launch");
 }
 
@@ -130,9 +131,10 @@ int hash_final_batch(int algo, const hb_state *states, const uint8_t *messages, 
     if (reinterpret_cast<uintptr_t>(digests_out) & 3u)
         return set_error(HB_EINVAL, "hash_final_batch: digests_out must be 4-byte aligned");
     hipStream_t s = static_cast<hipStream_t>(stream);
-    hipError_t e = algo == HB_MD5 ? launch_n(k_final<MD5>, n, s, states, messages, offsets, lengths, n, digests_out)
-                 : algo == HB_SHA1 ? launch_n(k_final<SHA1>, n, s, states, messages, offsets, lengths, n, digests_out)
-                                   : launch_n(k_final<SM3>, n, s, states, messages, offsets, lengths, n, digests_out);
+    const bool few = few_waves(n);
+    hipError_t e = algo == HB_MD5 ? launch_n(few ? k_final<MD5, false> : k_final<MD5, true>, n, s, states, messages, offsets, lengths, n, digests_out)
+                 : algo == HB_SHA1 ? launch_n(few ? k_final<SHA1, false> : k_final<SHA1, true>, n, s, states, messages, offsets, lengths, n, digests_out)
+                                   : launch_n(few ? k_final<SM3, false> : k_final<SM3, true>, n, s, states, messages, offsets, lengths, n, digests_out);
     return e == hipSuccess ? HB_OK : hip_error(e, "hash_final_batch: launch");
 }
 
