@@ -75,7 +75,9 @@ enum { HB_PROBE_ADD3 = 0, HB_PROBE_ALIGNBIT = 1, HB_PROBE_BITOP3 = 2, HB_PROBE_A
 int hb_probe_valu(int kind, int waves_per_simd, double *cycles_out, double *clock_ghz_out);
 
 /*
- * hash_batch -- plain batch hashing, one GPU lane per message, in index order.
+ * hash_batch -- plain batch hashing in one launch: tiles of consecutive messages, each sorted
+ * by block count in LDS and hashed longest first, one GPU lane per message (the longest of
+ * a tile with their schedules computed by a second wave).
  *   algo         HB_MD5 / HB_SHA1 / HB_SM3
  *   messages     device, packed message bytes
  *   offsets      device, n x uint64 byte offsets into messages
@@ -107,8 +109,8 @@ int hash_batch_fixed(int algo, const uint8_t *messages, uint64_t n, uint64_t msg
                      uint8_t *digests_out, void *stream);
 
 /*
- * hash_batch_mixed -- each message with its own algorithm, plain form: one launch per
- * algorithm present, each lane skipping messages of the other algorithms.
+ * hash_batch_mixed -- each message with its own algorithm, plain form: one launch as
+ * hash_batch's, with a workgroup per algorithm for each tile.
  *   algos        device, n x uint8 algorithm ids
  *   digests_out  device, n slots of 32 bytes (bytes past the digest size are zeroed)
  * An invalid id in algos is not detected on the device; its slot is left all zero.

@@ -82,8 +82,8 @@ int hash_batch_strided(int algo, const uint8_t *messages, const uint64_t *offset
     int rc = check_common(algo, messages, n, digests_out, stride, "hash_batch");
     if (rc != HB_OK || n == 0) return rc;
     if (!offsets || !lengths) return set_error(HB_EINVAL, "hash_batch: null offsets or lengths");
-    hipError_t e = launch_plain(algo, messages, offsets, lengths, n, false, 0, digests_out, uint32_t(stride), nullptr,
-                                static_cast<hipStream_t>(stream));
+    hipError_t e = launch_ragged(nullptr, algo, messages, offsets, lengths, n, digests_out, uint32_t(stride),
+                                 static_cast<hipStream_t>(stream));
     return e == hipSuccess ? HB_OK : hip_error(e, "hash_batch: launch");
 }
 
@@ -101,8 +101,7 @@ int hash_batch_fixed(int algo, const uint8_t *messages, uint64_t n, uint64_t msg
     int rc = check_common(algo, messages, n, digests_out, ds, "hash_batch_fixed");
     if (rc != HB_OK || n == 0) return rc;
     if (msg_len >= (1ull << 61)) return set_error(HB_EINVAL, "hash_batch_fixed: msg_len must be below 2^61");
-    hipError_t e = launch_plain(algo, messages, nullptr, nullptr, n, true, msg_len, digests_out, uint32_t(ds), nullptr,
-                                static_cast<hipStream_t>(stream));
+    hipError_t e = launch_fixed(algo, messages, n, msg_len, digests_out, uint32_t(ds), static_cast<hipStream_t>(stream));
     return e == hipSuccess ? HB_OK : hip_error(e, "hash_batch_fixed: launch");
 }
 
@@ -112,11 +111,9 @@ int hash_batch_mixed(const uint8_t *algos, const uint8_t *messages, const uint64
     int rc = check_common(HB_MD5, messages, n, digests_out, 32, "hash_batch_mixed");
     if (rc != HB_OK || n == 0) return rc;
     if (!algos || !offsets || !lengths) return set_error(HB_EINVAL, "hash_batch_mixed: null algos, offsets or lengths");
-    hipStream_t s = static_cast<hipStream_t>(stream);
-    for (int a = HB_MD5; a <= HB_SM3; ++a) {
-        hipError_t e = launch_plain(a, messages, offsets, lengths, n, false, 0, digests_out, 32u, algos, s);
-        if (e != hipSuccess) return hip_error(e, "hash_batch_mixed: launch");
-    }
+    hipError_t e = launch_ragged(algos, HB_MD5, messages, offsets, lengths, n, digests_out, 32u,
+                                 static_cast<hipStream_t>(stream));
+    if (e != hipSuccess) return hip_error(e, "hash_batch_mixed: launch");
     return HB_OK;
 }
 

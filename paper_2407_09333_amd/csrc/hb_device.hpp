@@ -235,6 +235,19 @@ template <int A, bool MANY = false> __device__ __forceinline__ void compress(uin
 // Message reading
 // ---------------------------------------------------------------------------------------
 
+// Workgroups are dealt round-robin to the GPU's XCDs (8 on MI355X, each with its own L2);
+// renumbering them so that each XCD takes a contiguous run of the grid makes each XCD
+// stream through one contiguous region of the input.  Measured on 2^20 x 1 KiB MD5: 205 us
+// against 210 us in dispatch order; a load-only stream: 5.7 against 5.4 TB/s.
+constexpr uint32_t kXcds = 8;
+
+__device__ __forceinline__ uint32_t xcd_contiguous(uint32_t b, uint32_t count)
+{
+    const uint32_t full = count & ~(kXcds - 1u);
+    if (b >= full) return b;  // the last count % 8 workgroups keep their number
+    return (b % kXcds) * (full / kXcds) + b / kXcds;
+}
+
 // A lane's view of its message: the dword holding the first byte, the byte offset r of
 // that byte inside it, the byte length and the v_perm selector for the algorithm's word
 // order.  Only dwords that hold at least one message byte are ever read, so no access
@@ -342,20 +355,15 @@ __device__ __forceinline__ void load_full_quad(const Msg &m, uint64_t blk, bool 
         for (int i = 0; i < 16; ++i) w[b][i] = perm(raw[16 * b + i + 1], raw[16 * b + i], m.sel);
 }
 
-// Any block of the padded message, including the tail block (message bytes, 0x80,
-// zeros), the length-only block and, when `last`, the 64-bit bit length in words 14-15
-// (low word first for MD5, high word first for SHA-1 / SM3).
+// The words of any block of the padded message from its raw dwords (zeros past the last
+// one that holds message bytes), rem being the message bytes from the block's start: the
+// tail block (message bytes, 0x80, zeros), the length-only block and, when `last`, the
+// 64-bit bit length in words 14-15 (low word first for MD5, high word first for SHA-1 / SM3).
 template <bool BE>
-__device__ __forceinline__ void load_any_block(const Msg &m, uint64_t blk, bool last, uint32_t w[16])
+__device__ __forceinline__ void assemble_block(const Msg &m, int64_t rem, bool last, const uint32_t raw[17], uint32_t w[16])
 {
-    const HB_GLOBAL uint32_t *q = m.p + blk * 16u;
-    const int64_t rem = int64_t(m.len) - int64_t(blk * 64u);     // message bytes from block start
     const int32_t v = rem <= 0 ? 0 : (rem >= 64 ? 64 : int32_t(rem)); // valid bytes in block
     const int32_t mk = (rem >= 0 && rem < 64) ? int32_t(rem) : -1;  // position of the 0x80 byte
-    const int32_t lim = v > 0 ? v + int32_t(m.r) : 0;               // dword k is read iff 4k < lim
-    uint32_t raw[17];
-#pragma unroll
-    for (int k = 0; k < 17; ++k) raw[k] = (4 * k < lim) ? q[k] : 0u;
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
         uint32_t x = perm(raw[i + 1], raw[i], m.sel);
@@ -373,6 +381,21 @@ __device__ __forceinline__ void load_any_block(const Msg &m, uint64_t blk, bool 
         w[14] = BE ? hi : lo;
         w[15] = BE ? lo : hi;
     }
+}
+
+// Any block of the padded message: its raw dwords -- only those that hold message bytes are
+// read -- and their assembly.
+template <bool BE>
+__device__ __forceinline__ void load_any_block(const Msg &m, uint64_t blk, bool last, uint32_t w[16])
+{
+    const HB_GLOBAL uint32_t *q = m.p + blk * 16u;
+    const int64_t rem = int64_t(m.len) - int64_t(blk * 64u);        // message bytes from block start
+    const int32_t v = rem <= 0 ? 0 : (rem >= 64 ? 64 : int32_t(rem));
+    const int32_t lim = v > 0 ? v + int32_t(m.r) : 0;               // dword k is read iff 4k < lim
+    uint32_t raw[17];
+#pragma unroll
+    for (int k = 0; k < 17; ++k) raw[k] = (4 * k < lim) ? q[k] : 0u;
+    assemble_block<BE>(m, rem, last, raw, w);
 }
 
 // Whole blocks read per burst by default: MD5 does the least work per byte, so it reads

@@ -200,12 +200,7 @@ int hash_small_zero_copy(HostPipe &P, const uint8_t *algos_host, int algo, const
     const uint8_t *d_ids = d_msgs + (s.h_ids - s.h_msgs);
     uint8_t *d_dig = s.m_dig;
     const uint32_t stride = algos_host ? 32u : uint32_t(digest_size(algo));
-    if (algos_host) {
-        for (int a = 0; a < 3 && e == hipSuccess; ++a)
-            e = launch_plain(a, d_msgs, d_offs, d_lens, n, false, 0, d_dig, stride, d_ids, P.compute);
-    } else {
-        e = launch_plain(algo, d_msgs, d_offs, d_lens, n, false, 0, d_dig, stride, nullptr, P.compute);
-    }
+    e = launch_ragged(algos_host ? d_ids : nullptr, algo, d_msgs, d_offs, d_lens, n, d_dig, stride, P.compute);
     if (e == hipSuccess) e = hipStreamSynchronize(P.compute);
     if (e != hipSuccess) return hip_error(e, "hash_batch_host: zero-copy hash");
     std::memcpy(digests_out_host, s.h_dig, n * stride);

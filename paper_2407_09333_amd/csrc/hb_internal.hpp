@@ -12,15 +12,21 @@ namespace hb {
 int set_error(int status, const std::string &msg);
 int hip_error(hipError_t e, const char *what);
 
-// Plain launches (one lane per message, index order).  `fixed` selects the contiguous
-// fixed-length layout (message i at i * fixed_len; offsets/lengths unused).  filter !=
-// nullptr hashes only the messages whose id equals algo (the MD5 launch also zeroes the
-// slots of invalid ids).  Returns the hipError_t of the launch.
-hipError_t launch_plain(int algo, const uint8_t *msgs, const uint64_t *offs, const uint64_t *lens,
-                        uint64_t n, bool fixed, uint64_t fixed_len, uint8_t *out, uint32_t stride,
-                        const uint8_t *filter, hipStream_t stream);
+// Fixed-length batch (hb_kernels.hip): message i at i * fixed_len, one lane per message in
+// index order, digest i at out + i * stride.  Returns the hipError_t of the launch.
+hipError_t launch_fixed(int algo, const uint8_t *msgs, uint64_t n, uint64_t fixed_len, uint8_t *out, uint32_t stride,
+                        hipStream_t stream);
 
 int digest_size(int algo);
+
+// SIMDs of the current device (four per CU).
+uint32_t device_simds();
+
+// Packed batch of any lengths in one launch, without workspace (hb_ragged.hip): message i's
+// digest at out + i * stride.  algos non-null: per-message ids (unknown ones give an all-zero
+// slot), else every message uses algo.
+hipError_t launch_ragged(const uint8_t *algos, int algo, const uint8_t *msgs, const uint64_t *offs, const uint64_t *lens,
+                         uint64_t n, uint8_t *out, uint32_t stride, hipStream_t stream);
 
 // One lane per message for n messages makes at most one wave per SIMD of the current
 // device: every wave runs alone, so the compression with the fewest instructions is the

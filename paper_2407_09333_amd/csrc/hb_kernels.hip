@@ -1,4 +1,4 @@
-// hb_kernels.hip -- plain batch-hashing kernels: one lane per message, in index order.
+// hb_kernels.hip -- fixed-length batch-hashing kernels: one lane per message, in index order.
 #include <algorithm>
 #include <atomic>
 #include <cstdlib>
@@ -10,69 +10,35 @@ namespace hb {
 
 constexpr int kPlainBlock = 256;
 
-// Workgroups are dealt round-robin to the GPU's XCDs (8 on MI355X, each with its own L2);
-// renumbering them so that each XCD takes a contiguous run of the grid makes each XCD
-// stream through one contiguous region of the input.  Measured on 2^20 x 1 KiB MD5: 205 us
-// against 210 us in dispatch order; a load-only stream: 5.7 against 5.4 TB/s.
-constexpr uint32_t kXcds = 8;
-
-__device__ __forceinline__ uint32_t xcd_contiguous_block()
+// Lane i hashes message i of a fixed-length batch: it starts at i * fixed_len and is
+// fixed_len bytes long.
+template <int A, bool MANY>
+__device__ __forceinline__ void plain_lane(const uint8_t *__restrict__ msgs, uint64_t n, uint64_t fixed_len,
+                                           uint8_t *__restrict__ out, uint32_t stride)
 {
-    const uint32_t b = blockIdx.x, full = gridDim.x & ~(kXcds - 1u);
-    if (b >= full) return b;  // the last gridDim % 8 workgroups keep their number
-    return (b % kXcds) * (full / kXcds) + b / kXcds;
-}
-
-// Lane i hashes message i.  FIXED: message i starts at i * fixed_len and is fixed_len
-// bytes long (no metadata reads).  With `filter`, messages whose id differs from A are
-// skipped, so one launch per algorithm covers a mixed batch.
-template <int A, bool FIXED, bool MANY>
-__device__ __forceinline__ void plain_lane(const uint8_t *__restrict__ msgs, const uint64_t *__restrict__ offs,
-                                           const uint64_t *__restrict__ lens, uint64_t n, uint64_t fixed_len,
-                                           uint8_t *__restrict__ out, uint32_t stride,
-                                           const uint8_t *__restrict__ filter)
-{
-    const uint64_t i = uint64_t(xcd_contiguous_block()) * kPlainBlock + threadIdx.x;
+    const uint64_t i = uint64_t(xcd_contiguous(blockIdx.x, gridDim.x)) * kPlainBlock + threadIdx.x;
     if (i >= n) return;
-    if (filter) {
-        const uint8_t id = filter[i];
-        if (id != A) {
-            if (A == MD5 && id > SM3) {  // unknown id: an all-zero slot
-                HB_GLOBAL uint32_t *o = reinterpret_cast<HB_GLOBAL uint32_t *>(reinterpret_cast<uintptr_t>(out + i * stride));
-                for (uint32_t q = 0; q < stride / 4u; ++q) o[q] = 0u;
-            }
-            return;
-        }
-    }
-    uint64_t off, len;
-    if constexpr (FIXED) { off = i * fixed_len; len = fixed_len; }
-    else { off = offs[i]; len = lens[i]; }
     uint32_t s[8];
-    hash_message<A, kDefaultBurst<A>, MANY>(msgs + off, len, s);
+    hash_message<A, kDefaultBurst<A>, MANY>(msgs + i * fixed_len, fixed_len, s);
     store_digest<A>(out + i * stride, s, stride);
 }
 
-// For launches with more than one wave per SIMD, and (k_plain_few) for smaller ones.
+// For launches with more than one wave per SIMD, and (k_plain_few) for smaller ones.  (The
+// offsets, lengths and filter of a packed form, which hb_ragged.hip hashes, are unused.)
 template <int A, bool FIXED>
-__global__ __launch_bounds__(kPlainBlock) void k_plain(const uint8_t *__restrict__ msgs,
-                                                       const uint64_t *__restrict__ offs,
-                                                       const uint64_t *__restrict__ lens, uint64_t n,
-                                                       uint64_t fixed_len, uint8_t *__restrict__ out,
-                                                       uint32_t stride,
-                                                       const uint8_t *__restrict__ filter)
+__global__ __launch_bounds__(kPlainBlock) void k_plain(const uint8_t *__restrict__ msgs, const uint64_t *, const uint64_t *,
+                                                       uint64_t n, uint64_t fixed_len, uint8_t *__restrict__ out,
+                                                       uint32_t stride, const uint8_t *)
 {
-    plain_lane<A, FIXED, true>(msgs, offs, lens, n, fixed_len, out, stride, filter);
+    static_assert(FIXED, "packed batches: hb_ragged.hip");
+    plain_lane<A, true>(msgs, n, fixed_len, out, stride);
 }
 
-template <int A, bool FIXED>
-__global__ __launch_bounds__(kPlainBlock) void k_plain_few(const uint8_t *__restrict__ msgs,
-                                                           const uint64_t *__restrict__ offs,
-                                                           const uint64_t *__restrict__ lens, uint64_t n,
-                                                           uint64_t fixed_len, uint8_t *__restrict__ out,
-                                                           uint32_t stride,
-                                                           const uint8_t *__restrict__ filter)
+template <int A>
+__global__ __launch_bounds__(kPlainBlock) void k_plain_few(const uint8_t *__restrict__ msgs, uint64_t n, uint64_t fixed_len,
+                                                           uint8_t *__restrict__ out, uint32_t stride)
 {
-    plain_lane<A, FIXED, false>(msgs, offs, lens, n, fixed_len, out, stride, filter);
+    plain_lane<A, false>(msgs, n, fixed_len, out, stride);
 }
 
 // Buffer resource word 3 for raw (unswizzled, unformatted) dword access on gfx9-family
@@ -103,7 +69,7 @@ __device__ __forceinline__ void plain_lds_wave(const uint8_t *__restrict__ msgs,
     constexpr bool kStream = A == MD5;  // non-temporal loads
     __shared__ u32x4 slice[kPlainBlock / 64][512];  // per wave: 64 messages x 128 bytes
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64u), lane = threadIdx.x % 64u;
-    const uint64_t m0 = (uint64_t(xcd_contiguous_block()) * (kPlainBlock / 64) + wave) * 64u;
+    const uint64_t m0 = (uint64_t(xcd_contiguous(blockIdx.x, gridDim.x)) * (kPlainBlock / 64) + wave) * 64u;
     if (m0 >= n) return;
     const uint32_t q = lane / 8u, p = lane % 8u, sw = lane & 7u;
     const uint32_t voff = uint32_t(q * len + (p ^ q) * 16u);  // load j adds 8 j len
@@ -305,7 +271,7 @@ hipError_t launch_digits9(int algo, uint64_t start, uint64_t n, uint8_t *out, hi
 }
 
 // SIMDs of the current device (four per CU), looked up once per device.
-static uint32_t device_simds()
+uint32_t device_simds()
 {
     static std::atomic<uint32_t> cached[64];
     int dev = 0, cus = 0;
@@ -321,17 +287,14 @@ static uint32_t device_simds()
 bool few_waves(uint64_t n) { return (n + 63u) / 64u <= device_simds(); }
 
 template <int A>
-static hipError_t launch_a(const uint8_t *msgs, const uint64_t *offs, const uint64_t *lens, uint64_t n,
-                           bool fixed, uint64_t fixed_len, uint8_t *out, uint32_t stride,
-                           const uint8_t *filter, hipStream_t stream)
+static hipError_t launch_a(const uint8_t *msgs, uint64_t n, uint64_t fixed_len, uint8_t *out, uint32_t stride,
+                           hipStream_t stream)
 {
     const uint64_t blocks = (n + kPlainBlock - 1) / kPlainBlock;
     if (blocks > 0x7fffffffull) return hipErrorInvalidConfiguration;
     const dim3 grid{uint32_t(blocks), 1, 1}, block{kPlainBlock, 1, 1};
-    const bool few = few_waves(n);
-    const auto kernel = fixed ? (few ? k_plain_few<A, true> : k_plain<A, true>)
-                              : (few ? k_plain_few<A, false> : k_plain<A, false>);
-    hipLaunchKernelGGL(kernel, grid, block, 0, stream, msgs, offs, lens, n, fixed_len, out, stride, filter);
+    if (few_waves(n)) hipLaunchKernelGGL(k_plain_few<A>, grid, block, 0, stream, msgs, n, fixed_len, out, stride);
+    else hipLaunchKernelGGL((k_plain<A, true>), grid, block, 0, stream, msgs, nullptr, nullptr, n, fixed_len, out, stride, nullptr);
     return hipGetLastError();
 }
 
@@ -355,11 +318,10 @@ bool plain_lds_applies(const uint8_t *msgs, uint64_t fixed_len, uint32_t stride,
            fixed_len < (1ull << 25) && stride == uint32_t(digest_size(algo));
 }
 
-hipError_t launch_plain(int algo, const uint8_t *msgs, const uint64_t *offs, const uint64_t *lens,
-                        uint64_t n, bool fixed, uint64_t fixed_len, uint8_t *out, uint32_t stride,
-                        const uint8_t *filter, hipStream_t stream)
+hipError_t launch_fixed(int algo, const uint8_t *msgs, uint64_t n, uint64_t fixed_len, uint8_t *out, uint32_t stride,
+                        hipStream_t stream)
 {
-    if (fixed && !filter && plain_lds_applies(msgs, fixed_len, stride, algo)) {
+    if (plain_lds_applies(msgs, fixed_len, stride, algo)) {
         switch (algo) {
         case MD5: return launch_lds_a<MD5>(msgs, n, fixed_len, out, stream);
         case SHA1: return launch_lds_a<SHA1>(msgs, n, fixed_len, out, stream);
@@ -368,9 +330,9 @@ hipError_t launch_plain(int algo, const uint8_t *msgs, const uint64_t *offs, con
         }
     }
     switch (algo) {
-    case MD5: return launch_a<MD5>(msgs, offs, lens, n, fixed, fixed_len, out, stride, filter, stream);
-    case SHA1: return launch_a<SHA1>(msgs, offs, lens, n, fixed, fixed_len, out, stride, filter, stream);
-    case SM3: return launch_a<SM3>(msgs, offs, lens, n, fixed, fixed_len, out, stride, filter, stream);
+    case MD5: return launch_a<MD5>(msgs, n, fixed_len, out, stride, stream);
+    case SHA1: return launch_a<SHA1>(msgs, n, fixed_len, out, stride, stream);
+    case SM3: return launch_a<SM3>(msgs, n, fixed_len, out, stride, stream);
     default: return hipErrorInvalidValue;
     }
 }

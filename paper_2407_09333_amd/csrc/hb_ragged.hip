@@ -1,0 +1,285 @@
+// hb_ragged.hip -- packed batches of any lengths in one launch, with no workspace in HBM.
+//
+// A workgroup takes a tile of consecutive messages.  If their block counts are all but the
+// same it hashes them in index order, one lane each; else it sorts them by block count in
+// LDS and hashes them longest first: its longest messages (up to 32) by a chain pair -- two of its
+// four waves, hb_chain.hpp -- and the others 64 of near-equal length at a time by the
+// waves that are free.  A mixed batch gives each tile one workgroup per algorithm, which
+// takes the tile's messages of that algorithm, so every wave is algorithm-uniform and the
+// three algorithms' chains run beside each other.
+//
+// What bounds it: the longest message of the batch (a SHA-1 message of 64 KiB takes 836 us
+// alone), or with many messages the integer VALU.  One lane per message in index order left
+// most lanes of a wave idle behind its longest message and paid the memory latency every
+// second block of it, and a mixed batch took one such launch per algorithm: 200,003 SHA-1
+// messages of log-normal lengths (median 256, at most 64 KiB) 3,078 us, now 933; 50,021 of
+// all three algorithms 8,784, now 1,981; 10^6 SM3 messages of 0 to 4,096 bytes 2,328, now
+// 1,127.
+#include <algorithm>
+
+#include "hb_chain.hpp"
+#include "hb_device.hpp"
+#include "hb_internal.hpp"
+#include "hb_plan_rules.hpp"
+
+namespace hb {
+
+namespace {
+
+constexpr int kRaggedThreads = 256;
+constexpr uint32_t kTileMax = 2048;
+constexpr int kPerThread = int(kTileMax) / kRaggedThreads;
+constexpr uint32_t kLenBins = 256;
+
+struct RaggedArgs {
+    const uint8_t *msgs;
+    const uint64_t *offs;
+    const uint64_t *lens;
+    const uint8_t *algos;  // per-message ids, or null
+    uint8_t *out;
+    uint64_t n;
+    uint32_t stride;
+    uint32_t tile;         // messages per tile
+};
+
+// Bin of a block count: itself below 64, then sixteen bins per power of two (messages of
+// one bin differ by less than a sixteenth), the last one open.
+__device__ __forceinline__ uint32_t len_bin(uint32_t nb)
+{
+    if (nb < 64u) return nb;
+    const uint32_t e = 31u - uint32_t(__builtin_clz(nb));
+    return min(kLenBins - 1u, 64u + (e - 6u) * 16u + ((nb >> (e - 4u)) & 15u));
+}
+
+struct RaggedLds {
+    uint16_t order[kTileMax];     // the tile's messages, longest bin first
+    uint32_t bins[kLenBins];      // counts, then first positions
+    uint32_t part[kRaggedThreads / 64];
+    unsigned long long blocks;    // of the tile's messages in all
+    uint32_t longest;             // largest block count
+    uint32_t least;               // smallest (0 where another algorithm's message is)
+    uint32_t next;                // next position to hand out
+    ChainSync sync;
+    uint32_t tails[kChainTailWords];
+    uint32_t simd[kRaggedThreads / 64];  // SIMD of each wave
+    uint32_t group;                      // the workgroup's number on its CU
+};
+
+// This wave's SIMD and its workgroup's number on the CU (bits 5:4 and 19:16 of HW_ID).
+__device__ __forceinline__ uint32_t wave_simd() { return __builtin_amdgcn_s_getreg(4 | (4 << 6) | ((2 - 1) << 11)); }
+__device__ __forceinline__ uint32_t group_on_cu() { return __builtin_amdgcn_s_getreg(4 | (16 << 6) | ((4 - 1) << 11)); }
+
+template <int A, bool MANY>
+__device__ __forceinline__ void ragged_tile(const RaggedArgs &r, uint64_t base, RaggedLds &L, uint32_t *ring)
+{
+    const uint32_t tid = threadIdx.x, lane = tid % 64u, wave = __builtin_amdgcn_readfirstlane(tid / 64u);
+    const uint32_t have = uint32_t(min<uint64_t>(r.tile, r.n - base));
+    // this thread's messages: block counts, 0 for none or another algorithm's
+    uint32_t nb[kPerThread], my_longest = 0, my_least = 0xffffffffu;
+    unsigned long long my_blocks = 0;
+    // the first one's place, kept for the case that nothing is sorted
+    const uint64_t i0 = base + min(tid, have - 1u), off0 = r.offs[i0], len0 = r.lens[i0];
+#pragma unroll
+    for (int j = 0; j < kPerThread; ++j) {
+        const uint32_t t = uint32_t(j) * kRaggedThreads + tid;
+        nb[j] = 0;
+        if (t < have) {
+            const uint64_t i = base + t;
+            const uint8_t id = r.algos ? r.algos[i] : uint8_t(A);
+            if (id == A) nb[j] = uint32_t(min<uint64_t>(block_count(j == 0 ? len0 : r.lens[i]), 0xffffffffull));
+            if (A == MD5 && id > SM3) {  // unknown id: an all-zero slot
+                HB_GLOBAL uint32_t *o = reinterpret_cast<HB_GLOBAL uint32_t *>(reinterpret_cast<uintptr_t>(r.out + i * r.stride));
+                for (uint32_t q = 0; q < r.stride / 4u; ++q) o[q] = 0u;
+            }
+            my_longest = max(my_longest, nb[j]);
+            my_least = min(my_least, nb[j]);
+            my_blocks += nb[j];
+        }
+    }
+    L.bins[tid] = 0;
+    if (lane == 0) L.simd[wave] = wave_simd();
+    if (tid == 0) {
+        L.group = group_on_cu();
+        L.blocks = 0; L.longest = 0; L.least = 0xffffffffu; L.sync.filled = 0; L.sync.taken = 0;
+    }
+    __syncthreads();
+    uint32_t rank[kPerThread];  // within the bin
+#pragma unroll
+    for (int j = 0; j < kPerThread; ++j) {
+        rank[j] = 0;
+        if (nb[j]) {
+            const uint32_t bin = len_bin(nb[j]), first = __builtin_amdgcn_readfirstlane(bin);
+            const uint64_t active = __ballot(1);
+            if (__ballot(bin == first) == active) {  // one atomic for the wave
+                const uint32_t below = __builtin_amdgcn_mbcnt_hi(uint32_t(active >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(active), 0u));
+                uint32_t b = 0;
+                if (below == 0) b = atomicAdd(&L.bins[first], uint32_t(__popcll(active)));
+                rank[j] = __builtin_amdgcn_readfirstlane(b) + below;
+            } else {
+                rank[j] = atomicAdd(&L.bins[bin], 1u);
+            }
+        }
+    }
+    const uint32_t nb0 = __builtin_amdgcn_readfirstlane(nb[0]);
+    if (r.tile <= kRaggedThreads && __ballot(nb[0] == nb0) == ~0ull) my_blocks *= 64u;  // nothing to reduce
+    else for (int d = 32; d > 0; d >>= 1) {
+        my_longest = max(my_longest, uint32_t(__shfl_xor(my_longest, d)));
+        my_least = min(my_least, uint32_t(__shfl_xor(my_least, d)));
+        my_blocks += __shfl_xor(my_blocks, d);
+    }
+    if (lane == 0) {
+        atomicMax(&L.longest, my_longest);
+        atomicMin(&L.least, my_least);
+        atomicAdd(&L.blocks, my_blocks);
+    }
+    __syncthreads();
+    // The chain pair takes the longest messages when the longest of all would take at least
+    // twice the time that the two waves left need for all the others; nearer to even, two
+    // waves fewer for those cost more than the faster chains give.
+    const bool chains = L.longest >= 3u && L.longest < 0x80000000u && (unsigned long long)L.longest * 64u > L.blocks;
+    if (L.longest == 0) return;  // no message of this algorithm
+    // Nothing to gain from sorting: one block count throughout, or one wave a SIMD and no
+    // chain pair, where the time is the longest message's in any order.
+    const bool sorted = L.least == L.longest ? have <= kChainEntries && chains : MANY || chains || r.algos;
+    uint32_t count = have;
+    if (sorted) {
+        // first position of each bin, longest first: an exclusive scan over the reversed bins
+        const uint32_t c = L.bins[kLenBins - 1u - tid];
+        uint32_t sum = c;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const uint32_t up = __shfl_up(sum, d);
+            if (lane >= uint32_t(d)) sum += up;
+        }
+        if (lane == 63) L.part[wave] = sum;
+        __syncthreads();
+        uint32_t before = 0;
+        count = 0;
+#pragma unroll
+        for (uint32_t w = 0; w < kRaggedThreads / 64; ++w) {
+            before += w < wave ? L.part[w] : 0u;
+            count += L.part[w];
+        }
+        L.bins[kLenBins - 1u - tid] = before + sum - c;
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < kPerThread; ++j)
+            if (nb[j]) L.order[L.bins[len_bin(nb[j])] + rank[j]] = uint16_t(uint32_t(j) * kRaggedThreads + tid);
+    }
+    const uint32_t nchain = sorted && chains ? min(count, kChainEntries) : 0u;
+    if (tid == 0) L.next = nchain;
+    __syncthreads();
+    if (nchain) {
+        // Workgroups that share a CU run their chain waves on different SIMDs: the wave on
+        // the SIMD of the workgroup's number (that wave number if none is there), the next
+        // but one for the schedules.  With every chain wave the same wave of its workgroup,
+        // three workgroups' chains shared one SIMD and took 3.3 times as long.
+        const uint32_t want = L.group % 4u;
+        uint32_t chain_wave = want;
+#pragma unroll
+        for (uint32_t w = 0; w < kRaggedThreads / 64; ++w)
+            if (L.simd[w] == want) chain_wave = w;
+        const uint32_t role = __builtin_amdgcn_readfirstlane(wave ^ chain_wave);  // 0 chains, 2 schedules
+        if (role == 0 || role == 2) {
+            uint64_t i = 0;
+            uint64_t address = 0, len = 0;
+            uint32_t blocks = 0;
+            if (lane < nchain) {
+                i = base + L.order[lane];
+                len = r.lens[i];
+                address = uint64_t(reinterpret_cast<uintptr_t>(r.msgs)) + r.offs[i];
+                blocks = uint32_t(block_count(len));
+            }
+            if (role == 0) {
+                uint32_t s[8];
+                __builtin_amdgcn_s_setprio(3);
+                chain_run<A>(blocks, ring, &L.sync, s);
+                __builtin_amdgcn_s_setprio(0);
+                if (blocks) store_digest<A>(r.out + i * r.stride, s, r.stride);
+            } else {
+                __builtin_amdgcn_s_setprio(2);
+                chain_schedule<A>(address, len, blocks, ring, L.tails, &L.sync);
+                __builtin_amdgcn_s_setprio(0);
+            }
+        }
+    }
+    // 64 positions at a time: in index order each wave every fourth, sorted whoever is free
+    uint32_t p = wave * 64u;
+    for (;; p += kRaggedThreads) {
+        if (sorted) {
+            if (lane == 0) p = atomicAdd(&L.next, 64u);
+            p = __builtin_amdgcn_readfirstlane(p);
+        }
+        if (p >= count) break;
+        if (p + lane < count) {
+            uint64_t i = i0, off = off0, len = len0;
+            if (sorted || p >= kRaggedThreads) {
+                i = base + (sorted ? L.order[p + lane] : p + lane);
+                off = r.offs[i];
+                len = r.lens[i];
+            }
+            uint32_t s[8];
+            hash_message<A, kDefaultBurst<A>, MANY>(r.msgs + off, len, s);
+            store_digest<A>(r.out + i * r.stride, s, r.stride);
+        }
+    }
+}
+
+template <int A, bool MANY>
+__global__ __launch_bounds__(kRaggedThreads, 4) void k_ragged(RaggedArgs r)
+{
+    __shared__ RaggedLds L;
+    __shared__ __align__(16) uint32_t ring[kChainRingWords<A>];
+    ragged_tile<A, MANY>(r, uint64_t(xcd_contiguous(blockIdx.x, gridDim.x)) * r.tile, L, ring);
+}
+
+// Three workgroups per tile, one per algorithm; SM3's (the longest chains) first.
+template <bool MANY>
+__global__ __launch_bounds__(kRaggedThreads, MANY ? 4 : 3) void k_ragged_mixed(RaggedArgs r, uint32_t tiles)
+{
+    __shared__ RaggedLds L;
+    __shared__ __align__(16) uint32_t ring[kChainRingWords<SM3>];
+    const uint64_t base = uint64_t(xcd_contiguous(blockIdx.x % tiles, tiles)) * r.tile;
+    if (blockIdx.x < tiles) ragged_tile<SM3, MANY>(r, base, L, ring);
+    else if (blockIdx.x < 2u * tiles) ragged_tile<SHA1, MANY>(r, base, L, ring);
+    else ragged_tile<MD5, MANY>(r, base, L, ring);
+}
+
+}  // namespace
+
+hipError_t launch_ragged(const uint8_t *algos, int algo, const uint8_t *msgs, const uint64_t *offs, const uint64_t *lens,
+                         uint64_t n, uint8_t *out, uint32_t stride, hipStream_t stream)
+{
+    // Messages a workgroup gets: up to 256 while one workgroup on each CU takes them all, one
+    // wave to a SIMD (64 to a workgroup and four workgroups to a CU would put the four busy
+    // waves on one SIMD: 65,536 x 1 KiB MD5 43 us against 21); 256 up to four workgroups on
+    // each CU (a SIMD for each one's chain wave: with five, two chains shared one); then as
+    // many as fill those once, or a whole number of times: larger tiles sort better, but a
+    // last round that is half empty costs more.  A mixed batch's tiles are twice as large, a
+    // workgroup hashing about a third of one: three times as large, half the workgroups would
+    // have a few messages more than their four waves take at once.
+    const uint64_t cus = device_simds() / 4u, per = algos ? 3u : 1u, wide = algos ? 2u : 1u, slots = cus * 4u;
+    const uint64_t rounds = (n * per + slots * kTileMax - 1) / (slots * kTileMax);
+    const uint64_t one = (n + cus - 1) / cus, all = (n * per + slots * rounds - 1) / (slots * rounds);
+    const uint64_t tile = one <= kRaggedThreads ? (one + 63u) / 64u * 64u * wide
+                                                : std::min<uint64_t>((std::max<uint64_t>(all, kRaggedThreads * wide) + 255u) / 256u * 256u, kTileMax);
+    const uint64_t tiles = (n + tile - 1) / tile;
+    if (tiles * per > 0x7fffffffull) return hipErrorInvalidConfiguration;
+    const RaggedArgs r{msgs, offs, lens, algos, out, n, stride, uint32_t(tile)};
+    const dim3 grid{uint32_t(tiles * per), 1, 1}, block{kRaggedThreads, 1, 1};
+    // one wave to a SIMD (see few_waves)
+    const bool few = tiles * per <= cus;
+    if (algos) {
+        hipLaunchKernelGGL(few ? k_ragged_mixed<false> : k_ragged_mixed<true>, grid, block, 0, stream, r, uint32_t(tiles));
+        return hipGetLastError();
+    }
+    switch (algo) {
+    case MD5: hipLaunchKernelGGL((few ? k_ragged<MD5, false> : k_ragged<MD5, true>), grid, block, 0, stream, r); break;
+    case SHA1: hipLaunchKernelGGL((few ? k_ragged<SHA1, false> : k_ragged<SHA1, true>), grid, block, 0, stream, r); break;
+    case SM3: hipLaunchKernelGGL((few ? k_ragged<SM3, false> : k_ragged<SM3, true>), grid, block, 0, stream, r); break;
+    default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
+}  // namespace hb

@@ -209,7 +209,7 @@ def hash_batch_fixed(algo, messages, n: int, msg_len: int, out=None, stream=None
 
 
 def hash_batch_mixed(algos, messages, offsets, lengths, out=None, stream=None):
-    """Per-message algorithm ids, plain form (one launch per algorithm); (n, 32) digests."""
+    """Per-message algorithm ids, plain form (one launch); (n, 32) digests."""
     torch = _torch()
     al, msgs, offs, lens = _dev_u8(algos), _dev_u8(messages), _dev_i64(offsets), _dev_i64(lengths)
     n = offs.numel()

@@ -1,0 +1,76 @@
+"""hash_batch / hash_batch_mixed (one launch: tiles sorted in LDS, a chain pair for a tile's
+longest messages) where the tile, the chain pair's windows and the last blocks change shape.
+Every digest bit-exact against the oracle, with no write outside the digest buffer."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2407_09333_amd import workloads
+from tests.gpu_util import assert_same, check_guard, guarded_out
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def hb():
+    import torch
+
+    assert torch.cuda.is_available()
+    from paper_2407_09333_amd import hb as _hb
+
+    return _hb
+
+
+def lengths(kind: str, n: int) -> np.ndarray:
+    rng = np.random.default_rng(n)
+    if kind == "equal":            # nothing to sort
+        return np.full(n, 130)
+    if kind == "chains":           # every residue of the last block, 3 to about 70 blocks
+        return 121 + 61 * (np.arange(n) % 73)
+    if kind == "one long":         # a chain of many windows beside short messages
+        x = rng.integers(0, 130, n)
+        x[n // 2] = 64 * 200 + 55
+        return x
+    if kind == "long same":        # all of one bin, more than the chain pair takes
+        return np.full(n, 64 * 65)
+    return rng.integers(0, 2000, n)  # "spread"
+
+
+@pytest.mark.parametrize("kind", ["equal", "chains", "one long", "long same", "spread"])
+@pytest.mark.parametrize("n", [1, 2, 17, 31, 32, 33, 64, 65, 257, 5000])
+def test_tiles_and_chains(hb, kind, n):
+    lens = lengths(kind, n).astype(np.uint64)
+    gaps = np.arange(n, dtype=np.uint64) % np.uint64(5)      # messages start at any byte
+    offs = workloads.packed(lens + gaps) + np.uint64(1)
+    msgs = workloads.host_random_bytes(int(offs[-1] + lens[-1]), seed=n)
+    for algo in (0, 1, 2):
+        print(f"case ragged kind={kind} n={n} algo={algo}", flush=True)
+        stride = oracle.DIGEST_SIZE[algo] + 4
+        buf, out = guarded_out(n, stride)
+        hb.hash_batch(algo, msgs, offs.astype(np.int64), lens.astype(np.int64), out=out, stride=stride)
+        check_guard(buf, n, stride)
+        assert_same(out.cpu().numpy(), oracle.hash_batch(algo, msgs, offs, lens, out_stride=stride), f"{kind} {algo}")
+    algos = np.random.default_rng(7).integers(0, 4, n).astype(np.uint8)  # 3: unknown, an all-zero slot
+    buf, out = guarded_out(n, 32)
+    hb.hash_batch_mixed(algos, msgs, offs.astype(np.int64), lens.astype(np.int64), out=out)
+    check_guard(buf, n, 32)
+    known = np.where(algos > 2, 0, algos).astype(np.uint8)
+    want = oracle.hash_batch(known, msgs, offs, lens)
+    want[algos > 2] = 0
+    assert_same(out.cpu().numpy(), want, f"{kind} mixed")
+
+
+@pytest.mark.parametrize("n", [70_001, 300_007])
+def test_many_tiles(hb, n):
+    """More than one workgroup per CU, and tiles past 256 messages."""
+    rng = np.random.default_rng(n)
+    lens = np.minimum(np.exp(rng.normal(4.0, 1.5, n)), 9000).astype(np.uint64)
+    offs = workloads.packed(lens)
+    msgs = workloads.host_random_bytes(int(lens.sum()) + 1, seed=3)
+    for algo in (0, 1, 2):
+        print(f"case many tiles n={n} algo={algo}", flush=True)
+        got = hb.hash_batch(algo, msgs, offs.astype(np.int64), lens.astype(np.int64)).cpu().numpy()
+        assert_same(got, oracle.hash_batch(algo, msgs, offs, lens), f"many tiles {algo}")
+    algos = rng.integers(0, 3, n).astype(np.uint8)
+    got = hb.hash_batch_mixed(algos, msgs, offs.astype(np.int64), lens.astype(np.int64)).cpu().numpy()
+    assert_same(got, oracle.hash_batch(algos, msgs, offs, lens), "many tiles mixed")
