@@ -184,19 +184,25 @@ enum {
  * build the launch plan.  The plan owns its workspace (about 4 bytes per message, a fixed
  * part of about 0.6 MB, and -- unless HB_PLAN_NO_LONG -- a long-chain scratch of
  * HB_LONG_SCRATCH_MB MiB, default 1024) and, with HB_PLAN_GRAPH, a hipGraph captured on
- * first run.  Long-chain path: messages of at least HB_LONG_MIN_BLOCKS blocks (default 256,
- * i.e. about 16 KiB) have every block's schedule words computed block-parallel first, then
- * run as rounds-only chains in a high-priority kernel beside the bulk kernel (a message's
- * blocks are strictly sequential, so this shortens the critical path, not the work);
- * those the scratch cannot hold run there as ordinary chains, at most one wave per SIMD
- * (the longest by blocks x ops per block), and when the longest chain dwarfs the rest the
- * bulk kernel runs on only as many waves as finish its work in 1/HB_BULK_MARGIN (default
- * 4; 0 = all waves) of that chain's time.  With HB_PLAN_LONG_INLINE the long-chain work
- * and the bulk run in one launch on the run's own stream (the long chains' workgroups
- * first), with the same concurrency and no side stream, for callers that keep several
- * plans busy on streams of their own and have no hardware queue to spare for each; that
- * launch takes the long-chain kernel's register budget, so its bulk waves run at lower
- * occupancy.  Returns HB_ENOMEM if the workspace cannot be allocated.
+ * the pipeline's first run.  By default a run is hash_batch's tiled launch; when the batch
+ * has more tiles than the GPU holds at once, its longest messages (of at least
+ * HB_LONG_MIN_BLOCKS blocks, default 256, and unless HB_PLAN_NO_LONG) are picked out on the
+ * device first and started ahead of the tiles.  The pipeline runs instead in plans with
+ * launch choices (hb_plan_set_config, HB_WAVES_PER_CU, HB_PLAN_AUTOTUNE where it finds the
+ * pipeline faster) and with HB_PLAN_NO_SORT.  Its long-chain path: messages of at least
+ * HB_LONG_MIN_BLOCKS blocks (i.e. about 16 KiB) have every block's schedule words computed
+ * block-parallel first, then run as rounds-only chains in a kernel of their own beside the
+ * bulk kernel (a message's blocks are strictly sequential, so this shortens the critical
+ * path, not the work); those the scratch cannot hold run there as ordinary chains, at most
+ * one wave per SIMD (the longest by blocks x ops per block), and when the longest chain
+ * dwarfs the rest the bulk kernel runs on only as many waves as finish its work in
+ * 1/HB_BULK_MARGIN (default 4; 0 = all waves) of that chain's time.  With
+ * HB_PLAN_LONG_INLINE the long-chain work and the bulk run in one launch on the run's own
+ * stream (the long chains' workgroups first), with the same concurrency and no side stream,
+ * for callers that keep several plans busy on streams of their own and have no hardware
+ * queue to spare for each; that launch takes the long-chain kernel's register budget, so its
+ * bulk waves run at lower occupancy.  Returns HB_ENOMEM if the workspace cannot be
+ * allocated.
  */
 int hb_plan_create(hb_plan **plan, uint64_t max_n, int flags);
 
@@ -204,12 +210,11 @@ int hb_plan_create(hb_plan **plan, uint64_t max_n, int flags);
  * hb_plan_run -- hash n <= max_n messages.  algos (device, n x uint8) gives per-message
  * algorithm ids; when algos is NULL every message uses algo.  digests_out stride is 32
  * bytes when algos != NULL, else hb_digest_size(algo).  Other arguments as hash_batch.
- * The steps (all on the device, in stream order): per-message block count
+ * The pipeline's steps (all on the device, in stream order): per-message block count
  * nb = floor((L + 8) / 64) + 1; counting sort by (algorithm, nb) descending; work items
  * of one wave each (algorithm-uniform lanes of near-equal nb); items merged by estimated
- * cost, longest first; one persistent launch whose waves pull items from an atomic queue.
- * Messages of at least HB_LONG_MIN_BLOCKS blocks take the long-chain path (see
- * hb_plan_create).  Per-run pointers and sizes reach the device through a one-thread
+ * cost, longest first; one persistent launch whose waves pull items from an atomic queue
+ * (hb_plan_create says when a run is the pipeline and when the tiled launch).  Per-run pointers and sizes reach the device through a one-thread
  * kernel launched ahead of the pipeline with them as arguments, so a captured graph is
  * replayed unchanged and consecutive runs need no host synchronisation.  Calls on one plan
  * must be serialised by the caller (a plan is not thread-safe) and one plan's runs must
@@ -219,24 +224,24 @@ int hb_plan_run(hb_plan *plan, const uint8_t *algos, int algo, const uint8_t *me
                 const uint64_t *offsets, const uint64_t *lengths, uint64_t n,
                 uint8_t *digests_out, void *stream);
 
-/* Launch choices of a plan (after autotuning, if enabled): persistent-kernel waves per CU,
- * messages per lane per work item, and the message-load scheme `variant`:
+/* Launch choices of a plan's pipeline (after autotuning, if enabled): persistent-kernel waves
+ * per CU, messages per lane per work item, and the message-load scheme `variant`:
  *   0  whole blocks in bursts of the default depth (MD5 four, SHA-1 / SM3 two) -- default
  *   1  SHA-1 / SM3 one block at a time with the next block's loads in flight; MD5 as 0
  *   2  one block per load
  *   3  bursts of two whole blocks for every algorithm
  *   4  bursts of four whole blocks for every algorithm
  * With HB_PLAN_AUTOTUNE the first run times waves per CU {8, 16, 32} x messages per lane
- * {1, 2} x the five schemes on its own input and keeps the fastest, cached per device, CU
+ * {1, 2} x the five schemes and the tiled launch on its own input and keeps the fastest, cached per device, CU
  * count, algorithm mix and length bucket (mean block count and spread, read from the
  * plan's histogram); HB_TUNE_CACHE names a file that keeps the cache across processes. */
 int hb_plan_config(const hb_plan *plan, int *waves_per_cu, int *msgs_per_lane, int *variant);
 
-/* Force launch choices (0 keeps the current waves per CU / messages per lane; variant is
- * set as given, 0..4); drops any captured graph.  HB_EINVAL outside those ranges. */
+/* Force launch choices, and so the pipeline (0 keeps the current waves per CU / messages per
+ * lane; variant is set as given, 0..4); drops any captured graph.  HB_EINVAL outside those ranges. */
 int hb_plan_set_config(hb_plan *plan, int waves_per_cu, int msgs_per_lane, int variant);
 
-/* Average duration in milliseconds of the persistent hashing kernel over the runs since
+/* Average duration in milliseconds of the hashing launch over the runs without a graph since
  * the last call, measured with HIP events around it on the plan's stream; -1 if none. */
 double hb_plan_kernel_ms(hb_plan *plan);
 
@@ -245,17 +250,11 @@ void hb_plan_destroy(hb_plan *plan);
 /*
  * hash_batch_bucketed_noalloc -- for callers that cannot allocate (code under hipGraph
  * capture, serving loops and harnesses that forbid hipMalloc): the batched form of
- * hb_plan_run without a plan.  Same arguments, digests and steps as hb_plan_run with
- * HB_PLAN_LONG_INLINE (bucketing, longest-first persistent launch, long chains beside the
- * bulk in one launch), except that every long chain is a direct chain (no schedule
- * scratch) and nothing is captured in a graph.  The workspace is a static device array of
- * about 4.6 MiB that each GPU the library runs on holds until the process ends; the first
- * call on a device looks up its address there.  No call allocates or frees memory.
+ * hb_plan_run without a plan, as one tiled launch (see hash_batch).  Same arguments and
+ * digests as hb_plan_run.  No call allocates or frees memory, and none holds any between
+ * calls, so calls may overlap on one GPU.
  *   n            at most 2^20 messages: larger n returns HB_EINVAL before anything is
  *                enqueued
- * Every call on a GPU uses that GPU's one array (each run clears what it needs first), so
- * calls that overlap on one GPU -- on different streams or from different threads --
- * race and give wrong digests: serialise them, for example on one stream.
  */
 int hash_batch_bucketed_noalloc(const uint8_t *algos, int algo, const uint8_t *messages,
                                 const uint64_t *offsets, const uint64_t *lengths, uint64_t n,

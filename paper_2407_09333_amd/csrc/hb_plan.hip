@@ -1,8 +1,11 @@
-// hb_plan.hip -- batched form: on-device bucketing by (algorithm, block count), work items
-// of one wave each ordered longest first, and one persistent fused launch whose waves pull
-// items from an atomic queue.  The pipeline is captured once in a hipGraph and replayed;
-// per-run pointers reach the captured kernels through a device-side parameter block that
-// a small kernel, launched ahead of the graph, fills from its own launch arguments.
+// hb_plan.hip -- batched form.  By default a run is the tiled launch of hb_ragged.hip, with the
+// longest messages picked out first when the batch has more tiles than the chip holds at once.
+// With launch choices of the caller's or the autotuner's, or without sorting, it is the
+// pipeline below: on-device bucketing by (algorithm, block count), work items of one wave
+// each ordered longest first, and one persistent fused launch whose waves pull items from an
+// atomic queue.  The pipeline is captured once in a hipGraph and replayed; per-run pointers
+// reach the captured kernels through a device-side parameter block that a small kernel,
+// launched ahead of the graph, fills from its own launch arguments.
 #include <hip/hip_runtime.h>
 
 #include <atomic>
@@ -20,6 +23,7 @@
 #include "hb_internal.hpp"
 #include "hb_long.hpp"
 #include "hb_plan_rules.hpp"
+#include "hb_ragged.hpp"
 
 namespace hb {
 
@@ -742,6 +746,7 @@ struct TuneChoice {
     int waves_per_cu;
     int mpl;
     int variant;
+    bool tiles;  // the tiled launch is faster than the pipeline at those choices
 };
 
 static std::mutex g_tune_mu;
@@ -749,7 +754,8 @@ static std::map<TuneKey, TuneChoice> g_tune_cache;
 static bool g_tune_loaded = false;
 
 // Optional persistence: HB_TUNE_CACHE names a text file of lines
-// "arch cus algo_mask length_bucket waves_per_cu msgs_per_lane variant".
+// "arch cus algo_mask length_bucket waves_per_cu msgs_per_lane variant tiles"; a line without
+// the last number names the pipeline.
 static void load_tune_cache()
 {
     std::lock_guard<std::mutex> g(g_tune_mu);
@@ -759,11 +765,14 @@ static void load_tune_cache()
     if (!path) return;
     FILE *f = std::fopen(path, "r");
     if (!f) return;
-    char arch[64];
-    int cus, mask, bucket, w, m, v;
-    while (std::fscanf(f, "%63s %d %d %d %d %d %d", arch, &cus, &mask, &bucket, &w, &m, &v) == 7)
-        if (w > 0 && w <= 64 && m > 0 && m <= kMaxMpl && v >= 0 && v < kLoadSchemes)
-            g_tune_cache[TuneKey{arch, cus, mask, bucket}] = TuneChoice{w, m, v};
+    char arch[64], line[256];
+    int cus, mask, bucket, w, m, v, t;
+    while (std::fgets(line, sizeof(line), f)) {
+        t = 0;
+        if (std::sscanf(line, "%63s %d %d %d %d %d %d %d", arch, &cus, &mask, &bucket, &w, &m, &v, &t) >= 7 && w > 0 &&
+            w <= 64 && m > 0 && m <= kMaxMpl && v >= 0 && v < kLoadSchemes)
+            g_tune_cache[TuneKey{arch, cus, mask, bucket}] = TuneChoice{w, m, v, t == 1};
+    }
     std::fclose(f);
 }
 
@@ -775,8 +784,8 @@ static void save_tune_cache()
     FILE *f = std::fopen(path, "w");
     if (!f) return;
     for (auto &kv : g_tune_cache)
-        std::fprintf(f, "%s %d %d %d %d %d %d\n", kv.first.arch.c_str(), kv.first.cus, kv.first.algo_mask,
-                     kv.first.len_bucket, kv.second.waves_per_cu, kv.second.mpl, kv.second.variant);
+        std::fprintf(f, "%s %d %d %d %d %d %d %d\n", kv.first.arch.c_str(), kv.first.cus, kv.first.algo_mask,
+                     kv.first.len_bucket, kv.second.waves_per_cu, kv.second.mpl, kv.second.variant, int(kv.second.tiles));
     std::fclose(f);
 }
 
@@ -792,6 +801,8 @@ struct hb_plan {
     int mpl = 1;
     int variant = 0;
     bool tuned = false;
+    bool tiles = true;              // runs are the tiled launch, not the pipeline
+    hb::LongWs long_ws{};           // its workspace for batches of more than one round of tiles
     int tune_bucket = -1;           // length bucket the autotuner keyed its choice by
     hipStream_t cap_stream = nullptr;
     hipGraph_t graph = nullptr;
@@ -935,8 +946,14 @@ static hipError_t enqueue_pipeline(hb_plan *p, hipStream_t s, bool timed)
     return hipGetLastError();
 }
 
+static hipError_t enqueue_tiles(hb_plan *p, const PlanDesc &d, hipStream_t s, bool timed);
+
 static int launch_run(hb_plan *p, const PlanDesc &d, hipStream_t s)
 {
+    if (p->tiles && d.sort) {
+        const hipError_t te = enqueue_tiles(p, d, s, (p->flags & HB_PLAN_GRAPH) == 0);
+        return te == hipSuccess ? HB_OK : hip_error(te, "hb_plan_run: launch");
+    }
     hipLaunchKernelGGL(k_set_desc, dim3(1), dim3(1), 0, s, d, p->ws.desc);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_error(e, "hb_plan_run: parameter kernel");
@@ -962,6 +979,26 @@ static int launch_run(hb_plan *p, const PlanDesc &d, hipStream_t s)
     e = enqueue_pipeline(p, s, true);
     if (e != hipSuccess) return hip_error(e, "hb_plan_run: launch");
     return HB_OK;
+}
+
+// The tiled launch.  The longest messages are picked out first only for a batch of more than
+// one round of tiles: in one, every message starts at once (SM3, 2^22 messages of log-normal
+// lengths up to 64 KiB, two rounds: 6.2 ms without, 1e6 messages up to 1 MiB, one round: the
+// longest message's own 27.9 ms either way).
+static hipError_t enqueue_tiles(hb_plan *p, const PlanDesc &d, hipStream_t s, bool timed)
+{
+    std::pair<hipEvent_t, hipEvent_t> ev{nullptr, nullptr};
+    if (timed) ev = take_events(p);
+    if (ev.first) hipEventRecord(ev.first, s);
+    const hipError_t e = p->long_on && !ragged_in_one_round(d.n, d.algos != nullptr)
+                             ? launch_ragged_long(p->long_ws, d.algos, d.algo, d.msgs, d.offs, d.lens, d.n, d.out, d.stride, s)
+                             : launch_ragged(d.algos, d.algo, d.msgs, d.offs, d.lens, d.n, d.out, d.stride, s);
+    if (ev.first) {
+        hipEventRecord(ev.second, s);
+        p->ev_pending.push_back(ev);
+        if (p->ev_pending.size() > 64) collect_timing(p, false);
+    }
+    return e;
 }
 
 // Length bucket of a batch, from the plan's own histogram of (algorithm, block count)
@@ -995,6 +1032,7 @@ static int autotune(hb_plan *p, const PlanDesc &d0, hipStream_t s, int algo_mask
 {
     const int flags_saved = p->flags;
     p->flags &= ~HB_PLAN_GRAPH;
+    p->tiles = false;
     // one run with the current choice fills the histogram that names the length bucket
     PlanDesc d = d0;
     d.mpl = p->mpl;
@@ -1010,13 +1048,14 @@ static int autotune(hb_plan *p, const PlanDesc &d0, hipStream_t s, int algo_mask
             p->waves_per_cu = it->second.waves_per_cu;
             p->mpl = it->second.mpl;
             p->variant = it->second.variant;
+            p->tiles = it->second.tiles;
             p->flags = flags_saved;
             p->tune_bucket = key.len_bucket;
             return HB_OK;
         }
     }
     float best = 1e30f;
-    TuneChoice bestc{p->waves_per_cu, p->mpl, p->variant};
+    TuneChoice bestc{p->waves_per_cu, p->mpl, p->variant, false};
     const int wpcs[] = {8, 16, 32};
     const int mpls[] = {1, 2};
     hipEvent_t a = nullptr, b = nullptr;
@@ -1040,8 +1079,20 @@ static int autotune(hb_plan *p, const PlanDesc &d0, hipStream_t s, int algo_mask
                     hipEventElapsedTime(&ms, a, b);
                     if (rep) tot += ms;  // first repetition is a warm-up
                 }
-                if (rc == HB_OK && tot < best) { best = tot; bestc = TuneChoice{w, mpl, var}; }
+                if (rc == HB_OK && tot < best) { best = tot; bestc = TuneChoice{w, mpl, var, false}; }
             }
+    if (d.sort) {  // and the tiled launch
+        p->tiles = true;
+        float tot = 0.f;
+        for (int rep = 0; rep < 2 && rc == HB_OK; ++rep) {
+            hipEventRecord(a, s);
+            rc = launch_run(p, d, s);
+            hipEventRecord(b, s);
+            hipEventSynchronize(b);
+            hipEventElapsedTime(&tot, a, b);
+        }
+        bestc.tiles = rc == HB_OK && tot < best;
+    }
     hipEventDestroy(a);
     hipEventDestroy(b);
     collect_timing(p, true);
@@ -1051,6 +1102,7 @@ static int autotune(hb_plan *p, const PlanDesc &d0, hipStream_t s, int algo_mask
     p->waves_per_cu = bestc.waves_per_cu;
     p->mpl = bestc.mpl;
     p->variant = bestc.variant;
+    p->tiles = bestc.tiles;
     p->tune_bucket = key.len_bucket;
     if (rc != HB_OK) return rc;
     {
@@ -1061,88 +1113,7 @@ static int autotune(hb_plan *p, const PlanDesc &d0, hipStream_t s, int algo_mask
     return HB_OK;
 }
 
-// ---------------------------------------------------------------------------------------
-// Allocation-free batched run: the plan's pipeline on a workspace that lives in a static
-// device array, for callers that cannot allocate (code under graph capture, serving loops
-// that must not call the allocator).  Long chains run as direct chains beside the bulk in
-// one launch (no schedule scratch), at most kStaticMaxN messages per call.
-// ---------------------------------------------------------------------------------------
-
-constexpr uint64_t kStaticMaxN = 1ull << 20;
-constexpr uint64_t kStaticLongWaves = 3;  // no scheduled long waves: wave_base holds only the end
-constexpr uint64_t up256(uint64_t x) { return (x + 255) & ~uint64_t(255); }
-constexpr uint64_t kStaticDesc = up256(sizeof(PlanDesc)), kStaticMeta = up256(sizeof(PlanMeta));
-constexpr uint64_t kStaticBins = up256(3ull * kBins * 4);
-constexpr uint64_t kStaticSorted = up256((kStaticMaxN + 3ull * 64 * kMaxMpl) * 4);
-constexpr uint64_t kStaticOrder = up256((kStaticMaxN / 64 + 4) * 4);
-constexpr uint64_t kStaticWaveBase = up256((kStaticLongWaves + 1) * 4);
-constexpr uint64_t kStaticBytes =
-    kStaticDesc + kStaticMeta + 3 * kStaticBins + kStaticSorted + kStaticOrder + kStaticWaveBase;
-
-// The workspace: one copy per device, held until the process ends.  Host code never uses
-// this name as an address (on the host it is only a handle); it uses the device address
-// that hipGetSymbolAddress returns for the current device.
-static __device__ __align__(256) uint8_t scratch[kStaticBytes];
-
-constexpr int kStaticDevices = 64;
-
-struct StaticDevice {
-    std::once_flag once;
-    int status = HB_OK;
-    std::string why;
-    uint8_t *ptr = nullptr;  // device address of `scratch` on this device
-    int cus = 0;
-};
-
-static StaticDevice g_static[kStaticDevices];
-
-// Set-up on the first call on a device, with that device current: the array's address
-// and the CU count (hipGetSymbolAddress and an attribute query; nothing is allocated).
-static StaticDevice *static_device(int dev)
-{
-    if (dev < 0 || dev >= kStaticDevices) return nullptr;
-    StaticDevice *sd = &g_static[dev];
-    std::call_once(sd->once, [sd, dev] {
-        void *ptr = nullptr;
-        hipError_t e = hipGetSymbolAddress(&ptr, HIP_SYMBOL(scratch));
-        if (e != hipSuccess || !ptr) {
-            sd->status = HB_EHIP;
-            sd->why = std::string("hash_batch_bucketed_noalloc: hipGetSymbolAddress: ") + hipGetErrorString(e);
-            return;
-        }
-        int cus = 0;
-        e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-        if (e != hipSuccess || cus <= 0) {
-            sd->status = HB_EHIP;
-            sd->why = std::string("hash_batch_bucketed_noalloc: CU count: ") + hipGetErrorString(e);
-            return;
-        }
-        sd->ptr = static_cast<uint8_t *>(ptr);
-        sd->cus = cus;
-    });
-    return sd;
-}
-
-// The plan workspace carved out of the device's copy of the array.
-static PlanWs static_ws(uint8_t *base, int cus)
-{
-    PlanWs ws{};
-    uint8_t *c = base;
-    ws.desc = reinterpret_cast<PlanDesc *>(c); c += kStaticDesc;
-    ws.meta = reinterpret_cast<PlanMeta *>(c); c += kStaticMeta;
-    ws.hist = reinterpret_cast<uint32_t *>(c); c += kStaticBins;
-    ws.cursor = reinterpret_cast<uint32_t *>(c); c += kStaticBins;
-    ws.bin_start = reinterpret_cast<uint32_t *>(c); c += kStaticBins;
-    ws.sorted = reinterpret_cast<uint32_t *>(c); c += kStaticSorted;
-    ws.order = reinterpret_cast<uint32_t *>(c); c += kStaticOrder;
-    ws.wave_base = reinterpret_cast<uint32_t *>(c);
-    ws.sched = nullptr;  // no schedule scratch: every long chain is a direct chain
-    ws.sched_blocks = 0;
-    ws.max_long_waves = uint32_t(kStaticLongWaves);
-    ws.max_direct_waves = uint32_t(cus) * 4u;
-    ws.max_n = kStaticMaxN;
-    return ws;
-}
+constexpr uint64_t kNoallocMaxN = 1ull << 20;
 
 }  // namespace hb
 
@@ -1168,7 +1139,7 @@ int hb_plan_create(hb_plan **plan, uint64_t max_n, int flags)
     const uint64_t items_cap = max_n / 64 + 4;
     const uint64_t sorted_cap = max_n + 3ull * 64 * kMaxMpl;
     auto up = [](uint64_t x) { return (x + 255) & ~uint64_t(255); };
-    const uint64_t sz_desc = up(sizeof(PlanDesc)), sz_meta = up(sizeof(PlanMeta));
+    const uint64_t sz_desc = up(sizeof(PlanDesc)), sz_meta = up(sizeof(PlanMeta)), sz_lmeta = up(sizeof(LongMeta));
     const uint64_t sz_bins = up(3ull * kBins * 4);
     const uint64_t sz_sorted = up(sorted_cap * 4), sz_order = up(items_cap * 4);
     // long-chain scratch: HB_LONG_SCRATCH_MB (default 1024) of precomputed block words for
@@ -1190,12 +1161,13 @@ int hb_plan_create(hb_plan **plan, uint64_t max_n, int flags)
         p->long_min_key = uint32_t(min_blocks);
     }
     const uint64_t sz_long = up((long_waves + 1) * 4), sz_sched = up(scratch_blocks * kWaveBlockWords * 4);
-    const uint64_t total = sz_desc + sz_meta + 3 * sz_bins + sz_sorted + sz_order + sz_long + sz_sched;
+    const uint64_t total = sz_desc + sz_meta + sz_lmeta + 3 * sz_bins + sz_sorted + sz_order + sz_long + sz_sched;
     e = hipMalloc(&p->alloc, total);
     if (e != hipSuccess) { delete p; return set_error(HB_ENOMEM, "hb_plan_create: workspace allocation failed"); }
     char *c = static_cast<char *>(p->alloc);
     p->ws.desc = reinterpret_cast<PlanDesc *>(c); c += sz_desc;
     p->ws.meta = reinterpret_cast<PlanMeta *>(c); c += sz_meta;
+    p->long_ws.meta = reinterpret_cast<LongMeta *>(c); c += sz_lmeta;
     p->ws.hist = reinterpret_cast<uint32_t *>(c); c += sz_bins;
     p->ws.cursor = reinterpret_cast<uint32_t *>(c); c += sz_bins;
     p->ws.bin_start = reinterpret_cast<uint32_t *>(c); c += sz_bins;
@@ -1207,6 +1179,11 @@ int hb_plan_create(hb_plan **plan, uint64_t max_n, int flags)
     p->ws.max_long_waves = uint32_t(long_waves);
     p->ws.max_direct_waves = p->long_on ? uint32_t(p->cus) * 4u : 0u;
     p->ws.max_n = max_n;
+    p->long_ws.hist = p->ws.hist;
+    p->long_ws.cursor = p->ws.cursor;
+    p->long_ws.start = p->ws.bin_start;
+    p->long_ws.sorted = p->ws.sorted;
+    p->long_ws.min_key = std::max<uint32_t>(p->long_min_key, 3);  // a chain's first message has a whole block
     // Streams only where needed: each stream may take one of the process's few hardware
     // queues, and streams sharing a queue wait behind each other's kernels.
     e = hipSuccess;
@@ -1220,7 +1197,10 @@ int hb_plan_create(hb_plan **plan, uint64_t max_n, int flags)
         hb_plan_destroy(p);
         return hip_error(e, "hb_plan_create: stream/event");
     }
-    if (const char *w = std::getenv("HB_WAVES_PER_CU")) p->waves_per_cu = std::atoi(w) > 0 ? std::atoi(w) : 16;
+    if (const char *w = std::getenv("HB_WAVES_PER_CU")) {
+        p->waves_per_cu = std::atoi(w) > 0 ? std::atoi(w) : 16;
+        p->tiles = false;  // a launch choice, and so the pipeline
+    }
     *plan = p;
     return HB_OK;
 }
@@ -1279,6 +1259,7 @@ int hb_plan_set_config(hb_plan *p, int waves_per_cu, int msgs_per_lane, int vari
     if (msgs_per_lane) p->mpl = msgs_per_lane;
     p->variant = variant;
     p->tuned = true;
+    p->tiles = false;
     drop_graph(p);
     return HB_OK;
 }
@@ -1315,45 +1296,13 @@ int hash_batch_bucketed_noalloc(const uint8_t *algos, int algo, const uint8_t *m
 {
     if (!algos && digest_size(algo) == 0) return set_error(HB_EINVAL, "hash_batch_bucketed_noalloc: unknown algorithm id");
     if (n == 0) return HB_OK;
-    if (n > kStaticMaxN)
-        return set_error(HB_EINVAL, "hash_batch_bucketed_noalloc: n exceeds the static workspace's 2^20 messages");
+    if (n > kNoallocMaxN) return set_error(HB_EINVAL, "hash_batch_bucketed_noalloc: n exceeds 2^20 messages");
     if (!messages || !offsets || !lengths || !digests_out)
         return set_error(HB_EINVAL, "hash_batch_bucketed_noalloc: null device pointer");
     if (reinterpret_cast<uintptr_t>(digests_out) & 3u)
         return set_error(HB_EINVAL, "hash_batch_bucketed_noalloc: digests_out must be 4-byte aligned");
-    int dev = 0;
-    hipError_t e = hipGetDevice(&dev);
-    if (e != hipSuccess) return hip_error(e, "hash_batch_bucketed_noalloc: hipGetDevice");
-    StaticDevice *sd = static_device(dev);
-    if (!sd) return set_error(HB_EINVAL, "hash_batch_bucketed_noalloc: device index out of range");
-    if (sd->status != HB_OK) return set_error(sd->status, sd->why);
-    // a plan object on the stack: launch settings only, its workspace is the static array
-    hb_plan p;
-    p.ws = static_ws(sd->ptr, sd->cus);
-    p.flags = HB_PLAN_LONG_INLINE;
-    p.device = dev;
-    p.cus = sd->cus;
-    p.long_on = true;
-    p.long_sched = false;
-    p.long_min_key = 256;
-    p.side = nullptr;  // long chains and bulk in one launch
-    PlanDesc d{};
-    d.algos = algos;
-    d.msgs = messages;
-    d.offs = offsets;
-    d.lens = lengths;
-    d.out = digests_out;
-    d.n = n;
-    d.stride = algos ? 32u : uint32_t(digest_size(algo));
-    d.algo = algos ? 0 : algo;
-    d.sort = 1;
-    d.mpl = p.mpl;
-    d.long_min_key = p.long_min_key;
-    d.bulk_margin = p.bulk_margin;
-    hipStream_t s = static_cast<hipStream_t>(stream);
-    hipLaunchKernelGGL(k_set_desc, dim3(1), dim3(1), 0, s, d, p.ws.desc);
-    e = hipGetLastError();
-    if (e == hipSuccess) e = enqueue_pipeline(&p, s, false);
+    const hipError_t e = launch_ragged(algos, algo, messages, offsets, lengths, n, digests_out,
+                                       algos ? 32u : uint32_t(digest_size(algo)), static_cast<hipStream_t>(stream));
     if (e != hipSuccess) return hip_error(e, "hash_batch_bucketed_noalloc: launch");
     return HB_OK;
 }

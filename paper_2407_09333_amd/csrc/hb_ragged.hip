@@ -21,6 +21,7 @@
 #include "hb_device.hpp"
 #include "hb_internal.hpp"
 #include "hb_plan_rules.hpp"
+#include "hb_ragged.hpp"
 
 namespace hb {
 
@@ -69,12 +70,58 @@ struct RaggedLds {
 __device__ __forceinline__ uint32_t wave_simd() { return __builtin_amdgcn_s_getreg(4 | (4 << 6) | ((2 - 1) << 11)); }
 __device__ __forceinline__ uint32_t group_on_cu() { return __builtin_amdgcn_s_getreg(4 | (16 << 6) | ((4 - 1) << 11)); }
 
+constexpr uint64_t kNoMessage = ~0ull;
+constexpr uint32_t kNoLong = 0xffffffffu;
+
+// The chain pair of a workgroup (its other two waves return at once): message i in lane
+// l < 32 (kNoMessage past the last; lane 0's has at least three blocks).  L.simd, L.group and
+// the zeroed L.sync are set, with a barrier since.
+template <int A>
+__device__ __forceinline__ void chain_pair(const RaggedArgs &r, uint64_t i, RaggedLds &L, uint32_t *ring)
+{
+    // Workgroups that share a CU run their chain waves on different SIMDs: the wave on the
+    // SIMD of the workgroup's number (that wave number if none is there), the next but one
+    // for the schedules.  With every chain wave the same wave of its workgroup, three
+    // workgroups' chains shared one SIMD and took 3.3 times as long.
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64u);
+    const uint32_t want = L.group % 4u;
+    uint32_t chain_wave = want;
+#pragma unroll
+    for (uint32_t w = 0; w < kRaggedThreads / 64; ++w)
+        if (L.simd[w] == want) chain_wave = w;
+    const uint32_t role = __builtin_amdgcn_readfirstlane(wave ^ chain_wave);  // 0 chains, 2 schedules
+    if (role != 0 && role != 2) return;
+    uint64_t address = 0, len = 0;
+    uint32_t blocks = 0;
+    if (i != kNoMessage) {
+        len = r.lens[i];
+        address = uint64_t(reinterpret_cast<uintptr_t>(r.msgs)) + r.offs[i];
+        blocks = uint32_t(block_count(len));
+    }
+    if (role == 0) {
+        uint32_t s[8];
+        __builtin_amdgcn_s_setprio(3);
+        chain_run<A>(blocks, ring, &L.sync, s);
+        __builtin_amdgcn_s_setprio(0);
+        if (blocks) store_digest<A>(r.out + i * r.stride, s, r.stride);
+    } else {
+        __builtin_amdgcn_s_setprio(2);
+        chain_schedule<A>(address, len, blocks, ring, L.tails, &L.sync);
+        __builtin_amdgcn_s_setprio(0);
+    }
+}
+
+// Messages of at least `from` blocks (by their capped sort key) and fewer than 2^31 are the
+// business of other workgroups (k_long_tiles).
+__device__ __forceinline__ bool is_long(uint32_t nb, uint32_t from) { return min(nb, kBins - 1u) >= from && nb < 0x80000000u; }
+
 template <int A, bool MANY>
-__device__ __forceinline__ void ragged_tile(const RaggedArgs &r, uint64_t base, RaggedLds &L, uint32_t *ring)
+__device__ __forceinline__ void ragged_tile(const RaggedArgs &r, uint64_t base, uint32_t long_from, RaggedLds &L,
+                                            uint32_t *ring)
 {
     const uint32_t tid = threadIdx.x, lane = tid % 64u, wave = __builtin_amdgcn_readfirstlane(tid / 64u);
     const uint32_t have = uint32_t(min<uint64_t>(r.tile, r.n - base));
-    // this thread's messages: block counts, 0 for none or another algorithm's
+    // this thread's messages: block counts, 0 for none or one that is not this workgroup's
     uint32_t nb[kPerThread], my_longest = 0, my_least = 0xffffffffu;
     unsigned long long my_blocks = 0;
     // the first one's place, kept for the case that nothing is sorted
@@ -91,6 +138,7 @@ __device__ __forceinline__ void ragged_tile(const RaggedArgs &r, uint64_t base, 
                 HB_GLOBAL uint32_t *o = reinterpret_cast<HB_GLOBAL uint32_t *>(reinterpret_cast<uintptr_t>(r.out + i * r.stride));
                 for (uint32_t q = 0; q < r.stride / 4u; ++q) o[q] = 0u;
             }
+            if (is_long(nb[j], long_from)) nb[j] = 0;
             my_longest = max(my_longest, nb[j]);
             my_least = min(my_least, nb[j]);
             my_blocks += nb[j];
@@ -170,38 +218,7 @@ __device__ __forceinline__ void ragged_tile(const RaggedArgs &r, uint64_t base, 
     if (tid == 0) L.next = nchain;
     __syncthreads();
     if (nchain) {
-        // Workgroups that share a CU run their chain waves on different SIMDs: the wave on
-        // the SIMD of the workgroup's number (that wave number if none is there), the next
-        // but one for the schedules.  With every chain wave the same wave of its workgroup,
-        // three workgroups' chains shared one SIMD and took 3.3 times as long.
-        const uint32_t want = L.group % 4u;
-        uint32_t chain_wave = want;
-#pragma unroll
-        for (uint32_t w = 0; w < kRaggedThreads / 64; ++w)
-            if (L.simd[w] == want) chain_wave = w;
-        const uint32_t role = __builtin_amdgcn_readfirstlane(wave ^ chain_wave);  // 0 chains, 2 schedules
-        if (role == 0 || role == 2) {
-            uint64_t i = 0;
-            uint64_t address = 0, len = 0;
-            uint32_t blocks = 0;
-            if (lane < nchain) {
-                i = base + L.order[lane];
-                len = r.lens[i];
-                address = uint64_t(reinterpret_cast<uintptr_t>(r.msgs)) + r.offs[i];
-                blocks = uint32_t(block_count(len));
-            }
-            if (role == 0) {
-                uint32_t s[8];
-                __builtin_amdgcn_s_setprio(3);
-                chain_run<A>(blocks, ring, &L.sync, s);
-                __builtin_amdgcn_s_setprio(0);
-                if (blocks) store_digest<A>(r.out + i * r.stride, s, r.stride);
-            } else {
-                __builtin_amdgcn_s_setprio(2);
-                chain_schedule<A>(address, len, blocks, ring, L.tails, &L.sync);
-                __builtin_amdgcn_s_setprio(0);
-            }
-        }
+        chain_pair<A>(r, lane < nchain ? base + L.order[lane] : kNoMessage, L, ring);
     }
     // 64 positions at a time: in index order each wave every fourth, sorted whoever is free
     uint32_t p = wave * 64u;
@@ -230,7 +247,7 @@ __global__ __launch_bounds__(kRaggedThreads, 4) void k_ragged(RaggedArgs r)
 {
     __shared__ RaggedLds L;
     __shared__ __align__(16) uint32_t ring[kChainRingWords<A>];
-    ragged_tile<A, MANY>(r, uint64_t(xcd_contiguous(blockIdx.x, gridDim.x)) * r.tile, L, ring);
+    ragged_tile<A, MANY>(r, uint64_t(xcd_contiguous(blockIdx.x, gridDim.x)) * r.tile, kNoLong, L, ring);
 }
 
 // Three workgroups per tile, one per algorithm; SM3's (the longest chains) first.
@@ -240,15 +257,192 @@ __global__ __launch_bounds__(kRaggedThreads, MANY ? 4 : 3) void k_ragged_mixed(R
     __shared__ RaggedLds L;
     __shared__ __align__(16) uint32_t ring[kChainRingWords<SM3>];
     const uint64_t base = uint64_t(xcd_contiguous(blockIdx.x % tiles, tiles)) * r.tile;
-    if (blockIdx.x < tiles) ragged_tile<SM3, MANY>(r, base, L, ring);
-    else if (blockIdx.x < 2u * tiles) ragged_tile<SHA1, MANY>(r, base, L, ring);
-    else ragged_tile<MD5, MANY>(r, base, L, ring);
+    if (blockIdx.x < tiles) ragged_tile<SM3, MANY>(r, base, kNoLong, L, ring);
+    else if (blockIdx.x < 2u * tiles) ragged_tile<SHA1, MANY>(r, base, kNoLong, L, ring);
+    else ragged_tile<MD5, MANY>(r, base, kNoLong, L, ring);
 }
 
-}  // namespace
+// ---------------------------------------------------------------------------------------
+// Batches of more tiles than the chip holds at once: the longest messages first
+// ---------------------------------------------------------------------------------------
+//
+// A long message in a tile that starts late would end late.  Up to kLongGroups groups of 32
+// messages, the longest by blocks x operations per block, are therefore picked out over the
+// whole batch and hashed by chain pairs of their own in the launch's first workgroups; the
+// tiles leave them out.
 
-hipError_t launch_ragged(const uint8_t *algos, int algo, const uint8_t *msgs, const uint64_t *offs, const uint64_t *lens,
-                         uint64_t n, uint8_t *out, uint32_t stride, hipStream_t stream)
+constexpr uint32_t kLongGroups = 512;  // two workgroups on each CU, beside two of the tiles'
+
+__host__ __device__ constexpr uint32_t block_ops(int a) { return a == MD5 ? 292u : (a == SHA1 ? 446u : 923u); }  // on a chain
+
+// Groups are numbered SM3's first: the algorithm of slot o.
+__device__ __forceinline__ int long_slot(int o) { return o == 0 ? SM3 : (o == 1 ? SHA1 : MD5); }
+
+__global__ __launch_bounds__(kRaggedThreads) void k_long_zero(LongWs w)
+{
+    const uint32_t t = blockIdx.x * kRaggedThreads + threadIdx.x, step = gridDim.x * kRaggedThreads;
+    for (uint32_t i = t; i < 3 * kBins; i += step) { w.hist[i] = 0; w.cursor[i] = 0; }
+    if (t == 0) w.meta->max_key = 0;
+}
+
+// Counts of the messages of at least min_key blocks, by algorithm and key.
+__global__ __launch_bounds__(kRaggedThreads) void k_long_count(RaggedArgs r, int algo, LongWs w)
+{
+    __shared__ uint32_t top;
+    if (threadIdx.x == 0) top = 0;
+    __syncthreads();
+    uint32_t mine = 0;
+    const uint64_t step = uint64_t(gridDim.x) * kRaggedThreads;
+    for (uint64_t i = uint64_t(blockIdx.x) * kRaggedThreads + threadIdx.x; i < r.n; i += step) {
+        const uint64_t nb = block_count(r.lens[i]);
+        if (nb < w.min_key || nb >= 0x80000000u) continue;
+        const int a = r.algos ? int(r.algos[i]) : algo;
+        if (a > SM3) continue;
+        const uint32_t key = uint32_t(min<uint64_t>(nb, kBins - 1u));
+        atomicAdd(&w.hist[uint32_t(a) * kBins + key], 1u);
+        mine = max(mine, key);
+    }
+    if (mine) atomicMax(&top, mine);
+    __syncthreads();
+    if (threadIdx.x == 0 && top) atomicMax(&w.meta->max_key, top);
+}
+
+constexpr int kPickThreads = 1024;
+
+// First position of each key, longest first, within its algorithm; then the smallest chain
+// cost (blocks x operations) from which up the messages fit the groups.  One workgroup.
+__global__ __launch_bounds__(kPickThreads) void k_long_pick(LongWs w)
+{
+    __shared__ uint32_t part[kPickThreads / 64];
+    LongMeta *m = w.meta;
+    const uint32_t lane = threadIdx.x % 64u, wave = threadIdx.x / 64u, top = m->max_key;
+    const uint32_t nkeys = top >= w.min_key ? top - w.min_key + 1u : 0u, per = (nkeys + kPickThreads - 1) / kPickThreads;
+    for (int a = 0; a < 3; ++a) {
+        const uint32_t *hist = w.hist + uint32_t(a) * kBins;
+        uint32_t local = 0;
+        for (uint32_t k = 0; k < per; ++k) {
+            const uint32_t x = threadIdx.x * per + k;
+            if (x < nkeys) local += hist[top - x];
+        }
+        uint32_t sum = local;
+        for (int d = 1; d < 64; d <<= 1) {
+            const uint32_t up = __shfl_up(sum, d);
+            if (lane >= uint32_t(d)) sum += up;
+        }
+        if (lane == 63) part[wave] = sum;
+        __syncthreads();
+        uint32_t run = sum - local;
+        for (uint32_t v = 0; v < wave; ++v) run += part[v];
+        for (uint32_t k = 0; k < per; ++k) {
+            const uint32_t x = threadIdx.x * per + k;
+            if (x < nkeys) {
+                w.start[uint32_t(a) * kBins + top - x] = run;
+                run += hist[top - x];
+            }
+        }
+        __syncthreads();
+    }
+    __threadfence_block();
+    __syncthreads();
+    // messages of algorithm a whose cost reaches c, and the key that takes
+    auto key_for = [&](int a, uint64_t c) {
+        const uint64_t k = (c + block_ops(a) - 1) / block_ops(a);
+        return uint32_t(min<uint64_t>(max<uint64_t>(k, w.min_key), 0xffffffffull));
+    };
+    auto messages = [&](int a, uint64_t c) {
+        const uint32_t k = key_for(a, c);
+        return k > top ? 0u : w.start[uint32_t(a) * kBins + k] + w.hist[uint32_t(a) * kBins + k];
+    };
+    auto fits = [&](uint64_t c) {
+        uint32_t g = 0;
+        for (int a = 0; a < 3; ++a) g += (messages(a, c) + kChainEntries - 1u) / kChainEntries;
+        return g <= kLongGroups;
+    };
+    // the smallest c that fits, a thousandth of what is left of the range at a time
+    uint64_t lo = 0, hi = uint64_t(kBins) * block_ops(SM3);  // hi fits: no message has that cost
+    if (!fits(0)) {
+        while (hi - lo > 1) {  // lo does not fit
+            const uint64_t d = (hi - lo + kPickThreads) / (kPickThreads + 1u);
+            const uint64_t c = min<uint64_t>(lo + d * (threadIdx.x + 1u), hi);
+            const uint32_t nfit = uint32_t(__syncthreads_count(fits(c)));  // fits is monotone in c
+            const uint64_t first = kPickThreads - nfit;                     // the first thread whose c fits
+            hi = min<uint64_t>(lo + d * (first + 1u), hi);
+            lo = min<uint64_t>(lo + d * first, hi - 1u);
+        }
+    } else {
+        hi = 0;
+    }
+    if (threadIdx.x == 0) {
+        uint32_t pos = 0, group = 0;
+        for (int o = 0; o < 3; ++o) {
+            const int a = long_slot(o);
+            m->from[a] = key_for(a, hi);
+            m->count[a] = messages(a, hi);
+            m->pos[a] = pos;
+            m->group[o] = group;
+            pos += m->count[a];
+            group += (m->count[a] + kChainEntries - 1u) / kChainEntries;
+        }
+        m->group[3] = group;
+    }
+}
+
+__global__ __launch_bounds__(kRaggedThreads) void k_long_scatter(RaggedArgs r, int algo, LongWs w)
+{
+    const uint64_t step = uint64_t(gridDim.x) * kRaggedThreads;
+    for (uint64_t i = uint64_t(blockIdx.x) * kRaggedThreads + threadIdx.x; i < r.n; i += step) {
+        const uint64_t nb = block_count(r.lens[i]);
+        if (nb < w.min_key || nb >= 0x80000000u) continue;
+        const int a = r.algos ? int(r.algos[i]) : algo;
+        if (a > SM3 || !is_long(uint32_t(nb), w.meta->from[a])) continue;
+        const uint32_t bin = uint32_t(a) * kBins + uint32_t(min<uint64_t>(nb, kBins - 1u));
+        w.sorted[w.meta->pos[a] + w.start[bin] + atomicAdd(&w.cursor[bin], 1u)] = uint32_t(i);
+    }
+}
+
+// One group of long messages.
+template <int A>
+__device__ __forceinline__ void long_group(const RaggedArgs &r, const LongWs &w, uint32_t k, RaggedLds &L, uint32_t *ring)
+{
+    const uint32_t lane = threadIdx.x % 64u, at = k * kChainEntries + lane;
+    if (lane == 0) L.simd[threadIdx.x / 64u] = wave_simd();
+    if (threadIdx.x == 0) { L.group = group_on_cu(); L.sync.filled = 0; L.sync.taken = 0; }
+    __syncthreads();
+    chain_pair<A>(r, lane < kChainEntries && at < w.meta->count[A] ? w.sorted[w.meta->pos[A] + at] : kNoMessage, L, ring);
+}
+
+// The long groups' workgroups, then the tiles'.  ALGO: the batch's algorithm, or -1 for a
+// mixed one (three workgroups a tile).
+template <int ALGO>
+__global__ __launch_bounds__(kRaggedThreads, 4) void k_long_tiles(RaggedArgs r, LongWs w, uint32_t tiles)
+{
+    __shared__ RaggedLds L;
+    __shared__ __align__(16) uint32_t ring[kChainRingWords<ALGO < 0 ? int(SM3) : ALGO>];
+    const LongMeta *m = w.meta;
+    if (blockIdx.x < kLongGroups) {
+        const uint32_t g = blockIdx.x;
+        if (g >= m->group[3]) return;
+        if constexpr (ALGO >= 0) long_group<ALGO>(r, w, g, L, ring);
+        else if (g < m->group[1]) long_group<SM3>(r, w, g, L, ring);
+        else if (g < m->group[2]) long_group<SHA1>(r, w, g - m->group[1], L, ring);
+        else long_group<MD5>(r, w, g - m->group[2], L, ring);
+        return;
+    }
+    const uint32_t b = blockIdx.x - kLongGroups;
+    const uint64_t base = uint64_t(xcd_contiguous(b % tiles, tiles)) * r.tile;
+    if constexpr (ALGO >= 0) ragged_tile<ALGO, true>(r, base, m->from[ALGO], L, ring);
+    else if (b < tiles) ragged_tile<SM3, true>(r, base, m->from[SM3], L, ring);
+    else if (b < 2u * tiles) ragged_tile<SHA1, true>(r, base, m->from[SHA1], L, ring);
+    else ragged_tile<MD5, true>(r, base, m->from[MD5], L, ring);
+}
+
+// How a batch is dealt out: messages per tile, tiles, workgroups per tile, and how many times
+// over its workgroups fill the chip.
+struct Tiling {
+    uint64_t tile, tiles, per, rounds;
+};
+
+Tiling tiling(uint64_t n, bool mixed)
 {
     // Messages a workgroup gets: up to 256 while one workgroup on each CU takes them all, one
     // wave to a SIMD (64 to a workgroup and four workgroups to a CU would put the four busy
@@ -258,17 +452,26 @@ hipError_t launch_ragged(const uint8_t *algos, int algo, const uint8_t *msgs, co
     // last round that is half empty costs more.  A mixed batch's tiles are twice as large, a
     // workgroup hashing about a third of one: three times as large, half the workgroups would
     // have a few messages more than their four waves take at once.
-    const uint64_t cus = device_simds() / 4u, per = algos ? 3u : 1u, wide = algos ? 2u : 1u, slots = cus * 4u;
+    const uint64_t cus = device_simds() / 4u, per = mixed ? 3u : 1u, wide = mixed ? 2u : 1u, slots = cus * 4u;
     const uint64_t rounds = (n * per + slots * kTileMax - 1) / (slots * kTileMax);
     const uint64_t one = (n + cus - 1) / cus, all = (n * per + slots * rounds - 1) / (slots * rounds);
     const uint64_t tile = one <= kRaggedThreads ? (one + 63u) / 64u * 64u * wide
                                                 : std::min<uint64_t>((std::max<uint64_t>(all, kRaggedThreads * wide) + 255u) / 256u * 256u, kTileMax);
-    const uint64_t tiles = (n + tile - 1) / tile;
+    return {tile, (n + tile - 1) / tile, per, rounds};
+}
+
+}  // namespace
+
+hipError_t launch_ragged(const uint8_t *algos, int algo, const uint8_t *msgs, const uint64_t *offs, const uint64_t *lens,
+                         uint64_t n, uint8_t *out, uint32_t stride, hipStream_t stream)
+{
+    const Tiling t = tiling(n, algos != nullptr);
+    const uint64_t tile = t.tile, tiles = t.tiles, per = t.per;
     if (tiles * per > 0x7fffffffull) return hipErrorInvalidConfiguration;
     const RaggedArgs r{msgs, offs, lens, algos, out, n, stride, uint32_t(tile)};
     const dim3 grid{uint32_t(tiles * per), 1, 1}, block{kRaggedThreads, 1, 1};
     // one wave to a SIMD (see few_waves)
-    const bool few = tiles * per <= cus;
+    const bool few = tiles * per <= device_simds() / 4u;
     if (algos) {
         hipLaunchKernelGGL(few ? k_ragged_mixed<false> : k_ragged_mixed<true>, grid, block, 0, stream, r, uint32_t(tiles));
         return hipGetLastError();
@@ -279,6 +482,27 @@ hipError_t launch_ragged(const uint8_t *algos, int algo, const uint8_t *msgs, co
     case SM3: hipLaunchKernelGGL((few ? k_ragged<SM3, false> : k_ragged<SM3, true>), grid, block, 0, stream, r); break;
     default: return hipErrorInvalidValue;
     }
+    return hipGetLastError();
+}
+
+bool ragged_in_one_round(uint64_t n, bool mixed) { return tiling(n, mixed).rounds <= 1; }
+
+hipError_t launch_ragged_long(const LongWs &w, const uint8_t *algos, int algo, const uint8_t *msgs, const uint64_t *offs,
+                              const uint64_t *lens, uint64_t n, uint8_t *out, uint32_t stride, hipStream_t stream)
+{
+    const Tiling t = tiling(n, algos != nullptr);
+    if (t.tiles * t.per + kLongGroups > 0x7fffffffull) return hipErrorInvalidConfiguration;
+    const RaggedArgs r{msgs, offs, lens, algos, out, n, stride, uint32_t(t.tile)};
+    const dim3 block{kRaggedThreads, 1, 1}, sweep{device_simds(), 1, 1}, grid{uint32_t(kLongGroups + t.tiles * t.per), 1, 1};
+    hipLaunchKernelGGL(k_long_zero, sweep, block, 0, stream, w);
+    hipLaunchKernelGGL(k_long_count, sweep, block, 0, stream, r, algo, w);
+    hipLaunchKernelGGL(k_long_pick, dim3(1), dim3(kPickThreads), 0, stream, w);
+    hipLaunchKernelGGL(k_long_scatter, sweep, block, 0, stream, r, algo, w);
+    if (algos) hipLaunchKernelGGL(k_long_tiles<-1>, grid, block, 0, stream, r, w, uint32_t(t.tiles));
+    else if (algo == MD5) hipLaunchKernelGGL(k_long_tiles<MD5>, grid, block, 0, stream, r, w, uint32_t(t.tiles));
+    else if (algo == SHA1) hipLaunchKernelGGL(k_long_tiles<SHA1>, grid, block, 0, stream, r, w, uint32_t(t.tiles));
+    else if (algo == SM3) hipLaunchKernelGGL(k_long_tiles<SM3>, grid, block, 0, stream, r, w, uint32_t(t.tiles));
+    else return hipErrorInvalidValue;
     return hipGetLastError();
 }
 

@@ -74,3 +74,31 @@ def test_many_tiles(hb, n):
     algos = rng.integers(0, 3, n).astype(np.uint8)
     got = hb.hash_batch_mixed(algos, msgs, offs.astype(np.int64), lens.astype(np.int64)).cpu().numpy()
     assert_same(got, oracle.hash_batch(algos, msgs, offs, lens), "many tiles mixed")
+
+
+@pytest.mark.parametrize("algo", [None, 0, 1, 2])
+def test_long_messages_first(hb, monkeypatch, algo):
+    """A plan whose batch has more than one round of tiles picks the longest messages out
+    first: here more of them than its groups hold, some past the saturated sort key, and
+    the same with the long path off."""
+    monkeypatch.setenv("HB_LONG_MIN_BLOCKS", "3")
+    n = 720_003 if algo is None else (1 << 21) + 1501
+    rng = np.random.default_rng(90)
+    lens = rng.integers(0, 100 if algo is None else 40, n)
+    lens[rng.integers(0, n, 30_000)] = rng.integers(120, 1500, 30_000)
+    lens[rng.integers(0, n, 40)] = rng.integers(30_000, 70_000, 40)
+    lens[rng.integers(0, n, 3)] = [1_100_000, 1_060_003, 1_300_001]
+    lens = lens.astype(np.uint64)
+    offs = workloads.packed(lens)
+    msgs = workloads.host_random_bytes(int(lens.sum()) + 1, seed=91)
+    algos = rng.integers(0, 3, n).astype(np.uint8) if algo is None else None
+    want = oracle.hash_batch(algo if algos is None else algos, msgs, offs, lens)
+    for flags in (hb.PLAN_GRAPH, hb.PLAN_NO_LONG):
+        print(f"case long first algo={algo} flags={flags}", flush=True)
+        plan = hb.Plan(n, flags=flags)
+        for _ in range(2):
+            buf, out = guarded_out(n, want.shape[1])
+            plan.run(msgs, offs, lens, algo=algo, algos=algos, out=out)
+            check_guard(buf, n, want.shape[1])
+            assert_same(out.cpu().numpy(), want, f"long first {algo} {flags}")
+        plan.close()
