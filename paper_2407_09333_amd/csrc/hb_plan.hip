@@ -982,9 +982,8 @@ static int launch_run(hb_plan *p, const PlanDesc &d, hipStream_t s)
 }
 
 // The tiled launch.  The longest messages are picked out first only for a batch of more than
-// one round of tiles: in one, every message starts at once (SM3, 2^22 messages of log-normal
-// lengths up to 64 KiB, two rounds: 6.2 ms without, 1e6 messages up to 1 MiB, one round: the
-// longest message's own 27.9 ms either way).
+// one round of tiles: in one, every message starts at once.  (2^22 SM3 messages of log-normal
+// lengths up to 64 KiB, two rounds: 5.9 ms in tiles alone, 3.5 ms with them picked out.)
 static hipError_t enqueue_tiles(hb_plan *p, const PlanDesc &d, hipStream_t s, bool timed)
 {
     std::pair<hipEvent_t, hipEvent_t> ev{nullptr, nullptr};
