@@ -27,6 +27,11 @@
 // two (5 + 4 a round), SM3 two of four (12 + 12 a round with its expansion).  Measured the
 // other way: MD5 without v_add3_u32 995, SHA-1 without 1,888, SM3 without v_xad_u32 3,924.
 //
+// What a kernel does between two blocks -- loads, realignment and byte reversal, v_perm_b32
+// being wide -- runs at the raised priority too, so that a wave gets its next loads out: each
+// function starts with a plain run and ends at the raised priority (2^22 SM3 messages of 0 to
+// 4,096 bytes: 4,849 us when it ended at the plain one, 4,688 so).
+//
 // A wave alone on its SIMD issues one instruction per four cycles or slower whatever its
 // kind, so there the two priority changes a round only cost (MD5 1,886 against 1,208
 // cycles): launches of at most one wave per SIMD take compress<A> instead.
@@ -66,7 +71,7 @@ static_assert(TT_XOR3 == 0x96 && TT_MAJ == 0xe8 && TT_CH == 0xca && TT_MD5_G == 
 __device__ __forceinline__ void md5_compress_many(uint32_t s[8], const uint32_t X[16])
 {
     uint32_t a = s[0], b = s[1], c = s[2], d = s[3], t;
-    asm volatile(
+    asm volatile(HB_PLAIN
         HB_MD5_I(a, b, c, d, w0, 25, 0xd76aa478, HB_TT_CH)
         HB_MD5_I(d, a, b, c, w1, 20, 0xe8c7b756, HB_TT_CH)
         HB_MD5_I(c, d, a, b, w2, 15, 0x242070db, HB_TT_CH)
@@ -131,6 +136,7 @@ __device__ __forceinline__ void md5_compress_many(uint32_t s[8], const uint32_t 
         HB_MD5_I(d, a, b, c, w11, 22, 0xbd3af235, HB_TT_I)
         HB_MD5_I(c, d, a, b, w2, 17, 0x2ad7d2bb, HB_TT_I)
         HB_MD5_I(b, c, d, a, w9, 11, 0xeb86d391, HB_TT_I)
+        HB_WIDE
         : [a] "+v"(a), [b] "+v"(b), [c] "+v"(c), [d] "+v"(d), [t] "=&v"(t)
         : [w0] "v"(X[0]), [w1] "v"(X[1]), [w2] "v"(X[2]), [w3] "v"(X[3]), [w4] "v"(X[4]), [w5] "v"(X[5]),
           [w6] "v"(X[6]), [w7] "v"(X[7]), [w8] "v"(X[8]), [w9] "v"(X[9]), [w10] "v"(X[10]), [w11] "v"(X[11]),
@@ -166,7 +172,7 @@ __device__ __forceinline__ void sha1_compress_many(uint32_t s[8], const uint32_t
 #pragma unroll
     for (int t = 0; t < 16; ++t) W[t] = M[t];
     uint32_t a = s[0], b = s[1], c = s[2], d = s[3], e = s[4], f, u;
-    asm volatile(
+    asm volatile(HB_PLAIN
         HB_SHA1_I(a, b, c, d, e, w0, k0, HB_TT_CH)
         HB_SHA1_I(e, a, b, c, d, w1, k0, HB_TT_CH)
         HB_SHA1_I(d, e, a, b, c, w2, k0, HB_TT_CH)
@@ -247,6 +253,7 @@ __device__ __forceinline__ void sha1_compress_many(uint32_t s[8], const uint32_t
         HB_SHA1_X(d, e, a, b, c, w13, w10, w5, w15, k3, HB_TT_XOR3)
         HB_SHA1_X(c, d, e, a, b, w14, w11, w6, w0, k3, HB_TT_XOR3)
         HB_SHA1_X(b, c, d, e, a, w15, w12, w7, w1, k3, HB_TT_XOR3)
+        HB_WIDE
         : [a] "+v"(a), [b] "+v"(b), [c] "+v"(c), [d] "+v"(d), [e] "+v"(e), [f] "=&v"(f), [u] "=&v"(u),
           [w0] "+v"(W[0]), [w1] "+v"(W[1]), [w2] "+v"(W[2]), [w3] "+v"(W[3]), [w4] "+v"(W[4]), [w5] "+v"(W[5]),
           [w6] "+v"(W[6]), [w7] "+v"(W[7]), [w8] "+v"(W[8]), [w9] "+v"(W[9]), [w10] "+v"(W[10]),
@@ -309,7 +316,7 @@ __device__ __forceinline__ void sm3_compress_many(uint32_t s8[8], const uint32_t
     // the 48 distinct round constants as scalar operands: 4-byte adds (3,613 against 3,690
     // cycles with 8-byte literals)
     asm volatile(
-        HB_SM3_H2(a)
+        HB_SM3_H2(a) HB_PLAIN
         HB_SM3_F(a, b, c, d, e, f, g, h, w0, w4, k0, HB_TT_XOR3, HB_TT_XOR3) HB_SM3_H0 HB_SM3_H1(b, d, f, h) HB_SM3_H2(d) HB_SM3_E(h)
         HB_SM3_F(d, a, b, c, h, e, f, g, w1, w5, k1, HB_TT_XOR3, HB_TT_XOR3) HB_SM3_H0 HB_SM3_H1(a, c, e, g) HB_SM3_H2(c) HB_SM3_E(g)
         HB_SM3_F(c, d, a, b, g, h, e, f, w2, w6, k2, HB_TT_XOR3, HB_TT_XOR3) HB_SM3_H0 HB_SM3_H1(d, b, h, f) HB_SM3_H2(b) HB_SM3_E(f)
@@ -374,6 +381,7 @@ __device__ __forceinline__ void sm3_compress_many(uint32_t s8[8], const uint32_t
         HB_SM3_F(d, a, b, c, h, e, f, g, w13, w1, k45, HB_TT_MAJ, HB_TT_CH) HB_SM3_F_X(x1, y1, w2, w9, w12) HB_SM3_H0 HB_SM3_H_X(x1, w2) HB_SM3_H1(a, c, e, g) HB_SM3_H_N(x0, y0, w0, w6) HB_SM3_H2(c) HB_SM3_E(g) HB_SM3_E_X(x1, y1, w2)
         HB_SM3_F(c, d, a, b, g, h, e, f, w14, w2, k46, HB_TT_MAJ, HB_TT_CH) HB_SM3_F_X(x0, y0, w3, w10, w13) HB_SM3_H0 HB_SM3_H_X(x0, w3) HB_SM3_H1(d, b, h, f) HB_SM3_H2(b) HB_SM3_E(f) HB_SM3_E_X(x0, y0, w3)
         HB_SM3_F(b, c, d, a, f, g, h, e, w15, w3, k47, HB_TT_MAJ, HB_TT_CH) HB_SM3_H0 HB_SM3_H1(c, a, g, e) HB_SM3_E(e)
+        HB_WIDE
         : [a] "+v"(a), [b] "+v"(b), [c] "+v"(c), [d] "+v"(d), [e] "+v"(e), [f] "+v"(f), [g] "+v"(g), [h] "+v"(h),
           [p] "=&v"(p), [q] "=&v"(q), [r] "=&v"(r), [s] "=&v"(s), [x0] "=&v"(x0), [x1] "=&v"(x1), [y0] "=&v"(y0),
           [y1] "=&v"(y1), [w0] "+v"(W[0]), [w1] "+v"(W[1]), [w2] "+v"(W[2]), [w3] "+v"(W[3]), [w4] "+v"(W[4]),
