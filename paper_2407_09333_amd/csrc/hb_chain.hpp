@@ -8,8 +8,8 @@
 // (the schedule wave) does the rest ahead of it: it reads the message blocks, pads the last
 // ones, expands the schedule words and hands them over in LDS.
 //
-// The LDS ring has a few windows of 32 entries, an entry holding one block's words.  A window
-// covers the next 32 / m blocks of each message, m being the number of messages still
+// The LDS ring has a few windows of E entries (32 or 64), an entry holding one block's words.
+// A window covers the next E / m blocks of each message, m being the number of messages still
 // running rounded up to a power of two, so a single message is read 2 KiB at a time by 32
 // lanes, and the latency of its loads is paid once: the schedule wave loads two windows
 // ahead of the one it expands.  Both waves derive the windows from the same block counts.
@@ -22,14 +22,14 @@
 
 namespace hb {
 
-constexpr uint32_t kChainEntries = 32;  // blocks per window, and messages at most
+constexpr uint32_t kChainMessages = 32;  // of a pair, at most, where a batch has more than pairs for all
 
 // Windows in the ring: MD5's schedules take about as long as its rounds, so its schedule
 // wave needs the slack of a third.
 template <int A> constexpr uint32_t kChainSlots = A == MD5 ? 3 : 2;
 
 // 4-byte words of LDS the ring takes for algorithm A.
-template <int A> constexpr uint32_t kChainRingWords = kChainSlots<A> * kChainEntries * SchedWords<A>::kN;
+template <int A, uint32_t E = kChainMessages> constexpr uint32_t kChainRingWords = kChainSlots<A> * E * SchedWords<A>::kN;
 
 // Hand-over counters, in LDS, zero at the start.
 struct ChainSync {
@@ -38,7 +38,7 @@ struct ChainSync {
 };
 
 // One window of the messages with nb blocks (one per lane, 0 in the lanes past them):
-// blocks first .. first + (32 >> shift) - 1 of lanes 0 .. (1 << shift) - 1; none left when
+// blocks first .. first + (E >> shift) - 1 of lanes 0 .. (1 << shift) - 1; none left when
 // `more` is false.
 struct ChainWindow {
     uint32_t shift;
@@ -131,22 +131,23 @@ struct ChainFetch {
     bool more;         // there is such a window (wave-uniform)
 };
 
-constexpr uint32_t kChainTailWords = 19 * kChainEntries;  // LDS for the partial blocks and the lengths
+// LDS words for the partial blocks and the lengths of up to M messages.
+template <uint32_t M = kChainMessages> constexpr uint32_t kChainTailWords = 19 * M;
 
-// The schedule wave.  Lane l < 32 brings message l (its address and length, and its block
+// The schedule wave.  Lane l < M <= E brings message l (its address and length, and its block
 // count nb; nb = 0 past the last); message 0 has at least one whole block.  Two windows are in
 // flight ahead of the one being scheduled: with 17 to 32 messages a window is one block of
 // each, 0.6 to 1.8 us of the chain wave's time.  So that the waits for them can be counted,
 // every fetch is the same five loads, made by every lane: a lane without a whole block in the
 // window reads message 0's first, and the dwords of each message's partial block are read at
 // the start and kept in LDS (`tails`).
-template <int A>
+template <int A, uint32_t E = kChainMessages, uint32_t M = kChainMessages>
 __device__ __forceinline__ void chain_schedule(uint64_t address, uint64_t length, uint32_t nb, uint32_t *ring,
                                                uint32_t *tails, ChainSync *sync)
 {
     constexpr int N = SchedWords<A>::kN;
     const uint32_t lane = __lane_id();
-    const uint32_t e = lane % kChainEntries;  // the entry this lane fills (lanes 32.. only shadow)
+    const uint32_t e = lane % E;  // the entry this lane fills (lanes E.. only shadow)
     const Msg m0 = make_msg<A>(reinterpret_cast<const uint8_t *>(uint64_t(__shfl(address, 0))), 64);
     if (nb) {
         const Msg m = make_msg<A>(reinterpret_cast<const uint8_t *>(address), length);
@@ -156,9 +157,9 @@ __device__ __forceinline__ void chain_schedule(uint64_t address, uint64_t length
 #pragma unroll
         for (uint32_t k = 0; k < 17; ++k) t[k] = 4 * k < lim ? q[k] : 0u;
 #pragma unroll
-        for (uint32_t k = 0; k < 17; ++k) tails[k * kChainEntries + lane] = t[k];
-        tails[17 * kChainEntries + lane] = uint32_t(length);
-        tails[18 * kChainEntries + lane] = uint32_t(length >> 32);
+        for (uint32_t k = 0; k < 17; ++k) tails[k * M + lane] = t[k];
+        tails[17 * M + lane] = uint32_t(length);
+        tails[18 * M + lane] = uint32_t(length >> 32);
     }
     Msg m = m0;
     uint32_t mnb = 0, mwhole = 0, shift = 0xffffffffu, first = 0, k = 0;
@@ -169,7 +170,7 @@ __device__ __forceinline__ void chain_schedule(uint64_t address, uint64_t length
             shift = w.shift;
             const int l = int(e & ((1u << shift) - 1u));
             m = make_msg<A>(reinterpret_cast<const uint8_t *>(uint64_t(__shfl(address, l))), __shfl(length, l));
-            mnb = lane < kChainEntries ? uint32_t(__shfl(nb, l)) : 0u;
+            mnb = lane < E ? uint32_t(__shfl(nb, l)) : 0u;
             mwhole = uint32_t(m.len / 64u);
         }
         const uint32_t blk = first + (e >> shift);
@@ -188,7 +189,7 @@ __device__ __forceinline__ void chain_schedule(uint64_t address, uint64_t length
             f.raw[4 * g] = v.x; f.raw[4 * g + 1] = v.y; f.raw[4 * g + 2] = v.z; f.raw[4 * g + 3] = v.w;
         }
         f.raw[16] = q[r ? 16 : 15];
-        first += kChainEntries >> shift;
+        first += E >> shift;
         __builtin_amdgcn_sched_barrier(0);  // one fetch's loads before the next one's
     };
     auto produce = [&](ChainFetch &f) {
@@ -196,12 +197,12 @@ __device__ __forceinline__ void chain_schedule(uint64_t address, uint64_t length
         const bool have = f.more, on = f.blk < f.nb;
         if (__any(on && f.blk >= f.whole)) {
             const uint32_t l = e & ((1u << f.shift) - 1u);
-            const uint64_t len = tails[17 * kChainEntries + l] | uint64_t(tails[18 * kChainEntries + l]) << 32;
+            const uint64_t len = tails[17 * M + l] | uint64_t(tails[18 * M + l]) << 32;
             // message bytes from the block's start (any value past the end stands for none)
             const int32_t rem = f.blk < f.whole ? 64 : (f.blk == f.whole ? int32_t(len % 64u) : -1);
             uint32_t raw[17], t[17];
 #pragma unroll
-            for (uint32_t i = 0; i < 17; ++i) t[i] = tails[i * kChainEntries + l];
+            for (uint32_t i = 0; i < 17; ++i) t[i] = tails[i * M + l];
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int i = 0; i < 17; ++i) raw[i] = rem >= 64 ? f.raw[i] : (rem > 0 ? t[i] : 0u);
@@ -218,9 +219,9 @@ __device__ __forceinline__ void chain_schedule(uint64_t address, uint64_t length
         // SM3's 128 would not fit the registers
         if (have && k >= kChainSlots<A>) chain_wait(&sync->taken, k - kChainSlots<A> + 1u);
         if (on) {
-            u32x4 *slot = reinterpret_cast<u32x4 *>(ring) + (k % kChainSlots<A>) * (N / 4) * kChainEntries + e;
+            u32x4 *slot = reinterpret_cast<u32x4 *>(ring) + (k % kChainSlots<A>) * (N / 4) * E + e;
             schedule_groups<A>(words, [&](int g, uint32_t a, uint32_t b, uint32_t c, uint32_t d) {
-                slot[g * int(kChainEntries)] = u32x4{a, b, c, d};
+                slot[g * int(E)] = u32x4{a, b, c, d};
             });
         }
         if (have) chain_post(&sync->filled, ++k);
@@ -277,13 +278,13 @@ template <int A, int C> __device__ __forceinline__ void quarter(uint32_t v[8], c
 
 // The words of quarter C of an entry: q is the entry's place in the window's first word
 // group.
-template <int A, int C> __device__ __forceinline__ void load_chunk(const u32x4 *q, uint32_t *ww)
+template <int A, int C, uint32_t E> __device__ __forceinline__ void load_chunk(const u32x4 *q, uint32_t *ww)
 {
     constexpr int kGroupsPer = kChunkRounds<A> / 4;  // SM3: of W', then as many of W
 #pragma unroll
     for (int g = 0; g < kChunkWords<A> / 4; ++g) {
         const int group = g < kGroupsPer ? kGroupsPer * C + g : 16 + kGroupsPer * C + g - kGroupsPer;
-        const u32x4 x = q[group * int(kChainEntries)];
+        const u32x4 x = q[group * int(E)];
         ww[4 * g] = x.x; ww[4 * g + 1] = x.y; ww[4 * g + 2] = x.z; ww[4 * g + 3] = x.w;
     }
 }
@@ -294,10 +295,10 @@ template <int A, int C> __device__ __forceinline__ void load_chunk(const u32x4 *
 // words are read while the quarter before it runs, the last one's over the first words of
 // the next block -- after a window's last block, of the next window if that is filled by
 // then, asked for a quarter earlier: waiting for it between blocks costs 150-250 ns.
-template <int A>
+template <int A, uint32_t E = kChainMessages>
 __device__ __forceinline__ void chain_run(uint32_t nb, const uint32_t *ring, ChainSync *sync, uint32_t s[8])
 {
-    constexpr uint32_t kWindow = SchedWords<A>::kN / 4 * kChainEntries;  // in 16-byte units
+    constexpr uint32_t kWindow = SchedWords<A>::kN / 4 * E;  // in 16-byte units
     const u32x4 *base = reinterpret_cast<const u32x4 *>(ring);
     const uint32_t lane = __lane_id();
     uint32_t top = nb;
@@ -316,15 +317,15 @@ __device__ __forceinline__ void chain_run(uint32_t nb, const uint32_t *ring, Cha
 #pragma unroll
         for (int i = 0; i < 8; ++i) v[i] = s[i];
         // the barriers keep each quarter's loads ahead of the rounds they run under
-        load_chunk<A, 1>(q, b1);
+        load_chunk<A, 1, E>(q, b1);
         __builtin_amdgcn_sched_barrier(0);
         quarter<A, 0>(v, b0);
         __builtin_amdgcn_sched_barrier(0);
-        load_chunk<A, 2>(q, b0);
+        load_chunk<A, 2, E>(q, b0);
         __builtin_amdgcn_sched_barrier(0);
         quarter<A, 1>(v, b1);
         __builtin_amdgcn_sched_barrier(0);
-        load_chunk<A, 3>(q, b1);
+        load_chunk<A, 3, E>(q, b1);
         if constexpr (LAST) filled = __hip_atomic_load(&sync->filled, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         __builtin_amdgcn_sched_barrier(0);
         quarter<A, 2>(v, b0);
@@ -338,7 +339,7 @@ __device__ __forceinline__ void chain_run(uint32_t nb, const uint32_t *ring, Cha
         } else {
             at = next;
         }
-        load_chunk<A, 0>(base + at, b0);
+        load_chunk<A, 0, E>(base + at, b0);
         __builtin_amdgcn_sched_barrier(0);
         quarter<A, 3>(v, b1);
         const bool live = nb > blk;
@@ -354,12 +355,12 @@ __device__ __forceinline__ void chain_run(uint32_t nb, const uint32_t *ring, Cha
         if (!ready) {
             chain_wait(&sync->filled, k + 1u);
             at = slot * kWindow + (lane & (per - 1u));
-            load_chunk<A, 0>(base + at, b0);
+            load_chunk<A, 0, E>(base + at, b0);
         }
         ++k;
         slot = slot + 1u == kChainSlots<A> ? 0u : slot + 1u;
         // (no block past the longest message's last)
-        for (uint32_t left = min(kChainEntries >> w.shift, longest - blk) - 1u; left; --left) block(std::false_type{}, at + per);
+        for (uint32_t left = min(E >> w.shift, longest - blk) - 1u; left; --left) block(std::false_type{}, at + per);
         w = chain_window(nb, blk + 1u);
         block(std::true_type{}, slot * kWindow + (lane & ((1u << w.shift) - 1u)));
         if (w.more) chain_post(&sync->taken, k);

@@ -17,6 +17,11 @@ int hip_error(hipError_t e, const char *what);
 hipError_t launch_fixed(int algo, const uint8_t *msgs, uint64_t n, uint64_t fixed_len, uint8_t *out, uint32_t stride,
                         hipStream_t stream);
 
+// As launch_fixed for packed digests, by chain pairs (hb_ragged.hip), for the batches that
+// fixed_chain_applies to: few messages.
+bool fixed_chain_applies(int algo, uint64_t n, uint64_t len);
+hipError_t launch_fixed_chain(int algo, const uint8_t *msgs, uint64_t n, uint64_t len, uint8_t *out, hipStream_t stream);
+
 int digest_size(int algo);
 
 // SIMDs of the current device (four per CU).

@@ -344,6 +344,9 @@ bool plain_lds_applies(const uint8_t *msgs, uint64_t fixed_len, uint32_t stride,
 hipError_t launch_fixed(int algo, const uint8_t *msgs, uint64_t n, uint64_t fixed_len, uint8_t *out, uint32_t stride,
                         hipStream_t stream)
 {
+    // few messages: chain pairs, unless HB_PLAIN_LDS asks for one of the kernels here
+    if (!std::getenv("HB_PLAIN_LDS") && stride == uint32_t(digest_size(algo)) && fixed_chain_applies(algo, n, fixed_len))
+        return launch_fixed_chain(algo, msgs, n, fixed_len, out, stream);
     if (plain_lds_applies(msgs, fixed_len, stride, algo)) {
         switch (algo) {
         case MD5: return launch_lds_a<MD5>(msgs, n, fixed_len, out, stream);

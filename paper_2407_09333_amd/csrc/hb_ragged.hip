@@ -61,7 +61,7 @@ struct RaggedLds {
     uint32_t least;               // smallest (0 where another algorithm's message is)
     uint32_t next;                // next position to hand out
     ChainSync sync;
-    uint32_t tails[kChainTailWords];
+    uint32_t tails[kChainTailWords<>];
     uint32_t simd[kRaggedThreads / 64];  // SIMD of each wave
     uint32_t group;                      // the workgroup's number on its CU
 };
@@ -188,7 +188,7 @@ __device__ __forceinline__ void ragged_tile(const RaggedArgs &r, uint64_t base, 
     if (L.longest == 0) return;  // no message of this algorithm
     // Nothing to gain from sorting: one block count throughout, or one wave a SIMD and no
     // chain pair, where the time is the longest message's in any order.
-    const bool sorted = L.least == L.longest ? have <= kChainEntries && chains : MANY || chains || r.algos;
+    const bool sorted = L.least == L.longest ? have <= kChainMessages && chains : MANY || chains || r.algos;
     uint32_t count = have;
     if (sorted) {
         // first position of each bin, longest first: an exclusive scan over the reversed bins
@@ -214,7 +214,7 @@ __device__ __forceinline__ void ragged_tile(const RaggedArgs &r, uint64_t base, 
         for (int j = 0; j < kPerThread; ++j)
             if (nb[j]) L.order[L.bins[len_bin(nb[j])] + rank[j]] = uint16_t(uint32_t(j) * kRaggedThreads + tid);
     }
-    const uint32_t nchain = sorted && chains ? min(count, kChainEntries) : 0u;
+    const uint32_t nchain = sorted && chains ? min(count, kChainMessages) : 0u;
     if (tid == 0) L.next = nchain;
     __syncthreads();
     if (nchain) {
@@ -355,7 +355,7 @@ __global__ __launch_bounds__(kPickThreads) void k_long_pick(LongWs w)
     };
     auto fits = [&](uint64_t c) {
         uint32_t g = 0;
-        for (int a = 0; a < 3; ++a) g += (messages(a, c) + kChainEntries - 1u) / kChainEntries;
+        for (int a = 0; a < 3; ++a) g += (messages(a, c) + kChainMessages - 1u) / kChainMessages;
         return g <= kLongGroups;
     };
     // the smallest c that fits, a thousandth of what is left of the range at a time
@@ -381,7 +381,7 @@ __global__ __launch_bounds__(kPickThreads) void k_long_pick(LongWs w)
             m->pos[a] = pos;
             m->group[o] = group;
             pos += m->count[a];
-            group += (m->count[a] + kChainEntries - 1u) / kChainEntries;
+            group += (m->count[a] + kChainMessages - 1u) / kChainMessages;
         }
         m->group[3] = group;
     }
@@ -408,12 +408,12 @@ template <int A>
 __device__ __forceinline__ void long_group(const RaggedArgs &r, const LongWs &w, uint32_t k, uint32_t groups, RaggedLds &L,
                                            uint32_t *ring)
 {
-    const uint32_t lane = threadIdx.x % 64u, count = w.meta->count[A], lead = min(groups, kChainEntries);
-    const uint32_t beside = min(lead * (kChainEntries - 1u), count - lead);  // of them, from the end of the order
+    const uint32_t lane = threadIdx.x % 64u, count = w.meta->count[A], lead = min(groups, kChainMessages);
+    const uint32_t beside = min(lead * (kChainMessages - 1u), count - lead);  // of them, from the end of the order
     uint32_t at = kNoLong;
-    if (lane < kChainEntries) {
+    if (lane < kChainMessages) {
         if (k >= lead) {
-            const uint32_t x = lead + (k - lead) * kChainEntries + lane;
+            const uint32_t x = lead + (k - lead) * kChainMessages + lane;
             if (x < count - beside) at = x;
         } else if (lane == 0) {
             at = k;
@@ -451,6 +451,48 @@ __global__ __launch_bounds__(kRaggedThreads, 4) void k_long_tiles(RaggedArgs r, 
     else if (b < tiles) ragged_tile<SM3, true>(r, base, m->from[SM3], L, ring);
     else if (b < 2u * tiles) ragged_tile<SHA1, true>(r, base, m->from[SHA1], L, ring);
     else ragged_tile<MD5, true>(r, base, m->from[MD5], L, ring);
+}
+
+// ---------------------------------------------------------------------------------------
+// Fixed-length batches of few messages
+// ---------------------------------------------------------------------------------------
+//
+// With at most 128 messages to a CU half its SIMDs would be idle and each wave's time is its
+// instructions: one workgroup on each CU runs two chain pairs of up to 64 messages, their
+// schedules on the other two SIMDs.  (Windows of 64 entries: the schedule wave works with all
+// its lanes.)  1,000 x 4 KiB: SHA-1 84.9 us with a lane to a message, 64.2 so; SM3 172 and 127.
+
+template <int A>
+__global__ __launch_bounds__(kRaggedThreads) void k_fixed_chain(const uint8_t *__restrict__ msgs, uint64_t n, uint64_t len,
+                                                               uint32_t per, uint8_t *__restrict__ out)
+{
+    constexpr uint32_t E = 64;
+    __shared__ __align__(16) uint32_t ring[2][kChainRingWords<A, E>];
+    __shared__ uint32_t tails[2][kChainTailWords<E>], simds[kRaggedThreads / 64];
+    __shared__ ChainSync sync[2];
+    const uint32_t lane = threadIdx.x % 64u, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64u);
+    if (lane == 0) simds[wave] = wave_simd();
+    if (threadIdx.x < 2) sync[threadIdx.x] = ChainSync{0, 0};
+    __syncthreads();
+    // chain waves on two SIMDs, schedule waves on the other two (by wave number if the four
+    // waves should not be on four SIMDs)
+    uint32_t seen = 0;
+#pragma unroll
+    for (uint32_t w = 0; w < kRaggedThreads / 64; ++w) seen |= 1u << simds[w];
+    const uint32_t role = __builtin_amdgcn_readfirstlane(seen == 15u ? simds[wave] : wave), pair = role % 2u;
+    const uint64_t first = (uint64_t(xcd_contiguous(blockIdx.x, gridDim.x)) * 2u + pair) * per, i = first + lane;
+    if (first >= n) return;  // both waves of the last pair
+    const uint32_t blocks = lane < per && i < n ? uint32_t(block_count(len)) : 0u;
+    if (role < 2u) {
+        uint32_t s[8];
+        __builtin_amdgcn_s_setprio(3);
+        chain_run<A, E>(blocks, ring[pair], &sync[pair], s);
+        if (blocks) store_digest<A>(out + i * Traits<A>::kDigest, s, Traits<A>::kDigest);
+    } else {
+        const uint64_t address = uint64_t(reinterpret_cast<uintptr_t>(msgs)) + (blocks ? i : first) * len;
+        __builtin_amdgcn_s_setprio(2);
+        chain_schedule<A, E, E>(address, len, blocks, ring[pair], tails[pair], &sync[pair]);
+    }
 }
 
 // How a batch is dealt out: messages per tile, tiles, workgroups per tile, and how many times
@@ -499,6 +541,29 @@ hipError_t launch_ragged(const uint8_t *algos, int algo, const uint8_t *msgs, co
     case SM3: hipLaunchKernelGGL((few ? k_ragged<SM3, false> : k_ragged<SM3, true>), grid, block, 0, stream, r); break;
     default: return hipErrorInvalidValue;
     }
+    return hipGetLastError();
+}
+
+bool fixed_chain_applies(int algo, uint64_t n, uint64_t len)
+{
+    // Where it was measured faster than a lane to a message (us, lane / chain): SM3 from three
+    // blocks on (120 bytes: 14.7 / 13.4; 512: 28.3 / 24.9), SHA-1 from four (250 bytes: 13.2 /
+    // 11.8; 120: 10.5 / 10.5), and past 32 messages to a pair, where a window is one block and
+    // the schedules take longer than the rounds, from 32 (20,011 x 512: 16.0 / 17.3; x 4 KiB:
+    // 89 / 79).  Not MD5, whose schedule is one addition to a word (1,000 x 1 KiB: 17.1 / 17.2).
+    const uint64_t nb = block_count(len), cus = device_simds() / 4u;
+    if (n > 128u * cus || nb >= 0x80000000u) return false;
+    return algo == SM3 ? nb >= 3 : algo == SHA1 && nb >= (n <= 64u * cus ? 4u : 32u);
+}
+
+hipError_t launch_fixed_chain(int algo, const uint8_t *msgs, uint64_t n, uint64_t len, uint8_t *out, hipStream_t stream)
+{
+    const uint64_t pairs = 2u * uint64_t(device_simds() / 4u);
+    const uint32_t per = uint32_t((n + pairs - 1) / pairs);  // messages of a pair
+    const dim3 grid{uint32_t((n + 2u * per - 1) / (2u * per)), 1, 1}, block{kRaggedThreads, 1, 1};
+    if (algo == SHA1) hipLaunchKernelGGL(k_fixed_chain<SHA1>, grid, block, 0, stream, msgs, n, len, per, out);
+    else if (algo == SM3) hipLaunchKernelGGL(k_fixed_chain<SM3>, grid, block, 0, stream, msgs, n, len, per, out);
+    else return hipErrorInvalidValue;
     return hipGetLastError();
 }
 

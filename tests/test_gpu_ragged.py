@@ -76,6 +76,28 @@ def test_many_tiles(hb, n):
     assert_same(got, oracle.hash_batch(algos, msgs, offs, lens), "many tiles mixed")
 
 
+@pytest.mark.parametrize("algo", [1, 2])
+@pytest.mark.parametrize("per_cu", [0, 1, 63, 64, 65, 128])
+def test_few_fixed_messages(hb, algo, per_cu):
+    """Fixed-length batches of few messages (chain pairs): one to 64 messages to a pair, a
+    ragged last one, every residue of the last block that changes its shape, any start."""
+    import torch
+
+    cus = hb.device_info()["cu_count"]
+    n = max(1, per_cu * cus - 3 if per_cu < 128 else per_cu * cus)
+    for L in (120, 128, 183, 247, 256, 2047) if per_cu < 64 else (184, 2040):
+        print(f"case few fixed algo={algo} n={n} L={L}", flush=True)
+        b = workloads.fixed_batch(algo, n, L, seed=L)
+        dev = torch.empty(b.messages.size + 1, dtype=torch.uint8, device="cuda")
+        msgs = dev[1:] if L % 2 else dev[:-1]
+        msgs.copy_(torch.from_numpy(b.messages))
+        ds = oracle.DIGEST_SIZE[algo]
+        buf, out = guarded_out(n, ds)
+        hb.hash_batch_fixed(algo, msgs, n, L, out=out)
+        check_guard(buf, n, ds)
+        assert_same(out.cpu().numpy(), oracle.hash_batch(algo, b.messages, b.offsets, b.lengths), f"few fixed {algo} {L}")
+
+
 @pytest.mark.parametrize("algo", [None, 0, 1, 2])
 def test_long_messages_first(hb, monkeypatch, algo):
     """A plan whose batch has more than one round of tiles picks the longest messages out
