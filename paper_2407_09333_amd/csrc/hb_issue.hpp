@@ -406,6 +406,116 @@ template <int A> __device__ __forceinline__ void compress_many(uint32_t s[8], co
     else sm3_compress_many(s, w);
 }
 
+// ---------------------------------------------------------------------------------------
+// A block whose words are the same for every lane -- the padding-only last block of a
+// fixed-length batch -- from schedule words the host has formed: the rounds alone, a third
+// fewer instructions (SM3 16 a round for 24).  Words: as md5_sched / sha1_sched / sm3_sched
+// (hb_long.hpp) give them: X + T; W + K; W' and then W.
+// ---------------------------------------------------------------------------------------
+
+template <int A> struct UniformWords;
+template <> struct UniformWords<MD5> { uint32_t w[64]; };
+template <> struct UniformWords<SHA1> { uint32_t w[80]; };
+template <> struct UniformWords<SM3> { uint32_t w[128]; };
+
+#define HB_MD5_U(a, b, c, d, x, s, F)                                                         \
+    "v_bitop3_b32 %[t], %[" #b "], %[" #c "], %[" #d "] bitop3:" F "\n\t"                     \
+    HB_WIDE                                                                                   \
+    "v_add3_u32 %[" #a "], %[" #a "], %[t], %[" #x "]\n\t"                                    \
+    "v_alignbit_b32 %[" #a "], %[" #a "], %[" #a "], " #s "\n\t"                              \
+    HB_PLAIN                                                                                  \
+    "v_add_u32 %[" #a "], %[" #a "], %[" #b "]\n\t"
+#define HB_MD5_U4(F, s0, s1, s2, s3)                                                          \
+    asm volatile(HB_MD5_U(a, b, c, d, x0, s0, F) HB_MD5_U(d, a, b, c, x1, s1, F)              \
+                 HB_MD5_U(c, d, a, b, x2, s2, F) HB_MD5_U(b, c, d, a, x3, s3, F)              \
+                 : [a] "+v"(a), [b] "+v"(b), [c] "+v"(c), [d] "+v"(d), [t] "=&v"(t)           \
+                 : [x0] "s"(x[0]), [x1] "s"(x[1]), [x2] "s"(x[2]), [x3] "s"(x[3]))
+
+#define HB_SHA1_U(a, b, c, d, e, w, F)                                                        \
+    "v_bitop3_b32 %[f], %[" #b "], %[" #c "], %[" #d "] bitop3:" F "\n\t"                     \
+    "v_add_u32 %[" #e "], %[" #w "], %[" #e "]\n\t"                                           \
+    HB_WIDE                                                                                   \
+    "v_alignbit_b32 %[u], %[" #a "], %[" #a "], 27\n\t"                                       \
+    "v_alignbit_b32 %[" #b "], %[" #b "], %[" #b "], 2\n\t"                                   \
+    "v_add3_u32 %[" #e "], %[" #e "], %[f], %[u]\n\t"                                         \
+    HB_PLAIN
+#define HB_SHA1_U5(F)                                                                         \
+    asm volatile(HB_SHA1_U(a, b, c, d, e, x0, F) HB_SHA1_U(e, a, b, c, d, x1, F)              \
+                 HB_SHA1_U(d, e, a, b, c, x2, F) HB_SHA1_U(c, d, e, a, b, x3, F)              \
+                 HB_SHA1_U(b, c, d, e, a, x4, F)                                              \
+                 : [a] "+v"(a), [b] "+v"(b), [c] "+v"(c), [d] "+v"(d), [e] "+v"(e), [f] "=&v"(f), [u] "=&v"(u) \
+                 : [x0] "s"(x[0]), [x1] "s"(x[1]), [x2] "s"(x[2]), [x3] "s"(x[3]), [x4] "s"(x[4]))
+
+#define HB_SM3_U(a, b, c, d, e, f, g, h, w, x, k, FF, GG)                                     \
+    "v_add_u32 %[s], %[" #k "], %[" #e "]\n\t"                                                \
+    "v_bitop3_b32 %[p], %[" #a "], %[" #b "], %[" #c "] bitop3:" FF "\n\t"                    \
+    "v_bitop3_b32 %[q], %[" #e "], %[" #f "], %[" #g "] bitop3:" GG "\n\t"                    \
+    "v_add_u32 %[s], %[s], %[r]\n\t"                                                          \
+    "v_add_u32 %[" #h "], %[" #w "], %[" #h "]\n\t"                                           \
+    "v_add_u32 %[" #d "], %[" #d "], %[p]\n\t"                                                \
+    "v_add_u32 %[" #d "], %[" #x "], %[" #d "]\n\t"                                           \
+    HB_SM3_H0 HB_SM3_H1(b, d, f, h) HB_SM3_H2(d) HB_SM3_E(h)
+#define HB_SM3_U4(FF, GG)                                                                     \
+    asm volatile(HB_SM3_U(a, b, c, d, e, f, g, h, w0, x0, k0, FF, GG)                         \
+                 HB_SM3_U(d, a, b, c, h, e, f, g, w1, x1, k1, FF, GG)                         \
+                 HB_SM3_U(c, d, a, b, g, h, e, f, w2, x2, k2, FF, GG)                         \
+                 HB_SM3_U(b, c, d, a, f, g, h, e, w3, x3, k3, FF, GG)                         \
+                 : [a] "+v"(a), [b] "+v"(b), [c] "+v"(c), [d] "+v"(d), [e] "+v"(e), [f] "+v"(f), [g] "+v"(g), \
+                   [h] "+v"(h), [r] "+v"(r), [p] "=&v"(p), [q] "=&v"(q), [s] "=&v"(s)         \
+                 : [x0] "s"(x[0]), [x1] "s"(x[1]), [x2] "s"(x[2]), [x3] "s"(x[3]), \
+                   [w0] "s"(x[64]), [w1] "s"(x[65]), [w2] "s"(x[66]), [w3] "s"(x[67]), \
+                   [k0] "s"(sm3_tj(j)), [k1] "s"(sm3_tj(j + 1)), [k2] "s"(sm3_tj(j + 2)), [k3] "s"(sm3_tj(j + 3)))
+
+#define HB_CONSTANT __attribute__((address_space(4)))
+
+// The words are read a few rounds at a time, each read behind an opaque zero: all together
+// would not fit the scalar registers, and the compiler would read them so.
+template <int A> __device__ __forceinline__ void compress_uniform(uint32_t v[8], const HB_CONSTANT uint32_t *words)
+{
+    auto next = [&](int j) {
+        uint32_t zero = 0;
+        asm volatile("" : "+s"(zero));
+        return words + zero + j;
+    };
+    if constexpr (A == MD5) {
+        uint32_t a = v[0], b = v[1], c = v[2], d = v[3], t;
+#pragma unroll
+        for (int j = 0; j < 64; j += 4) {
+            const HB_CONSTANT uint32_t *x = next(j);
+            if (j < 16) HB_MD5_U4(HB_TT_CH, 25, 20, 15, 10);
+            else if (j < 32) HB_MD5_U4(HB_TT_G, 27, 23, 18, 12);
+            else if (j < 48) HB_MD5_U4(HB_TT_XOR3, 28, 21, 16, 9);
+            else HB_MD5_U4(HB_TT_I, 26, 22, 17, 11);
+        }
+        v[0] += a; v[1] += b; v[2] += c; v[3] += d;
+    } else if constexpr (A == SHA1) {
+        uint32_t a = v[0], b = v[1], c = v[2], d = v[3], e = v[4], f, u;
+#pragma unroll
+        for (int j = 0; j < 80; j += 5) {
+            const HB_CONSTANT uint32_t *x = next(j);
+            if (j < 20) HB_SHA1_U5(HB_TT_CH);
+            else if (j < 40 || j >= 60) HB_SHA1_U5(HB_TT_XOR3);
+            else HB_SHA1_U5(HB_TT_MAJ);
+        }
+        v[0] += a; v[1] += b; v[2] += c; v[3] += d; v[4] += e;
+    } else {
+        uint32_t a = v[0], b = v[1], c = v[2], d = v[3], e = v[4], f = v[5], g = v[6], h = v[7], p, q, r = rotl<12>(a), s;
+#pragma unroll
+        for (int j = 0; j < 64; j += 4) {
+            const HB_CONSTANT uint32_t *x = next(j);
+            if (j < 16) HB_SM3_U4(HB_TT_XOR3, HB_TT_XOR3);
+            else HB_SM3_U4(HB_TT_MAJ, HB_TT_CH);
+        }
+        v[0] ^= a; v[1] ^= b; v[2] ^= c; v[3] ^= d; v[4] ^= e; v[5] ^= f; v[6] ^= g; v[7] ^= h;
+    }
+}
+
+#undef HB_MD5_U
+#undef HB_MD5_U4
+#undef HB_SHA1_U
+#undef HB_SHA1_U5
+#undef HB_SM3_U
+#undef HB_SM3_U4
 #undef HB_MD5_I
 #undef HB_SHA1_PLAIN
 #undef HB_SHA1_WIDE

@@ -62,9 +62,11 @@ constexpr int kCpolNonTemporal = 2;
 // loads.  All three run five waves per SIMD, the most the LDS holds (8 KiB per wave).  On
 // 2^20 x 1 KiB the three launches took 1,132 us with the compiler's order of the
 // compressions and take 998 us with the shared-SIMD order (hb_issue.hpp).
-template <int A, bool MANY>
+// PAD: len is a multiple of 64, and `pad` the schedule words of the padding-only last block,
+// the same for every message of the batch.
+template <int A, bool MANY, bool PAD = false>
 __device__ __forceinline__ void plain_lds_wave(const uint8_t *__restrict__ msgs, uint64_t n, uint64_t len,
-                                               uint8_t *__restrict__ out)
+                                               uint8_t *__restrict__ out, const HB_CONSTANT uint32_t *pad = nullptr)
 {
     constexpr bool kStream = A == MD5;  // non-temporal loads
     __shared__ u32x4 slice[kPlainBlock / 64][512];  // per wave: 64 messages x 128 bytes
@@ -151,7 +153,9 @@ __device__ __forceinline__ void plain_lds_wave(const uint8_t *__restrict__ msgs,
         load_full_block(m, blk, w);
         compress<A, MANY>(s, w);
     }
-    if (len % 64u == 0) {
+    if constexpr (PAD) {
+        compress_uniform<A>(s, pad);
+    } else if (len % 64u == 0) {
         // the last block is padding only -- 0x80, zeros, the bit length -- and the same for
         // every message of the batch: wave-uniform words, nothing to read or assemble
         constexpr bool kBE = Traits<A>::kBE;
@@ -179,6 +183,18 @@ __global__ __launch_bounds__(kPlainBlock) __attribute__((amdgpu_waves_per_eu(A =
 k_plain_lds(const uint8_t *__restrict__ msgs, uint64_t n, uint64_t len, uint8_t *__restrict__ out)
 {
     plain_lds_wave<A, true>(msgs, n, len, out);
+}
+
+// As k_plain_lds for lengths divisible by 64: the last block's words come formed from the host
+// (compress_uniform).  2^22 x 256 bytes, a fifth of whose blocks are such: SM3 602 us with the
+// schedule expanded by every lane, 565 so, SHA-1 330 and 310; 300,007 x 64 SM3 21.5 and 20.4.
+template <int A>
+__global__ __launch_bounds__(kPlainBlock) __attribute__((amdgpu_waves_per_eu(A == MD5 ? 5 : 4))) void
+k_plain_lds_pad(const uint8_t *__restrict__ msgs, uint64_t n, uint64_t len, uint8_t *__restrict__ out, UniformWords<A>)
+{
+    // the words where they are in the kernel's arguments, after four of eight bytes
+    const HB_CONSTANT uint32_t *pad = (const HB_CONSTANT uint32_t *)__builtin_amdgcn_kernarg_segment_ptr() + 8;
+    plain_lds_wave<A, true, true>(msgs, n, len, out, pad);
 }
 
 template <int A>
@@ -321,13 +337,49 @@ static hipError_t launch_a(const uint8_t *msgs, uint64_t n, uint64_t fixed_len, 
     return hipGetLastError();
 }
 
+// Schedule words of the padding-only block of a message of len bytes (RFC 1321 Sec. 3.1-3.2,
+// FIPS 180-4 Sec. 5.1.1 and 6.1.2, GB/T 32905 Sec. 5.2-5.3.2).
+template <int A> static UniformWords<A> pad_words(uint64_t len)
+{
+    UniformWords<A> u;
+    uint32_t W[80] = {};
+    const uint64_t bits = len << 3;
+    auto rol = [](uint32_t x, int s) { return (x << s) | (x >> (32 - s)); };
+    W[0] = A == MD5 ? 0x80u : 0x80000000u;
+    W[14] = A == MD5 ? uint32_t(bits) : uint32_t(bits >> 32);
+    W[15] = A == MD5 ? uint32_t(bits >> 32) : uint32_t(bits);
+    if constexpr (A == MD5) {
+        for (int i = 0; i < 64; ++i) {
+            const int j = i & 15;
+            u.w[i] = W[i < 16 ? j : (i < 32 ? (1 + 5 * j) & 15 : (i < 48 ? (5 + 3 * j) & 15 : (7 * j) & 15))] + kMd5T[i];
+        }
+    } else if constexpr (A == SHA1) {
+        for (int t = 0; t < 80; ++t) {
+            if (t >= 16) W[t] = rol(W[t - 3] ^ W[t - 8] ^ W[t - 14] ^ W[t - 16], 1);
+            u.w[t] = W[t] + (t < 20 ? 0x5a827999u : (t < 40 ? 0x6ed9eba1u : (t < 60 ? 0x8f1bbcdcu : 0xca62c1d6u)));
+        }
+    } else {
+        for (int i = 16; i < 68; ++i) {
+            const uint32_t x = W[i - 16] ^ W[i - 9] ^ rol(W[i - 3], 15);
+            W[i] = x ^ rol(x, 15) ^ rol(x, 23) ^ rol(W[i - 13], 7) ^ W[i - 6];
+        }
+        for (int j = 0; j < 64; ++j) {
+            u.w[j] = W[j] ^ W[j + 4];
+            u.w[64 + j] = W[j];
+        }
+    }
+    return u;
+}
+
 template <int A>
 static hipError_t launch_lds_a(const uint8_t *msgs, uint64_t n, uint64_t len, uint8_t *out, hipStream_t stream)
 {
     const uint64_t blocks = (n + kPlainBlock - 1) / kPlainBlock;
     if (blocks > 0x7fffffffull) return hipErrorInvalidConfiguration;
-    hipLaunchKernelGGL(few_waves(n) ? k_plain_lds_few<A> : k_plain_lds<A>, dim3(uint32_t(blocks)), dim3(kPlainBlock), 0,
-                       stream, msgs, n, len, out);
+    const dim3 grid{uint32_t(blocks), 1, 1}, block{kPlainBlock, 1, 1};
+    if (few_waves(n)) hipLaunchKernelGGL(k_plain_lds_few<A>, grid, block, 0, stream, msgs, n, len, out);
+    else if (len % 64u == 0) hipLaunchKernelGGL(k_plain_lds_pad<A>, grid, block, 0, stream, msgs, n, len, out, pad_words<A>(len));
+    else hipLaunchKernelGGL(k_plain_lds<A>, grid, block, 0, stream, msgs, n, len, out);
     return hipGetLastError();
 }
 
