@@ -61,8 +61,8 @@ ALGO_NAMES = ["md5", "sha1", "sm3"]
 # byte order.  MD5's words are little-endian as loaded, so on dword-aligned messages (the
 # fixed-length batches) it needs none: 64 steps x 5 + 4.
 OPS_PER_BLOCK = {"md5": 324, "sha1": 613, "sm3": 1348}
-# The same count split by issue rate: (full-rate, half-rate).  A gfx950 SIMD issues a wave64
-# VALU instruction in 2 cycles for the plain 32-bit ops used here (v_bitop3_b32, VOP2
+# The same count split by issue rate: (full-rate, half-rate).  One instruction kind by itself
+# goes at 2 cycles per wave64 instruction and SIMD for the plain 32-bit ops used here (v_bitop3_b32, VOP2
 # v_add_u32 / v_xor_b32: 32 lanes per clock, the rate behind the 157.3 TFLOP/s fp32 vector
 # peak) and in 4 cycles for the others (v_add3_u32, v_xad_u32, v_alignbit_b32, v_perm_b32).
 #   MD5   per step F, + T, + b (full); add3, rotate (half); 4 final adds (full)
@@ -86,6 +86,23 @@ def mix_peak_tops(name):
 
 
 ALU_PEAK_MIX_TOPS = {a: mix_peak_tops(a) for a in OPS_PER_BLOCK}  # MD5 56.37, SHA-1 47.59, SM3 47.93
+
+
+def co_issue_cycles(name):
+    """Least SIMD cycles per wave and block when waves share a SIMD's two VALU places.  A
+    wave64 instruction holds a place for 4 cycles; a full-rate op may take either place, a
+    half-rate one only the first, so `half` and `total` ops need max(4 half, 2 total) cycles.
+    Where the half-rate ops are the longer side, x fused sums (v_add3, v_xad: half-rate) may
+    be written as two full-rate ops each, and x = (2 half - total) / 3 evens the two sides."""
+    full, half = OPS_BY_RATE[name]
+    x = max(0.0, (2 * half - (full + half)) / 3)
+    return max(4 * (half - x), 2 * (full + half + x))
+
+
+# the roofline's peak: the counted ops over those cycles (648, 1,351 and 2,949 per wave and
+# block) on 1,024 SIMDs at 2.4 GHz
+ALU_PEAK_CO_ISSUE_TOPS = {a: OPS_PER_BLOCK[a] * LANES * CUS * SIMDS_PER_CU * CLOCK_GHZ * 1e9 / co_issue_cycles(a) / 1e12
+                          for a in OPS_PER_BLOCK}  # MD5 78.64, SHA-1 71.39, SM3 71.89
 HBM_PEAK_GBS = 8000.0
 TRAFFIC_FILE = ROOT / "profiles" / "traffic.json"
 
@@ -127,7 +144,7 @@ def parse():
 def kernel_source_hash() -> str:
     """Hash of the sources the plain kernels are built from (the roofline kernel)."""
     h = hashlib.sha256()
-    for f in ("hb_device.hpp", "hb_kernels.hip"):
+    for f in ("hb_device.hpp", "hb_issue.hpp", "hb_kernels.hip"):
         h.update((ROOT / "paper_2407_09333_amd" / "csrc" / f).read_bytes())
     return h.hexdigest()[:16]
 
@@ -169,14 +186,17 @@ def record_traffic(fetch_dir: str, write_dir: str):
                      "--only-headline --no-cpu-baseline --steps 3 --warmup 1 --copy-calibration`, written by "
                      "`python3 bench.py --record-traffic FETCH_DIR WRITE_DIR`; each counter scaled by the factor "
                      "that makes it read 1 GiB for the plain 1 GiB copy kernel of that run "
-                     "(__amd_rocclr_copyBuffer). source_hash = hash of hb_device.hpp and hb_kernels.hip when "
+                     "(__amd_rocclr_copyBuffer). source_hash = hash of hb_device.hpp, hb_issue.hpp and "
+                     "hb_kernels.hip when "
                      "the counters were taken.",
            "read_factor": rf, "write_factor": wf}
     for a, name in enumerate(ALGO_NAMES):
-        # the default plain kernel (LDS-staged) and the alternative (per lane)
-        kernels = {"fixed": f"hb::k_plain_lds<{a}>", "fixed_alt": f"hb::k_plain<{a}, true>"}
-        for key, kname in kernels.items():
-            k = next((k for k in fetch if kname in k), None)
+        # the default plain kernel (LDS-staged; its form for lengths divisible by 64 where the
+        # run launched that) and the alternative (per lane)
+        kernels = {"fixed": (f"hb::k_plain_lds_pad<{a}>", f"hb::k_plain_lds<{a}>"),
+                   "fixed_alt": (f"hb::k_plain<{a}, true>",)}
+        for key, knames in kernels.items():
+            k, kname = next(((k, kn) for kn in knames for k in fetch if kn in k), (None, None))
             if k is None or k not in write:
                 continue
             fb = sum(fetch[k]) / len(fetch[k]) * rf
@@ -250,8 +270,9 @@ def bench_valu_probe():
     """The integer-VALU issue rates the roofline's peak rests on (hb_probe_valu): SIMD cycles
     per wave instruction for each instruction kind and two mixes, and per wave and 64-byte
     block for each algorithm's compression from registers, at 1, 4 and 8 waves per SIMD (one
-    wave alone shows a lone chain's issue limit); beside them the op-mix model (2 cycles per
-    full-rate op, 4 per half-rate op) and the fraction of it each compression reaches."""
+    wave alone shows a lone chain's issue limit); beside them the cycles of the two issue
+    models (every op at its own kind's rate; both VALU places kept busy) and the fraction of
+    each that the compressions as compiled from C++ reach."""
     from paper_2407_09333_amd import hb
 
     out = {"unit": "SIMD cycles per wave instruction (md5/sha1/sm3: per wave and 64-byte block)"}
@@ -264,6 +285,9 @@ def bench_valu_probe():
     out["mix_model_cycles_per_block"] = model
     out["compression_frac_of_mix_peak_at_4_waves"] = {
         a: round(model[a] / out["waves_per_simd_4"][a]["cycles"], 3) for a in ALGO_NAMES}
+    out["co_issue_cycles_per_block"] = {a: round(co_issue_cycles(a), 1) for a in ALGO_NAMES}
+    out["compression_frac_of_co_issue_peak_at_4_waves"] = {
+        a: round(co_issue_cycles(a) / out["waves_per_simd_4"][a]["cycles"], 3) for a in ALGO_NAMES}
     return out
 
 
@@ -320,7 +344,8 @@ def bench_fixed(args):
             "kernel_ms_min": round(float(np.min(per_step[name])), 4),
             "hashed_GBps": round(payload / t / 1e9, 1),
             "alu_Tops": round(ops / t / 1e12, 2),
-            "alu_frac": round(ops / t / 1e12 / ALU_PEAK_MIX_TOPS[name], 4),
+            "alu_frac": round(ops / t / 1e12 / ALU_PEAK_CO_ISSUE_TOPS[name], 4),
+            "alu_frac_no_co_issue": round(ops / t / 1e12 / ALU_PEAK_MIX_TOPS[name], 4),
             "alu_frac_one_op_per_lane_clock": round(ops / t / 1e12 / ALU_PEAK_TOPS, 4),
             "hbm_frac_payload": round(payload / t / 1e9 / HBM_PEAK_GBS, 4),
         }
@@ -351,14 +376,18 @@ def bench_fixed(args):
     t_dom = kms[dom] / 1e3
     ops_dom = blocks * OPS_PER_BLOCK[dom]
     traffic = measured_traffic(dom, "fixed")
-    roofline = {"kernel": f"k_plain_lds<{dom}>", "bound": "alu", "achieved": round(ops_dom / t_dom / 1e12, 3),
-                "peak": round(ALU_PEAK_MIX_TOPS[dom], 2), "unit": "Tops/s (int32 lane-ops)",
-                "frac": round(ops_dom / t_dom / 1e12 / ALU_PEAK_MIX_TOPS[dom], 4), "traffic": traffic,
+    roofline = {"kernel": f"k_plain_lds_pad<{dom}>", "bound": "alu", "achieved": round(ops_dom / t_dom / 1e12, 3),
+                "peak": round(ALU_PEAK_CO_ISSUE_TOPS[dom], 2), "unit": "Tops/s (int32 lane-ops)",
+                "frac": round(ops_dom / t_dom / 1e12 / ALU_PEAK_CO_ISSUE_TOPS[dom], 4), "traffic": traffic,
                 "ops_per_launch": ops_dom, "ops_per_block": OPS_PER_BLOCK[dom], "blocks_per_launch": blocks,
                 "ops_per_block_full_half_rate": list(OPS_BY_RATE[dom]),
-                "peak_note": "peak for the algorithm's op mix: full-rate ops (bitop3, VOP2 add/xor) 2 cycles, "
-                             "half-rate ops (add3, xad, alignbit, perm) 4 cycles per wave64 instruction per SIMD, "
-                             "1,024 SIMDs at 2.4 GHz",
+                "peak_note": "peak for the algorithm's op mix with both of a SIMD's VALU places busy: a wave64 "
+                             "instruction holds a place 4 cycles; bitop3 and VOP2 add/xor go to either place, "
+                             "add3, xad, alignbit and perm to one; fused sums traded for plain adds until the "
+                             "two are even; 1,024 SIMDs at 2.4 GHz.  peak_no_co_issue adds up each kind's own "
+                             "rate (2 and 4 cycles) instead",
+                "peak_no_co_issue": round(ALU_PEAK_MIX_TOPS[dom], 2),
+                "frac_no_co_issue": round(ops_dom / t_dom / 1e12 / ALU_PEAK_MIX_TOPS[dom], 4),
                 "peak_one_op_per_lane_clock": round(ALU_PEAK_TOPS, 2),
                 "frac_one_op_per_lane_clock": round(ops_dom / t_dom / 1e12 / ALU_PEAK_TOPS, 4)}
     rec = {
@@ -458,7 +487,8 @@ def _inputs_record(args, name, **arrays):
 
 def bench_uneven(args, steps=5, warmup=2):
     """SM3 over 2^22 messages with lengths uniform on 0..4096 bytes, packed: the bucketed
-    persistent plan (hipGraph) against the plain one-lane-per-message kernel."""
+    plan (hipGraph) against the plain form (both take the tiled launch by default; the
+    autotuner may choose the plan's bucketed pipeline)."""
     import torch
 
     from paper_2407_09333_amd import hb, workloads
@@ -477,8 +507,8 @@ def bench_uneven(args, steps=5, warmup=2):
     _time_ms(lambda: plan_e.run(b.messages, offs, lens, algo=2, out=out_d), steps, 1, stream)
     same_eager = bool(torch.equal(out_d, out))
     k_ms = plan_e.kernel_ms()
-    # the same plan at the untuned defaults (16 waves per CU, one message per lane, default
-    # bursts), to state what the autotuner's choice gains
+    # the same plan untuned (the tiled launch, which the plain form runs too), to state what
+    # the autotuner's choice gains
     plan_d = hb.Plan(b.n, flags=hb.PLAN_GRAPH)
     t_default = _time_ms(lambda: plan_d.run(b.messages, offs, lens, algo=2, out=out_d), steps, 1, stream)
     same_default = bool(torch.equal(out_d, out))
@@ -500,14 +530,15 @@ def bench_uneven(args, steps=5, warmup=2):
         "batched_hash_kernel_ms": round(k_ms, 3),
         "plain_ms": round(t_plain, 3), "plain_GBps": round(payload / t_plain / 1e6, 1),
         "speedup_vs_plain": round(t_plain / t_plan, 3),
-        "alu_frac_batched_kernel": round(ops / (k_ms / 1e3) / 1e12 / ALU_PEAK_MIX_TOPS["sm3"], 4),
-        "alu_frac_plain": round(ops / (t_plain / 1e3) / 1e12 / ALU_PEAK_MIX_TOPS["sm3"], 4),
+        "alu_frac_batched_kernel": round(ops / (k_ms / 1e3) / 1e12 / ALU_PEAK_CO_ISSUE_TOPS["sm3"], 4),
+        "alu_frac_plain": round(ops / (t_plain / 1e3) / 1e12 / ALU_PEAK_CO_ISSUE_TOPS["sm3"], 4),
         "alu_frac_batched_kernel_one_op_per_lane_clock": round(ops / (k_ms / 1e3) / 1e12 / ALU_PEAK_TOPS, 4),
         "critical_path_ms_bound": round(_critical_path_ms(b.lengths, None, 2), 3),
         "plan_config": cfg,
         "plan_config_note": "autotuned: waves per CU x messages per lane x load scheme (variant 0 default "
                             "bursts, 1 next-block prefetch, 2 one block per load, 3 two-block and 4 "
-                            "four-block bursts), timed on this batch",
+                            "four-block bursts), timed on this batch against the tiled launch, which "
+                            "an untuned plan runs",
         "untuned_config": default_cfg, "untuned_ms": round(t_default, 3),
         "autotune_gain": round(t_default / t_plan, 3),
         "digests_equal_plain": same_plain,
@@ -522,8 +553,8 @@ def bench_uneven(args, steps=5, warmup=2):
 
 def bench_mixed(args, steps=3, warmup=1):
     """8 GiB, algorithm uniform per message, log-normal lengths (median 512 B, sigma 1.5,
-    cap 1 MiB): one fused persistent launch in a hipGraph against one plain launch per
-    algorithm."""
+    cap 1 MiB): the plan in a hipGraph against the plain form, the tiled launch with chain
+    groups for the longest messages in both."""
     import torch
 
     from paper_2407_09333_amd import hb, workloads
@@ -543,8 +574,8 @@ def bench_mixed(args, steps=3, warmup=1):
     payload = int(b.lengths.sum())
     nb = (b.lengths.astype(np.int64) + 8) // 64 + 1
     ops = int((nb * np.array([OPS_PER_BLOCK[a] for a in ALGO_NAMES])[b.algos]).sum())
-    # the throughput bound: each algorithm's ops at its own mix peak
-    t_peak_s = float(sum((nb[b.algos == k].sum() * OPS_PER_BLOCK[a]) / (ALU_PEAK_MIX_TOPS[a] * 1e12)
+    # the throughput bound: each algorithm's ops at its own co-issue peak
+    t_peak_s = float(sum((nb[b.algos == k].sum() * OPS_PER_BLOCK[a]) / (ALU_PEAK_CO_ISSUE_TOPS[a] * 1e12)
                          for k, a in enumerate(ALGO_NAMES)))
     cp = _critical_path_ms(b.lengths, b.algos, None)
     cp_ro = _critical_path_ms(b.lengths, b.algos, None, per_block=ROUNDS_ONLY_OPS)
@@ -554,6 +585,7 @@ def bench_mixed(args, steps=3, warmup=1):
         "messages": b.n, "payload_bytes": payload, "max_len": int(b.lengths.max()),
         "fused_ms": round(t_plan, 3), "fused_ms_median": round(st_plan["median"], 3),
         "fused_ms_min": round(st_plan["min"], 3), "fused_GBps": round(payload / t_plan / 1e6, 1),
+        # the plain form (one tiled launch for the three algorithms; the key's name is older)
         "plain_3_launches_ms": round(t_plain, 3), "plain_GBps": round(payload / t_plain / 1e6, 1),
         "speedup_vs_plain": round(t_plain / t_plan, 3),
         "throughput_bound_ms": round(t_peak_s * 1e3, 3),

@@ -307,7 +307,7 @@ class Plan:
             pass
 
 
-NOALLOC_MAX_N = 1 << 20  # the static workspace's message limit (include/hb.h)
+NOALLOC_MAX_N = 1 << 20  # messages per allocation-free call (include/hb.h)
 
 
 def hash_batch_bucketed_noalloc(messages, offsets, lengths, algo=None, algos=None, out=None, stream=None):
