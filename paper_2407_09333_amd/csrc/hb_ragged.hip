@@ -56,9 +56,9 @@ struct RaggedLds {
     uint16_t order[kTileMax];     // the tile's messages, longest bin first
     uint32_t bins[kLenBins];      // counts, then first positions
     uint32_t part[kRaggedThreads / 64];
-    unsigned long long blocks;    // of the tile's messages in all
-    uint32_t longest;             // largest block count
-    uint32_t least;               // smallest (0 where another algorithm's message is)
+    // of each wave's messages: block counts in all, the largest, the smallest (0 where
+    // another algorithm's message is)
+    uint32_t blocks[kRaggedThreads / 64], longest[kRaggedThreads / 64], least[kRaggedThreads / 64];
     uint32_t next;                // next position to hand out
     ChainSync sync;
     uint32_t tails[kChainTailWords<>];
@@ -69,6 +69,15 @@ struct RaggedLds {
 // This wave's SIMD and its workgroup's number on the CU (bits 5:4 and 19:16 of HW_ID).
 __device__ __forceinline__ uint32_t wave_simd() { return __builtin_amdgcn_s_getreg(4 | (4 << 6) | ((2 - 1) << 11)); }
 __device__ __forceinline__ uint32_t group_on_cu() { return __builtin_amdgcn_s_getreg(4 | (16 << 6) | ((4 - 1) << 11)); }
+
+// Fewest blocks of a tile's longest message that a chain pair is for: below, handing the
+// schedules over costs more than it saves (16,000 messages, us with / without a pair: MD5 of
+// 0 to 2,048 bytes 32.9 / 30.1, 0 to 4,096 55.3 / 56.1; SHA-1 of 0 to 257 14.0 / 13.7, 0 to
+// 1,024 27.6 / 29.3; SM3 of 0 to 130 13.7 / 15.2).
+template <int A> constexpr uint32_t kChainLeast = A == MD5 ? 48u : (A == SHA1 ? 8u : 3u);
+// Operations per block, and how many of them per message sorting has to save (ragged_tile).
+template <int A> constexpr uint32_t kBlockOps = A == MD5 ? 324u : (A == SHA1 ? 613u : 1348u);
+constexpr uint32_t kSortOps = 700;
 
 constexpr uint64_t kNoMessage = ~0ull;
 constexpr uint32_t kNoLong = 0xffffffffu;
@@ -115,19 +124,36 @@ __device__ __forceinline__ void chain_pair(const RaggedArgs &r, uint64_t i, Ragg
 // business of other workgroups (k_long_tiles).
 __device__ __forceinline__ bool is_long(uint32_t nb, uint32_t from) { return min(nb, kBins - 1u) >= from && nb < 0x80000000u; }
 
-template <int A, bool MANY>
+// Lane 63: op over the wave (rows of 16 lanes, then their last lanes into the rows after).
+// Cross-lane moves, not LDS: every tile does three of these before it can start hashing.
+template <class Op>
+__device__ __forceinline__ uint32_t reduce_to_last(uint32_t x, uint32_t none, Op op)
+{
+#define HB_STEP(ctrl) x = op(x, uint32_t(__builtin_amdgcn_update_dpp(int(none), int(x), ctrl, 0xf, 0xf, false)))
+    HB_STEP(0x111); HB_STEP(0x112); HB_STEP(0x114); HB_STEP(0x118);  // row_shr:1, 2, 4, 8
+    HB_STEP(0x142); HB_STEP(0x143);                                  // row_bcast:15, 31
+#undef HB_STEP
+    return x;
+}
+
+template <int A, bool MANY, int PER>
 __device__ __forceinline__ void ragged_tile(const RaggedArgs &r, uint64_t base, uint32_t long_from, RaggedLds &L,
                                             uint32_t *ring)
 {
     const uint32_t tid = threadIdx.x, lane = tid % 64u, wave = __builtin_amdgcn_readfirstlane(tid / 64u);
     const uint32_t have = uint32_t(min<uint64_t>(r.tile, r.n - base));
     // this thread's messages: block counts, 0 for none or one that is not this workgroup's
-    uint32_t nb[kPerThread], my_longest = 0, my_least = 0xffffffffu;
-    unsigned long long my_blocks = 0;
+    uint32_t nb[PER], longest = 0, least = 0xffffffffu, blocks = 0;
     // the first one's place, kept for the case that nothing is sorted
     const uint64_t i0 = base + min(tid, have - 1u), off0 = r.offs[i0], len0 = r.lens[i0];
+    // With a SIMD to each wave, its first byte, read for the line it brings in while the tile
+    // is looked over (65,536 SM3 messages of 0 to 257 bytes 20.5 us without, 20.4 with; 100 of
+    // MD5 and 0 to 512 13.5 and 13.3).  Waves that share a SIMD cover that time for each other
+    // (262,144 MD5 messages of 0 to 512 bytes: 29.6 without, 31.2 with).
+    uint32_t first_byte = 0;
+    if (!MANY && PER == 1 && len0) first_byte = r.msgs[off0];
 #pragma unroll
-    for (int j = 0; j < kPerThread; ++j) {
+    for (int j = 0; j < PER; ++j) {
         const uint32_t t = uint32_t(j) * kRaggedThreads + tid;
         nb[j] = 0;
         if (t < have) {
@@ -139,58 +165,69 @@ __device__ __forceinline__ void ragged_tile(const RaggedArgs &r, uint64_t base, 
                 for (uint32_t q = 0; q < r.stride / 4u; ++q) o[q] = 0u;
             }
             if (is_long(nb[j], long_from)) nb[j] = 0;
-            my_longest = max(my_longest, nb[j]);
-            my_least = min(my_least, nb[j]);
-            my_blocks += nb[j];
+            longest = max(longest, nb[j]);
+            least = min(least, nb[j]);
+            blocks += min(nb[j], 1u << 20);  // so that a tile's sum fits
         }
     }
     L.bins[tid] = 0;
-    if (lane == 0) L.simd[wave] = wave_simd();
+    longest = reduce_to_last(longest, 0u, [](uint32_t x, uint32_t y) { return max(x, y); });
+    least = reduce_to_last(least, 0xffffffffu, [](uint32_t x, uint32_t y) { return min(x, y); });
+    blocks = reduce_to_last(blocks, 0u, [](uint32_t x, uint32_t y) { return x + y; });
+    if (lane == 63) {
+        L.simd[wave] = wave_simd();
+        L.longest[wave] = longest;
+        L.least[wave] = least;
+        L.blocks[wave] = blocks;
+    }
     if (tid == 0) {
         L.group = group_on_cu();
-        L.blocks = 0; L.longest = 0; L.least = 0xffffffffu; L.sync.filled = 0; L.sync.taken = 0;
+        L.sync.filled = 0; L.sync.taken = 0;
     }
     __syncthreads();
-    uint32_t rank[kPerThread];  // within the bin
+    longest = 0, least = 0xffffffffu, blocks = 0;
 #pragma unroll
-    for (int j = 0; j < kPerThread; ++j) {
-        rank[j] = 0;
-        if (nb[j]) {
-            const uint32_t bin = len_bin(nb[j]), first = __builtin_amdgcn_readfirstlane(bin);
-            const uint64_t active = __ballot(1);
-            if (__ballot(bin == first) == active) {  // one atomic for the wave
-                const uint32_t below = __builtin_amdgcn_mbcnt_hi(uint32_t(active >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(active), 0u));
-                uint32_t b = 0;
-                if (below == 0) b = atomicAdd(&L.bins[first], uint32_t(__popcll(active)));
-                rank[j] = __builtin_amdgcn_readfirstlane(b) + below;
-            } else {
-                rank[j] = atomicAdd(&L.bins[bin], 1u);
-            }
-        }
+    for (uint32_t w = 0; w < kRaggedThreads / 64; ++w) {
+        longest = max(longest, L.longest[w]);
+        least = min(least, L.least[w]);
+        blocks += L.blocks[w];
     }
-    const uint32_t nb0 = __builtin_amdgcn_readfirstlane(nb[0]);
-    if (r.tile <= kRaggedThreads && __ballot(nb[0] == nb0) == ~0ull) my_blocks *= 64u;  // nothing to reduce
-    else for (int d = 32; d > 0; d >>= 1) {
-        my_longest = max(my_longest, uint32_t(__shfl_xor(my_longest, d)));
-        my_least = min(my_least, uint32_t(__shfl_xor(my_least, d)));
-        my_blocks += __shfl_xor(my_blocks, d);
-    }
-    if (lane == 0) {
-        atomicMax(&L.longest, my_longest);
-        atomicMin(&L.least, my_least);
-        atomicAdd(&L.blocks, my_blocks);
-    }
-    __syncthreads();
+    longest = __builtin_amdgcn_readfirstlane(longest);
+    least = __builtin_amdgcn_readfirstlane(least);
+    blocks = __builtin_amdgcn_readfirstlane(blocks);
+    if (longest == 0) return;  // no message of this algorithm
     // The chain pair takes the longest messages when the longest of all would take at least
     // twice the time that the two waves left need for all the others; nearer to even, two
-    // waves fewer for those cost more than the faster chains give.
-    const bool chains = L.longest >= 3u && L.longest < 0x80000000u && (unsigned long long)L.longest * 64u > L.blocks;
-    if (L.longest == 0) return;  // no message of this algorithm
+    // waves fewer for those cost more than the faster chains give; and it has enough blocks.
+    const bool chains = longest >= kChainLeast<A> && longest < 0x80000000u && uint64_t(longest) * 64u > blocks;
     // Nothing to gain from sorting: one block count throughout, or one wave a SIMD and no
-    // chain pair, where the time is the longest message's in any order.
-    const bool sorted = L.least == L.longest ? have <= kChainMessages && chains : MANY || chains || r.algos;
+    // chain pair, where the time is the longest message's in any order.  With one message a
+    // thread, sorting has each wave do about the mean of the block counts, not the largest,
+    // and takes some 2 us: it is left out where it saves fewer than kSortOps operations a
+    // message (262,144 messages, us with / without: MD5 of 0 to 64 bytes 14.3 / 12.2, 0 to 130
+    // 17.7 / 16.8; SHA-1 18.4 / 16.2 and 23.6 / 22.5; MD5 of 0 to 257 20.2 sorted, 22.6 before).
+    const bool worth = PER > 1 || (uint64_t(longest) * have - blocks) * kBlockOps<A> > uint64_t(kSortOps) * have;
+    const bool sorted = least == longest ? have <= kChainMessages && chains : chains || least == 0 || (MANY && worth);
     uint32_t count = have;
     if (sorted) {
+        uint32_t rank[PER];  // within the bin
+#pragma unroll
+        for (int j = 0; j < PER; ++j) {
+            rank[j] = 0;
+            if (nb[j]) {
+                const uint32_t bin = len_bin(nb[j]), first = __builtin_amdgcn_readfirstlane(bin);
+                const uint64_t active = __ballot(1);
+                if (__ballot(bin == first) == active) {  // one atomic for the wave
+                    const uint32_t below = __builtin_amdgcn_mbcnt_hi(uint32_t(active >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(active), 0u));
+                    uint32_t b = 0;
+                    if (below == 0) b = atomicAdd(&L.bins[first], uint32_t(__popcll(active)));
+                    rank[j] = __builtin_amdgcn_readfirstlane(b) + below;
+                } else {
+                    rank[j] = atomicAdd(&L.bins[bin], 1u);
+                }
+            }
+        }
+        __syncthreads();
         // first position of each bin, longest first: an exclusive scan over the reversed bins
         const uint32_t c = L.bins[kLenBins - 1u - tid];
         uint32_t sum = c;
@@ -211,12 +248,14 @@ __device__ __forceinline__ void ragged_tile(const RaggedArgs &r, uint64_t base, 
         L.bins[kLenBins - 1u - tid] = before + sum - c;
         __syncthreads();
 #pragma unroll
-        for (int j = 0; j < kPerThread; ++j)
+        for (int j = 0; j < PER; ++j)
             if (nb[j]) L.order[L.bins[len_bin(nb[j])] + rank[j]] = uint16_t(uint32_t(j) * kRaggedThreads + tid);
     }
     const uint32_t nchain = sorted && chains ? min(count, kChainMessages) : 0u;
-    if (tid == 0) L.next = nchain;
-    __syncthreads();
+    if (sorted) {
+        if (tid == 0) L.next = nchain;
+        __syncthreads();
+    }
     if (nchain) {
         chain_pair<A>(r, lane < nchain ? base + L.order[lane] : kNoMessage, L, ring);
     }
@@ -230,7 +269,7 @@ __device__ __forceinline__ void ragged_tile(const RaggedArgs &r, uint64_t base, 
         if (p >= count) break;
         if (p + lane < count) {
             uint64_t i = i0, off = off0, len = len0;
-            if (sorted || p >= kRaggedThreads) {
+            if (sorted || (PER > 1 && p >= kRaggedThreads)) {
                 i = base + (sorted ? L.order[p + lane] : p + lane);
                 off = r.offs[i];
                 len = r.lens[i];
@@ -240,26 +279,27 @@ __device__ __forceinline__ void ragged_tile(const RaggedArgs &r, uint64_t base, 
             store_digest<A>(r.out + i * r.stride, s, r.stride);
         }
     }
+    if (!MANY && PER == 1) asm volatile("" ::"v"(first_byte));
 }
 
-template <int A, bool MANY>
+template <int A, bool MANY, int PER>
 __global__ __launch_bounds__(kRaggedThreads, 4) void k_ragged(RaggedArgs r)
 {
     __shared__ RaggedLds L;
     __shared__ __align__(16) uint32_t ring[kChainRingWords<A>];
-    ragged_tile<A, MANY>(r, uint64_t(xcd_contiguous(blockIdx.x, gridDim.x)) * r.tile, kNoLong, L, ring);
+    ragged_tile<A, MANY, PER>(r, uint64_t(xcd_contiguous(blockIdx.x, gridDim.x)) * r.tile, kNoLong, L, ring);
 }
 
 // Three workgroups per tile, one per algorithm; SM3's (the longest chains) first.
-template <bool MANY>
+template <bool MANY, int PER>
 __global__ __launch_bounds__(kRaggedThreads, MANY ? 4 : 3) void k_ragged_mixed(RaggedArgs r, uint32_t tiles)
 {
     __shared__ RaggedLds L;
     __shared__ __align__(16) uint32_t ring[kChainRingWords<SM3>];
     const uint64_t base = uint64_t(xcd_contiguous(blockIdx.x % tiles, tiles)) * r.tile;
-    if (blockIdx.x < tiles) ragged_tile<SM3, MANY>(r, base, kNoLong, L, ring);
-    else if (blockIdx.x < 2u * tiles) ragged_tile<SHA1, MANY>(r, base, kNoLong, L, ring);
-    else ragged_tile<MD5, MANY>(r, base, kNoLong, L, ring);
+    if (blockIdx.x < tiles) ragged_tile<SM3, MANY, PER>(r, base, kNoLong, L, ring);
+    else if (blockIdx.x < 2u * tiles) ragged_tile<SHA1, MANY, PER>(r, base, kNoLong, L, ring);
+    else ragged_tile<MD5, MANY, PER>(r, base, kNoLong, L, ring);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -447,10 +487,10 @@ __global__ __launch_bounds__(kRaggedThreads, 4) void k_long_tiles(RaggedArgs r, 
     }
     const uint32_t b = blockIdx.x - kLongGroups;
     const uint64_t base = uint64_t(xcd_contiguous(b % tiles, tiles)) * r.tile;
-    if constexpr (ALGO >= 0) ragged_tile<ALGO, true>(r, base, m->from[ALGO], L, ring);
-    else if (b < tiles) ragged_tile<SM3, true>(r, base, m->from[SM3], L, ring);
-    else if (b < 2u * tiles) ragged_tile<SHA1, true>(r, base, m->from[SHA1], L, ring);
-    else ragged_tile<MD5, true>(r, base, m->from[MD5], L, ring);
+    if constexpr (ALGO >= 0) ragged_tile<ALGO, true, kPerThread>(r, base, m->from[ALGO], L, ring);
+    else if (b < tiles) ragged_tile<SM3, true, kPerThread>(r, base, m->from[SM3], L, ring);
+    else if (b < 2u * tiles) ragged_tile<SHA1, true, kPerThread>(r, base, m->from[SHA1], L, ring);
+    else ragged_tile<MD5, true, kPerThread>(r, base, m->from[MD5], L, ring);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -529,18 +569,21 @@ hipError_t launch_ragged(const uint8_t *algos, int algo, const uint8_t *msgs, co
     if (tiles * per > 0x7fffffffull) return hipErrorInvalidConfiguration;
     const RaggedArgs r{msgs, offs, lens, algos, out, n, stride, uint32_t(tile)};
     const dim3 grid{uint32_t(tiles * per), 1, 1}, block{kRaggedThreads, 1, 1};
-    // one wave to a SIMD (see few_waves)
-    const bool few = tiles * per <= device_simds() / 4u;
+    // one wave to a SIMD (see few_waves); and a form each for tiles of one message a thread (two
+    // in a mixed batch) and larger ones: unrolled for eight, the short batches' launches spent
+    // a microsecond passing over code they had no messages for
+    const bool few = tiles * per <= device_simds() / 4u, small = tile <= kRaggedThreads * (algos ? 2u : 1u);
     if (algos) {
-        hipLaunchKernelGGL(few ? k_ragged_mixed<false> : k_ragged_mixed<true>, grid, block, 0, stream, r, uint32_t(tiles));
+        hipLaunchKernelGGL((!small ? k_ragged_mixed<true, kPerThread> : few ? k_ragged_mixed<false, 2> : k_ragged_mixed<true, 2>), grid, block, 0,
+                           stream, r, uint32_t(tiles));
         return hipGetLastError();
     }
-    switch (algo) {
-    case MD5: hipLaunchKernelGGL((few ? k_ragged<MD5, false> : k_ragged<MD5, true>), grid, block, 0, stream, r); break;
-    case SHA1: hipLaunchKernelGGL((few ? k_ragged<SHA1, false> : k_ragged<SHA1, true>), grid, block, 0, stream, r); break;
-    case SM3: hipLaunchKernelGGL((few ? k_ragged<SM3, false> : k_ragged<SM3, true>), grid, block, 0, stream, r); break;
-    default: return hipErrorInvalidValue;
-    }
+    auto *kernel = algo == MD5  ? (!small ? k_ragged<MD5, true, kPerThread> : few ? k_ragged<MD5, false, 1> : k_ragged<MD5, true, 1>)
+                 : algo == SHA1 ? (!small ? k_ragged<SHA1, true, kPerThread> : few ? k_ragged<SHA1, false, 1> : k_ragged<SHA1, true, 1>)
+                 : algo == SM3  ? (!small ? k_ragged<SM3, true, kPerThread> : few ? k_ragged<SM3, false, 1> : k_ragged<SM3, true, 1>)
+                                : nullptr;
+    if (!kernel) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(kernel, grid, block, 0, stream, r);
     return hipGetLastError();
 }
 

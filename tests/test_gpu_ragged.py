@@ -76,6 +76,32 @@ def test_many_tiles(hb, n):
     assert_same(got, oracle.hash_batch(algos, msgs, offs, lens), "many tiles mixed")
 
 
+@pytest.mark.parametrize("n", [65_536, 70_001])
+@pytest.mark.parametrize("top", [64, 130, 300])
+def test_short_messages(hb, n, top):
+    """One message a thread, on both sides of one wave a SIMD: tiles that are not sorted
+    because it would save too little, and ones that are."""
+    lens = np.random.default_rng(top).integers(0, top + 1, n).astype(np.uint64)
+    offs = workloads.packed(lens)
+    msgs = workloads.host_random_bytes(int(lens.sum()) + 1, seed=top)
+    for algo in (0, 1, 2):
+        print(f"case short n={n} top={top} algo={algo}", flush=True)
+        got = hb.hash_batch(algo, msgs, offs.astype(np.int64), lens.astype(np.int64)).cpu().numpy()
+        assert_same(got, oracle.hash_batch(algo, msgs, offs, lens), f"short {algo}")
+
+
+@pytest.mark.parametrize("blocks", [2, 3, 7, 8, 47, 48])
+def test_fewest_blocks_of_a_chain(hb, blocks):
+    """The longest message on each side of an algorithm's least for a chain pair."""
+    lens = np.random.default_rng(blocks).integers(0, 64 * blocks - 8, 65).astype(np.uint64)
+    lens[40] = 64 * blocks - 9
+    offs = workloads.packed(lens)
+    msgs = workloads.host_random_bytes(int(lens.sum()) + 1, seed=blocks)
+    for algo in (0, 1, 2):
+        got = hb.hash_batch(algo, msgs, offs.astype(np.int64), lens.astype(np.int64)).cpu().numpy()
+        assert_same(got, oracle.hash_batch(algo, msgs, offs, lens), f"{blocks} blocks {algo}")
+
+
 @pytest.mark.parametrize("algo", [1, 2])
 @pytest.mark.parametrize("per_cu", [0, 1, 63, 64, 65, 128])
 def test_few_fixed_messages(hb, algo, per_cu):
