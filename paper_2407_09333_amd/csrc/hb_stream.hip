@@ -29,6 +29,29 @@ __global__ __launch_bounds__(kStreamBlock) void k_init(hb_state *__restrict__ st
     st[i].flags = 0;
 }
 
+// A message's state and its piece's place, all read at once: one after another, as the checks
+// use them, they cost three memory latencies before the first block's own (524,288 pieces of
+// 64 / 256 bytes, us: MD5 20.0 / 37.6, so 18.0 / 33.9; SM3 28.2 / 68.7, so 26.5 / 68.2; a
+// batch whose states stay in the caches, 262,144 pieces, within 1 %).
+struct Piece {
+    uint32_t s[8];
+    uint64_t bytes, flags, off, len;
+};
+
+__device__ __forceinline__ Piece load_piece(const hb_state *st, const uint64_t *offs, const uint64_t *lens, uint64_t i)
+{
+    Piece p;
+    for (int q = 0; q < 8; ++q) p.s[q] = st[i].h[q];
+    p.bytes = st[i].bytes;
+    p.flags = st[i].flags;
+    p.off = offs[i];
+    p.len = lens[i];
+    // here, or the compiler moves each behind the branch that comes before its use
+    for (int q = 0; q < 8; ++q) asm volatile("" : "+v"(p.s[q]));
+    asm volatile("" : "+v"(p.bytes), "+v"(p.flags), "+v"(p.off), "+v"(p.len));
+    return p;
+}
+
 template <int A, bool MANY>
 __global__ __launch_bounds__(kStreamBlock) void k_update(hb_state *__restrict__ st, const uint8_t *__restrict__ msgs,
                                                          const uint64_t *__restrict__ offs,
@@ -36,18 +59,16 @@ __global__ __launch_bounds__(kStreamBlock) void k_update(hb_state *__restrict__ 
 {
     const uint64_t i = uint64_t(blockIdx.x) * kStreamBlock + threadIdx.x;
     if (i >= n) return;
-    const uint64_t len = lens[i];
-    if (st[i].flags) return;
-    if (len % 64u) {  // only whole blocks can be absorbed before the final piece
+    Piece p = load_piece(st, offs, lens, i);
+    if (p.flags) return;
+    if (p.len % 64u) {  // only whole blocks can be absorbed before the final piece
         st[i].flags = kInvalidState;
         return;
     }
-    uint32_t s[8];
-    for (int q = 0; q < 8; ++q) s[q] = st[i].h[q];
-    const Msg m = make_msg<A>(msgs + offs[i], len);
-    absorb<A, false, kDefaultBurst<A>, MANY>(m, s);
-    for (int q = 0; q < Traits<A>::kWords; ++q) st[i].h[q] = s[q];
-    st[i].bytes += len;
+    const Msg m = make_msg<A>(msgs + p.off, p.len);
+    absorb<A, false, kDefaultBurst<A>, MANY>(m, p.s);
+    for (int q = 0; q < Traits<A>::kWords; ++q) st[i].h[q] = p.s[q];
+    st[i].bytes = p.bytes + p.len;
 }
 
 template <int A, bool MANY>
@@ -59,18 +80,16 @@ __global__ __launch_bounds__(kStreamBlock) void k_final(const hb_state *__restri
     const uint64_t i = uint64_t(blockIdx.x) * kStreamBlock + threadIdx.x;
     if (i >= n) return;
     uint8_t *o = out + i * Traits<A>::kDigest;
-    if (st[i].flags) {
+    Piece p = load_piece(st, offs, lens, i);
+    if (p.flags) {
         HB_GLOBAL uint32_t *ow = reinterpret_cast<HB_GLOBAL uint32_t *>(reinterpret_cast<uintptr_t>(o));
         for (int q = 0; q < Traits<A>::kWords; ++q) ow[q] = 0u;
         return;
     }
-    uint32_t s[8];
-    for (int q = 0; q < 8; ++q) s[q] = st[i].h[q];
-    const uint64_t len = lens[i];
-    Msg m = make_msg<A>(msgs + offs[i], len);
-    m.bits = (st[i].bytes + len) << 3;
-    absorb<A, true, kDefaultBurst<A>, MANY>(m, s);
-    store_digest<A>(o, s, Traits<A>::kDigest);
+    Msg m = make_msg<A>(msgs + p.off, p.len);
+    m.bits = (p.bytes + p.len) << 3;
+    absorb<A, true, kDefaultBurst<A>, MANY>(m, p.s);
+    store_digest<A>(o, p.s, Traits<A>::kDigest);
 }
 
 template <class K, class... Args>
