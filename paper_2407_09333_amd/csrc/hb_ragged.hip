@@ -590,9 +590,12 @@ bool fixed_chain_applies(int algo, uint64_t n, uint64_t len)
     // blocks on (120 bytes: 14.7 / 13.4; 512: 28.3 / 24.9), SHA-1 from four (250 bytes: 13.2 /
     // 11.8; 120: 10.5 / 10.5), and past 32 messages to a pair, where a window is one block and
     // the schedules take longer than the rounds, from 32 (20,011 x 512: 16.0 / 17.3; x 4 KiB:
-    // 89 / 79).  Not MD5, whose schedule is one addition to a word (1,000 x 1 KiB: 17.1 / 17.2).
+    // 89 / 79).  MD5, whose schedule is one addition to
+    // a word, for its loads: from 64 blocks, up to 32 messages to a pair (144 x 2 KiB 27.2 / 27.0,
+    // x 35,664 bytes 562 / 309; 12,000 x 4 KiB 58.8 / 48.1; 20,011 x 4 KiB 50.3 / 51.5).
     const uint64_t nb = block_count(len), cus = device_simds() / 4u;
     if (n > 128u * cus || nb >= 0x80000000u) return false;
+    if (algo == MD5) return n <= 64u * cus && nb >= 64;
     return algo == SM3 ? nb >= 3 : algo == SHA1 && nb >= (n <= 64u * cus ? 4u : 32u);
 }
 
@@ -602,6 +605,7 @@ hipError_t launch_fixed_chain(int algo, const uint8_t *msgs, uint64_t n, uint64_
     const uint32_t per = uint32_t((n + pairs - 1) / pairs);  // messages of a pair
     const dim3 grid{uint32_t((n + 2u * per - 1) / (2u * per)), 1, 1}, block{kRaggedThreads, 1, 1};
     if (algo == SHA1) hipLaunchKernelGGL(k_fixed_chain<SHA1>, grid, block, 0, stream, msgs, n, len, per, out);
+    else if (algo == MD5) hipLaunchKernelGGL(k_fixed_chain<MD5>, grid, block, 0, stream, msgs, n, len, per, out);
     else if (algo == SM3) hipLaunchKernelGGL(k_fixed_chain<SM3>, grid, block, 0, stream, msgs, n, len, per, out);
     else return hipErrorInvalidValue;
     return hipGetLastError();

@@ -150,3 +150,18 @@ def test_long_messages_first(hb, monkeypatch, algo):
             check_guard(buf, n, want.shape[1])
             assert_same(out.cpu().numpy(), want, f"long first {algo} {flags}")
         plan.close()
+
+
+@pytest.mark.parametrize("per_cu", [0, 1, 63, 64, 65])
+def test_few_long_fixed_md5(hb, per_cu):
+    """MD5's batches of few messages run as chain pairs from 64 blocks (4,024 bytes) on."""
+    import torch
+
+    n = max(1, per_cu * torch.cuda.get_device_properties(0).multi_processor_count - 3)
+    for L in (4020, 4024, 4096, 4156):
+        print(f"case few long md5 n={n} L={L}", flush=True)
+        b = workloads.fixed_batch(0, n, L, seed=L)
+        buf, out = guarded_out(n, 16)
+        hb.hash_batch_fixed(0, torch.from_numpy(b.messages).cuda(), n, L, out=out)
+        check_guard(buf, n, 16)
+        assert_same(out.cpu().numpy(), oracle.hash_batch(0, b.messages, b.offsets, b.lengths), f"few long md5 {L}")
