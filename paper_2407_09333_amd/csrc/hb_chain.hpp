@@ -22,7 +22,7 @@
 
 namespace hb {
 
-constexpr uint32_t kChainMessages = 32;  // of a pair, at most, where a batch has more than pairs for all
+constexpr uint32_t kChainMessages = kTileChains;  // of a pair, at most, where a batch has more than pairs for all
 
 // Windows in the ring: MD5's schedules take about as long as its rounds, so its schedule
 // wave needs the slack of a third.

@@ -27,8 +27,7 @@ namespace hb {
 
 namespace {
 
-constexpr int kRaggedThreads = 256;
-constexpr uint32_t kTileMax = 2048;
+constexpr int kRaggedThreads = int(kTileThreads);
 constexpr int kPerThread = int(kTileMax) / kRaggedThreads;
 // (Tiles of 512 read fewer cache lines twice, neighbours in memory being nearer in time -- 4,000,000
 // messages of 0 to 512 bytes, us: MD5 410 for 501, SHA-1 483 for 580 -- but the longest messages
@@ -265,17 +264,19 @@ __device__ __forceinline__ void ragged_tile(const RaggedArgs &r, uint64_t base, 
             p = __builtin_amdgcn_readfirstlane(p);
         }
         if (p >= count) break;
-        if (p + lane < count) {
-            uint64_t i = i0, off = off0, len = len0;
-            if (sorted || (PER > 1 && p >= kRaggedThreads)) {
-                i = base + (sorted ? L.order[p + lane] : p + lane);
-                off = r.offs[i];
-                len = r.lens[i];
-            }
-            uint32_t s[8];
-            hash_message<A, kDefaultBurst<A>, MANY>(r.msgs + off, len, s);
-            store_digest<A>(r.out + i * r.stride, s, r.stride);
+        // A lane past the last message hashes that one again and stores nothing: a wave with
+        // half its lanes off issues more slowly (33 messages of 2 KiB MD5, one to a
+        // workgroup: 30.8 us with the others off, 23.5 so).
+        const uint32_t at = min(p + lane, count - 1u);
+        uint64_t i = i0, off = off0, len = len0;
+        if (sorted || (PER > 1 && p >= kRaggedThreads)) {
+            i = base + (sorted ? L.order[at] : at);
+            off = r.offs[i];
+            len = r.lens[i];
         }
+        uint32_t s[8];
+        hash_message<A, kDefaultBurst<A>, MANY>(r.msgs + off, len, s);
+        if (p + lane < count) store_digest<A>(r.out + i * r.stride, s, r.stride);
     }
 }
 
@@ -532,36 +533,12 @@ __global__ __launch_bounds__(kRaggedThreads) void k_fixed_chain(const uint8_t *_
     }
 }
 
-// How a batch is dealt out: messages per tile, tiles, workgroups per tile, and how many times
-// over its workgroups fill the chip.
-struct Tiling {
-    uint64_t tile, tiles, per, rounds;
-};
-
-Tiling tiling(uint64_t n, bool mixed)
-{
-    // Messages a workgroup gets: up to 256 while one workgroup on each CU takes them all, one
-    // wave to a SIMD (64 to a workgroup and four workgroups to a CU would put the four busy
-    // waves on one SIMD: 65,536 x 1 KiB MD5 43 us against 21); 256 up to four workgroups on
-    // each CU (a SIMD for each one's chain wave: with five, two chains shared one); then as
-    // many as fill those once, or a whole number of times: larger tiles sort better, but a
-    // last round that is half empty costs more.  A mixed batch's tiles are twice as large, a
-    // workgroup hashing about a third of one: three times as large, half the workgroups would
-    // have a few messages more than their four waves take at once.
-    const uint64_t cus = device_simds() / 4u, per = mixed ? 3u : 1u, wide = mixed ? 2u : 1u, slots = cus * 4u;
-    const uint64_t rounds = (n * per + slots * kTileMax - 1) / (slots * kTileMax);
-    const uint64_t one = (n + cus - 1) / cus, all = (n * per + slots * rounds - 1) / (slots * rounds);
-    const uint64_t tile = one <= kRaggedThreads ? (one + 63u) / 64u * 64u * wide
-                                                : std::min<uint64_t>((std::max<uint64_t>(all, kRaggedThreads * wide) + 255u) / 256u * 256u, kTileMax);
-    return {tile, (n + tile - 1) / tile, per, rounds};
-}
-
 }  // namespace
 
 hipError_t launch_ragged(const uint8_t *algos, int algo, const uint8_t *msgs, const uint64_t *offs, const uint64_t *lens,
                          uint64_t n, uint8_t *out, uint32_t stride, hipStream_t stream)
 {
-    const Tiling t = tiling(n, algos != nullptr);
+    const Tiling t = tiling(n, algos != nullptr, device_simds() / 4u);
     const uint64_t tile = t.tile, tiles = t.tiles, per = t.per;
     if (tiles * per > 0x7fffffffull) return hipErrorInvalidConfiguration;
     const RaggedArgs r{msgs, offs, lens, algos, out, n, stride, uint32_t(tile)};
@@ -611,12 +588,12 @@ hipError_t launch_fixed_chain(int algo, const uint8_t *msgs, uint64_t n, uint64_
     return hipGetLastError();
 }
 
-bool ragged_in_one_round(uint64_t n, bool mixed) { return tiling(n, mixed).rounds <= 1; }
+bool ragged_in_one_round(uint64_t n, bool mixed) { return tiling(n, mixed, device_simds() / 4u).rounds <= 1; }
 
 hipError_t launch_ragged_long(const LongWs &w, const uint8_t *algos, int algo, const uint8_t *msgs, const uint64_t *offs,
                               const uint64_t *lens, uint64_t n, uint8_t *out, uint32_t stride, hipStream_t stream)
 {
-    const Tiling t = tiling(n, algos != nullptr);
+    const Tiling t = tiling(n, algos != nullptr, device_simds() / 4u);
     if (t.tiles * t.per + kLongGroups > 0x7fffffffull) return hipErrorInvalidConfiguration;
     const RaggedArgs r{msgs, offs, lens, algos, out, n, stride, uint32_t(t.tile)};
     const dim3 block{kRaggedThreads, 1, 1}, sweep{device_simds(), 1, 1}, grid{uint32_t(kLongGroups + t.tiles * t.per), 1, 1};
