@@ -81,8 +81,13 @@ inline Tiling tiling(uint64_t n, bool mixed, uint64_t cus)
         // Then 256 up to four workgroups on each CU (a SIMD for each one's chain wave: with
         // five, two chains shared one), and past those as many as fill them once, or a whole
         // number of times: larger tiles sort better, but a last round that is half empty
-        // costs more.
-        tile = all < kTileThreads * wide ? kTileThreads * wide : (all + 255u) / 256u * 256u;
+        // costs more.  Past 512, one algorithm's tiles grow by a wave's 64 messages, so that
+        // all four workgroups of a CU have work: by 256, three of 768 for some CUs and four
+        // for others (600,011 messages of 16 bytes, MD5 / SHA-1 / SM3, us: 16.6 / 22.6 / 36.3,
+        // so 15.5 / 20.9 / 32.0).  Up to 512 the whole step is faster (300,007: of 320 11.7 /
+        // 14.7 / 22.7, of 512 10.6 / 13.4 / 20.7).
+        const uint64_t step = mixed || all <= 512u ? 256u : 64u;
+        tile = all < kTileThreads * wide ? kTileThreads * wide : (all + step - 1) / step * step;
         tile = tile < kTileMax ? tile : kTileMax;
     }
     return {tile, (n + tile - 1) / tile, per, rounds};

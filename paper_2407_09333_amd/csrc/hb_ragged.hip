@@ -256,9 +256,12 @@ __device__ __forceinline__ void ragged_tile(const RaggedArgs &r, uint64_t base, 
     if (nchain) {
         chain_pair<A>(r, lane < nchain ? base + L.order[lane] : kNoMessage, L, ring);
     }
-    // 64 positions at a time: in index order each wave every fourth, sorted whoever is free
+    // 64 positions at a time: in index order each wave one of every four -- past the first,
+    // not the same one in each of the CU's workgroups, so that the odd ones of tiles that are
+    // no multiple of 256 go to different SIMDs -- and sorted whoever is free
     uint32_t p = wave * 64u;
-    for (;; p += kRaggedThreads) {
+    for (uint32_t turn = 0;; ++turn) {
+        if (turn) p = turn * kRaggedThreads + (wave - L.group) % 4u * 64u;
         if (sorted) {
             if (lane == 0) p = atomicAdd(&L.next, 64u);
             p = __builtin_amdgcn_readfirstlane(p);
@@ -533,6 +536,18 @@ __global__ __launch_bounds__(kRaggedThreads) void k_fixed_chain(const uint8_t *_
     }
 }
 
+// A form each for tiles of one message a thread, two and more: unrolled for eight, the short
+// batches' launches spent a microsecond passing over code they had no messages for (300,007
+// messages of 16 bytes in tiles of 512, MD5 / SHA-1 / SM3, us: 11.2 / 14.0 / 21.5 unrolled for
+// eight, 10.6 / 13.4 / 20.7 for two).
+template <int A> auto *ragged_form(uint64_t tile, bool few)
+{
+    return tile > 2u * kRaggedThreads ? k_ragged<A, true, kPerThread>
+         : tile > kRaggedThreads      ? k_ragged<A, true, 2>
+         : few                        ? k_ragged<A, false, 1>
+                                      : k_ragged<A, true, 1>;
+}
+
 }  // namespace
 
 hipError_t launch_ragged(const uint8_t *algos, int algo, const uint8_t *msgs, const uint64_t *offs, const uint64_t *lens,
@@ -543,19 +558,14 @@ hipError_t launch_ragged(const uint8_t *algos, int algo, const uint8_t *msgs, co
     if (tiles * per > 0x7fffffffull) return hipErrorInvalidConfiguration;
     const RaggedArgs r{msgs, offs, lens, algos, out, n, stride, uint32_t(tile)};
     const dim3 grid{uint32_t(tiles * per), 1, 1}, block{kRaggedThreads, 1, 1};
-    // one wave to a SIMD (see few_waves); and a form each for tiles of one message a thread (two
-    // in a mixed batch) and larger ones: unrolled for eight, the short batches' launches spent
-    // a microsecond passing over code they had no messages for
-    const bool few = tiles * per <= device_simds() / 4u, small = tile <= kRaggedThreads * (algos ? 2u : 1u);
+    const bool few = tiles * per <= device_simds() / 4u;  // one wave to a SIMD (see few_waves)
     if (algos) {
-        hipLaunchKernelGGL((!small ? k_ragged_mixed<true, kPerThread> : few ? k_ragged_mixed<false, 2> : k_ragged_mixed<true, 2>), grid, block, 0,
-                           stream, r, uint32_t(tiles));
+        hipLaunchKernelGGL((tile > 2u * kRaggedThreads ? k_ragged_mixed<true, kPerThread> : few ? k_ragged_mixed<false, 2> : k_ragged_mixed<true, 2>),
+                           grid, block, 0, stream, r, uint32_t(tiles));
         return hipGetLastError();
     }
-    auto *kernel = algo == MD5  ? (!small ? k_ragged<MD5, true, kPerThread> : few ? k_ragged<MD5, false, 1> : k_ragged<MD5, true, 1>)
-                 : algo == SHA1 ? (!small ? k_ragged<SHA1, true, kPerThread> : few ? k_ragged<SHA1, false, 1> : k_ragged<SHA1, true, 1>)
-                 : algo == SM3  ? (!small ? k_ragged<SM3, true, kPerThread> : few ? k_ragged<SM3, false, 1> : k_ragged<SM3, true, 1>)
-                                : nullptr;
+    auto *kernel = algo == MD5 ? ragged_form<MD5>(tile, few) : algo == SHA1 ? ragged_form<SHA1>(tile, few)
+                 : algo == SM3 ? ragged_form<SM3>(tile, few) : nullptr;
     if (!kernel) return hipErrorInvalidValue;
     hipLaunchKernelGGL(kernel, grid, block, 0, stream, r);
     return hipGetLastError();

@@ -26,6 +26,11 @@ void check(uint64_t n, bool mixed, uint64_t cus)
     if (n <= (mixed ? 2u : 1u) * hb::kTileChains * (cus / t.per) &&
         (t.tile > (mixed ? 2u : 1u) * hb::kTileChains || t.tiles * t.per > cus))
         fail("few messages", n, mixed, cus);
+    // tiles past two messages a thread: the busiest CU's waves of 64 are within an eighth of
+    // the mean, and one a workgroup
+    const uint64_t waves = (t.tiles + cus - 1) / cus * ((t.tile + 63) / 64);
+    if (!mixed && t.tile > 512 && double(waves) > 1.125 * double(n) / 64.0 / double(cus) + 4.0 * double(t.rounds))
+        fail("busiest CU", n, mixed, cus);
 }
 
 }  // namespace

@@ -57,3 +57,11 @@ def test_few_alike_messages(hb, length, per_cu, extra):
     lens = np.full(n, length, np.uint64)
     got = hb.hash_batch_mixed(algos, msgs, offs, lens).cpu().numpy()
     assert_same(got, oracle.hash_batch(algos, msgs, offs, lens), "few alike mixed")
+
+
+@pytest.mark.parametrize("per_cu", [1024, 1025, 2048, 2049, 2300])
+def test_messages_in_index_order(hb, per_cu):
+    """Messages of one block count, hashed in index order: tiles of one message a thread, two
+    and more, and tiles that are no multiple of 256."""
+    n = per_cu * hb.device_info()["cu_count"] + 7
+    check_batch(hb, 16 + np.arange(n) % 7, 6, "index order", mixed=False)
