@@ -29,10 +29,9 @@ namespace {
 
 constexpr int kRaggedThreads = int(kTileThreads);
 constexpr int kPerThread = int(kTileMax) / kRaggedThreads;
-// (Tiles of 512 read fewer cache lines twice, neighbours in memory being nearer in time -- 4,000,000
-// messages of 0 to 512 bytes, us: MD5 410 for 501, SHA-1 483 for 580 -- but the longest messages
-// of more, smaller tiles start later: 1,000,003 of log-normal lengths up to 64 KiB MD5 1,087 for
-// 715, SHA-1 2,167 for 1,053.)
+// (Tiles of 512 would read fewer cache lines twice, as sorting 512 at a time does for short
+// messages (ragged_tile), but the longest messages of more, smaller tiles start later: 1,000,003
+// of log-normal lengths up to 64 KiB MD5 1,087 us for 715, SHA-1 2,167 for 1,053.)
 constexpr uint32_t kLenBins = 256;
 
 struct RaggedArgs {
@@ -205,6 +204,18 @@ __device__ __forceinline__ void ragged_tile(const RaggedArgs &r, uint64_t base, 
     // 17.7 / 16.8; SHA-1 18.4 / 16.2 and 23.6 / 22.5; MD5 of 0 to 257 20.2 sorted, 22.6 before).
     const bool worth = PER > 1 || (uint64_t(longest) * have - blocks) * kBlockOps<A> > uint64_t(kSortOps) * have;
     const bool sorted = least == longest ? have <= kChainMessages && chains : chains || least == 0 || (MANY && worth);
+    // Short messages of one algorithm are sorted within 512 at a time (the last 512 to 1,023 of
+    // the tile), each with bins of its own: neighbours in memory share cache lines, and hashed
+    // a whole tile apart they were read twice (4,000,000 messages of 0 to 257 / 1,024 bytes,
+    // us: MD5 320 / 790 and 284 / 715, SHA-1 353 / 940 and 314 / 859; SM3, bound by its
+    // compression, gained nothing).
+    constexpr uint32_t kSub = 512, kSubBins = kLenBins * kSub / kTileMax;
+    const bool local = A != SM3 && PER == kPerThread && !chains && !r.algos && longest < kSubBins;
+    auto bin_of = [&](int j, uint32_t blocks_of) {
+        if (!local) return len_bin(blocks_of);
+        const uint32_t sub = min(uint32_t(j) * kRaggedThreads / kSub, max(r.tile / kSub, 1u) - 1u);
+        return (kTileMax / kSub - 1u - sub) * kSubBins + blocks_of;
+    };
     uint32_t count = have;
     if (sorted) {
         uint32_t rank[PER];  // within the bin
@@ -212,7 +223,7 @@ __device__ __forceinline__ void ragged_tile(const RaggedArgs &r, uint64_t base, 
         for (int j = 0; j < PER; ++j) {
             rank[j] = 0;
             if (nb[j]) {
-                const uint32_t bin = len_bin(nb[j]), first = __builtin_amdgcn_readfirstlane(bin);
+                const uint32_t bin = bin_of(j, nb[j]), first = __builtin_amdgcn_readfirstlane(bin);
                 const uint64_t active = __ballot(1);
                 if (__ballot(bin == first) == active) {  // one atomic for the wave
                     const uint32_t below = __builtin_amdgcn_mbcnt_hi(uint32_t(active >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(active), 0u));
@@ -246,7 +257,7 @@ __device__ __forceinline__ void ragged_tile(const RaggedArgs &r, uint64_t base, 
         __syncthreads();
 #pragma unroll
         for (int j = 0; j < PER; ++j)
-            if (nb[j]) L.order[L.bins[len_bin(nb[j])] + rank[j]] = uint16_t(uint32_t(j) * kRaggedThreads + tid);
+            if (nb[j]) L.order[L.bins[bin_of(j, nb[j])] + rank[j]] = uint16_t(uint32_t(j) * kRaggedThreads + tid);
     }
     const uint32_t nchain = sorted && chains ? min(count, kChainMessages) : 0u;
     if (sorted) {

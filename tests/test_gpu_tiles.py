@@ -65,3 +65,15 @@ def test_messages_in_index_order(hb, per_cu):
     and more, and tiles that are no multiple of 256."""
     n = per_cu * hb.device_info()["cu_count"] + 7
     check_batch(hb, 16 + np.arange(n) % 7, 6, "index order", mixed=False)
+
+
+@pytest.mark.parametrize("longest", [63, 64])
+@pytest.mark.parametrize("per_cu", [2300, 4096, 6200, 8192])
+def test_short_messages_sorted_512_at_a_time(hb, per_cu, longest):
+    """Short messages in tiles of one to four times 512, and a little more, the longest on both
+    sides of the last block count that is sorted so."""
+    n = per_cu * hb.device_info()["cu_count"] - 5
+    rng = np.random.default_rng(longest)
+    lens = rng.integers(0, 150, n)
+    lens[rng.choice(n, 3 * n // 2000, replace=False)] = 64 * longest - 9   # in most tiles
+    check_batch(hb, lens, 7, "short sorted", mixed=per_cu == 2300)
