@@ -267,12 +267,9 @@ __device__ __forceinline__ void ragged_tile(const RaggedArgs &r, uint64_t base, 
     if (nchain) {
         chain_pair<A>(r, lane < nchain ? base + L.order[lane] : kNoMessage, L, ring);
     }
-    // 64 positions at a time: in index order each wave one of every four -- past the first,
-    // not the same one in each of the CU's workgroups, so that the odd ones of tiles that are
-    // no multiple of 256 go to different SIMDs -- and sorted whoever is free
+    // 64 positions at a time: in index order each wave every fourth, sorted whoever is free
     uint32_t p = wave * 64u;
-    for (uint32_t turn = 0;; ++turn) {
-        if (turn) p = turn * kRaggedThreads + (wave - L.group) % 4u * 64u;
+    for (;; p += kRaggedThreads) {
         if (sorted) {
             if (lane == 0) p = atomicAdd(&L.next, 64u);
             p = __builtin_amdgcn_readfirstlane(p);
