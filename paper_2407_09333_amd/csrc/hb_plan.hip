@@ -648,21 +648,24 @@ constexpr int kLoadSchemes = 5;
 template <int V, int A>
 constexpr int scheme_burst() { return V == 2 ? 1 : (V == 3 ? 2 : (V == 4 ? 4 : kDefaultBurst<A>)); }
 
-template <int A, int V>
+template <int A, int V, bool MANY>
 __device__ __forceinline__ void hash_lane(const PlanDesc &d, uint32_t idx)
 {
     uint32_t s[8];
     const uint64_t off = reinterpret_cast<const HB_GLOBAL uint64_t *>(reinterpret_cast<uintptr_t>(d.offs))[idx];
     const uint64_t len = reinterpret_cast<const HB_GLOBAL uint64_t *>(reinterpret_cast<uintptr_t>(d.lens))[idx];
     if constexpr (V == 1 && A != MD5) hash_message_prefetch<A>(d.msgs + off, len, s);
-    else hash_message<A, scheme_burst<V, A>(), true>(d.msgs + off, len, s);
+    else hash_message<A, scheme_burst<V, A>(), MANY>(d.msgs + off, len, s);
     store_digest<A>(d.out + uint64_t(idx) * d.stride, s, d.stride);
 }
 
 // Persistent fused kernel: each wave takes items from the queue until none are left.
 // An item is 64 * mpl sorted positions of one algorithm; lane l hashes positions
-// l, l + 64, ... of it.  PF is the load scheme (see kLoadSchemes).
-template <int PF>
+// l, l + 64, ... of it.  PF is the load scheme (see kLoadSchemes); MANY: waves share SIMDs
+// (see pipeline_few_waves).  Items of long messages don't run at a raised priority: MANY's
+// compressions raise and lower it themselves, and with a wave to a SIMD it changed nothing
+// (20,000 messages of 0 to 4,096 bytes, SM3: 282 us at either).
+template <int PF, bool MANY>
 __device__ __forceinline__ void persistent_wave(const PlanWs &ws, uint32_t block)
 {
     const PlanDesc d = *ws.desc;
@@ -701,27 +704,27 @@ __device__ __forceinline__ void persistent_wave(const PlanWs &ws, uint32_t block
             if (pos < long_end) continue;
             const uint32_t idx = ws.sorted[pos];
             if (idx == kInvalid) continue;
-            if (a == MD5) hash_lane<MD5, PF>(d, idx);
-            else if (a == SHA1) hash_lane<SHA1, PF>(d, idx);
-            else hash_lane<SM3, PF>(d, idx);
+            if (a == MD5) hash_lane<MD5, PF, MANY>(d, idx);
+            else if (a == SHA1) hash_lane<SHA1, PF, MANY>(d, idx);
+            else hash_lane<SM3, PF, MANY>(d, idx);
         }
     }
 }
 
-template <int PF>
+template <int PF, bool MANY>
 __global__ __launch_bounds__(kThreads) void k_hash_persistent(PlanWs ws)
 {
-    persistent_wave<PF>(ws, blockIdx.x);
+    persistent_wave<PF, MANY>(ws, blockIdx.x);
 }
 
 // The long-chain kernel and the persistent kernel in one launch: workgroups below
 // long_blocks run the long chains (dispatched first), the rest the bulk.  Same work and
 // concurrency as the two kernels on two streams, without a second stream.
-template <int SCHED, int PF>
+template <int SCHED, int PF, bool MANY>
 __global__ __launch_bounds__(kThreads) void k_hash_fused(PlanWs ws, uint32_t long_blocks)
 {
     if (blockIdx.x < long_blocks) long_lane<SCHED>(ws, blockIdx.x * kThreads + threadIdx.x);
-    else persistent_wave<PF>(ws, blockIdx.x - long_blocks);
+    else persistent_wave<PF, MANY>(ws, blockIdx.x - long_blocks);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -805,9 +808,12 @@ struct hb_plan {
     hb::LongWs long_ws{};           // its workspace for batches of more than one round of tiles
     int tune_bucket = -1;           // length bucket the autotuner keyed its choice by
     hipStream_t cap_stream = nullptr;
-    hipGraph_t graph = nullptr;
-    hipGraphExec_t exec = nullptr;
-    int graph_mpl = 0, graph_sort = -1;
+    struct Graph {
+        hipGraph_t graph = nullptr;
+        hipGraphExec_t exec = nullptr;
+        int mpl = 0, sort = -1;
+    };
+    Graph graphs[2];                // the captured pipeline, for few waves and for many
     std::vector<std::pair<hipEvent_t, hipEvent_t>> ev_free, ev_pending;  // hash-kernel timing
     bool long_on = false;           // long-chain path enabled
     bool long_sched = true;         // precomputed schedule words (else direct reads)
@@ -822,12 +828,12 @@ struct hb_plan {
 
 namespace hb {
 
-static void drop_graph(hb_plan *p)
+static void drop_graph(hb_plan::Graph &g)
 {
-    if (p->exec) hipGraphExecDestroy(p->exec);
-    if (p->graph) hipGraphDestroy(p->graph);
-    p->exec = nullptr;
-    p->graph = nullptr;
+    if (g.exec) hipGraphExecDestroy(g.exec);
+    if (g.graph) hipGraphDestroy(g.graph);
+    g.exec = nullptr;
+    g.graph = nullptr;
 }
 
 static int grid_items(const hb_plan *p) { return p->cus * 4; }
@@ -862,37 +868,54 @@ static void collect_timing(hb_plan *p, bool wait)
 }
 
 template <int V>
-static void launch_fused_v(bool sched, dim3 grid, hipStream_t s, const PlanWs &ws, uint32_t long_blocks)
+static void launch_fused_v(bool sched, bool many, dim3 grid, hipStream_t s, const PlanWs &ws, uint32_t long_blocks)
 {
-    if (sched) hipLaunchKernelGGL((k_hash_fused<1, V>), grid, dim3(kThreads), 0, s, ws, long_blocks);
-    else hipLaunchKernelGGL((k_hash_fused<0, V>), grid, dim3(kThreads), 0, s, ws, long_blocks);
+    auto *kernel = sched ? (many ? k_hash_fused<1, V, true> : k_hash_fused<1, V, false>)
+                         : (many ? k_hash_fused<0, V, true> : k_hash_fused<0, V, false>);
+    hipLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, s, ws, long_blocks);
 }
 
-static void launch_fused(bool sched, int variant, dim3 grid, hipStream_t s, const PlanWs &ws, uint32_t long_blocks)
+static void launch_fused(bool sched, int variant, bool many, dim3 grid, hipStream_t s, const PlanWs &ws, uint32_t long_blocks)
 {
     switch (variant) {
-    case 1: launch_fused_v<1>(sched, grid, s, ws, long_blocks); break;
-    case 2: launch_fused_v<2>(sched, grid, s, ws, long_blocks); break;
-    case 3: launch_fused_v<3>(sched, grid, s, ws, long_blocks); break;
-    case 4: launch_fused_v<4>(sched, grid, s, ws, long_blocks); break;
-    default: launch_fused_v<0>(sched, grid, s, ws, long_blocks); break;
+    case 1: launch_fused_v<1>(sched, many, grid, s, ws, long_blocks); break;
+    case 2: launch_fused_v<2>(sched, many, grid, s, ws, long_blocks); break;
+    case 3: launch_fused_v<3>(sched, many, grid, s, ws, long_blocks); break;
+    case 4: launch_fused_v<4>(sched, many, grid, s, ws, long_blocks); break;
+    default: launch_fused_v<0>(sched, many, grid, s, ws, long_blocks); break;
     }
 }
 
-static void launch_persistent(int variant, dim3 grid, hipStream_t s, const PlanWs &ws)
+template <int V> static void launch_persistent_v(bool many, dim3 grid, hipStream_t s, const PlanWs &ws)
+{
+    hipLaunchKernelGGL((many ? k_hash_persistent<V, true> : k_hash_persistent<V, false>), grid, dim3(kThreads), 0, s, ws);
+}
+
+static void launch_persistent(int variant, bool many, dim3 grid, hipStream_t s, const PlanWs &ws)
 {
     switch (variant) {
-    case 1: hipLaunchKernelGGL(k_hash_persistent<1>, grid, dim3(kThreads), 0, s, ws); break;
-    case 2: hipLaunchKernelGGL(k_hash_persistent<2>, grid, dim3(kThreads), 0, s, ws); break;
-    case 3: hipLaunchKernelGGL(k_hash_persistent<3>, grid, dim3(kThreads), 0, s, ws); break;
-    case 4: hipLaunchKernelGGL(k_hash_persistent<4>, grid, dim3(kThreads), 0, s, ws); break;
-    default: hipLaunchKernelGGL(k_hash_persistent<0>, grid, dim3(kThreads), 0, s, ws); break;
+    case 1: launch_persistent_v<1>(many, grid, s, ws); break;
+    case 2: launch_persistent_v<2>(many, grid, s, ws); break;
+    case 3: launch_persistent_v<3>(many, grid, s, ws); break;
+    case 4: launch_persistent_v<4>(many, grid, s, ws); break;
+    default: launch_persistent_v<0>(many, grid, s, ws); break;
     }
+}
+
+// The batch's items or the launch's waves make at most one wave per SIMD: the compression for
+// a wave alone on its SIMD is then the faster (hb_issue.hpp).  A run of 20,000 messages of 0
+// to 4,096 bytes takes, MD5 / SHA-1 / SM3, 154 / 188 / 282 us so and 168 / 210 / 302 with
+// the form for shared SIMDs.  Kernels of their own: with both forms in one, the registers of
+// the first would cost the second a wave per SIMD.
+static bool pipeline_few_waves(const hb_plan *p, const PlanDesc &d)
+{
+    const uint64_t per = 64u * uint64_t(d.mpl), items = (d.n + per - 1) / per + (d.algos ? 2u : 0u);
+    return std::min<uint64_t>(items, uint64_t(p->cus) * uint64_t(p->waves_per_cu)) <= uint64_t(p->cus) * 4u;
 }
 
 // Enqueue the pipeline (after k_set_desc) on stream s.  With `timed`, HIP events on s
 // bracket the persistent hashing kernel.
-static hipError_t enqueue_pipeline(hb_plan *p, hipStream_t s, bool timed)
+static hipError_t enqueue_pipeline(hb_plan *p, bool many, hipStream_t s, bool timed)
 {
     const PlanWs &ws = p->ws;
     const int g = grid_items(p);
@@ -916,7 +939,7 @@ static hipError_t enqueue_pipeline(hb_plan *p, hipStream_t s, bool timed)
         const uint32_t long_blocks =
             uint32_t((uint64_t(ws.max_long_waves + ws.max_direct_waves) * 64u + kThreads - 1) / kThreads);
         const dim3 grid{long_blocks + uint32_t(hash_blocks), 1, 1};
-        launch_fused(p->long_sched, p->variant, grid, s, ws, long_blocks);
+        launch_fused(p->long_sched, p->variant, many, grid, s, ws, long_blocks);
     } else if (p->long_on) {
         // fork: the long chains start first on the side stream and run beside the bulk.  A
         // failed fork or join is returned: unjoined, the run's stream could report the
@@ -932,7 +955,7 @@ static hipError_t enqueue_pipeline(hb_plan *p, hipStream_t s, bool timed)
         if ((fe = hipEventRecord(p->ev_join, p->side)) != hipSuccess) return fe;
     }
     if (!fused) {
-        launch_persistent(p->variant, dim3(hash_blocks), s, ws);
+        launch_persistent(p->variant, many, dim3(hash_blocks), s, ws);
     }
     if (p->long_on && !fused) {  // join
         const hipError_t je = hipStreamWaitEvent(s, p->ev_join, 0);
@@ -957,26 +980,28 @@ static int launch_run(hb_plan *p, const PlanDesc &d, hipStream_t s)
     hipLaunchKernelGGL(k_set_desc, dim3(1), dim3(1), 0, s, d, p->ws.desc);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_error(e, "hb_plan_run: parameter kernel");
+    const bool many = !pipeline_few_waves(p, d);
     const bool use_graph = (p->flags & HB_PLAN_GRAPH) != 0;
     if (use_graph) {
-        if (p->exec && (p->graph_mpl != d.mpl || p->graph_sort != d.sort)) drop_graph(p);
-        if (!p->exec) {
+        hb_plan::Graph &g = p->graphs[many];  // one for each form of the compressions
+        if (g.exec && (g.mpl != d.mpl || g.sort != d.sort)) drop_graph(g);
+        if (!g.exec) {
             e = hipStreamBeginCapture(p->cap_stream, hipStreamCaptureModeThreadLocal);
             if (e != hipSuccess) return hip_error(e, "hb_plan_run: begin capture");
-            hipError_t le = enqueue_pipeline(p, p->cap_stream, false);
-            e = hipStreamEndCapture(p->cap_stream, &p->graph);
-            if (le != hipSuccess) { drop_graph(p); return hip_error(le, "hb_plan_run: captured launch"); }
-            if (e != hipSuccess) { drop_graph(p); return hip_error(e, "hb_plan_run: end capture"); }
-            e = hipGraphInstantiate(&p->exec, p->graph, nullptr, nullptr, 0);
-            if (e != hipSuccess) { drop_graph(p); return hip_error(e, "hb_plan_run: instantiate"); }
-            p->graph_mpl = d.mpl;
-            p->graph_sort = d.sort;
+            hipError_t le = enqueue_pipeline(p, many, p->cap_stream, false);
+            e = hipStreamEndCapture(p->cap_stream, &g.graph);
+            if (le != hipSuccess) { drop_graph(g); return hip_error(le, "hb_plan_run: captured launch"); }
+            if (e != hipSuccess) { drop_graph(g); return hip_error(e, "hb_plan_run: end capture"); }
+            e = hipGraphInstantiate(&g.exec, g.graph, nullptr, nullptr, 0);
+            if (e != hipSuccess) { drop_graph(g); return hip_error(e, "hb_plan_run: instantiate"); }
+            g.mpl = d.mpl;
+            g.sort = d.sort;
         }
-        e = hipGraphLaunch(p->exec, s);
+        e = hipGraphLaunch(g.exec, s);
         if (e != hipSuccess) return hip_error(e, "hb_plan_run: graph launch");
         return HB_OK;
     }
-    e = enqueue_pipeline(p, s, true);
+    e = enqueue_pipeline(p, many, s, true);
     if (e != hipSuccess) return hip_error(e, "hb_plan_run: launch");
     return HB_OK;
 }
@@ -1259,7 +1284,7 @@ int hb_plan_set_config(hb_plan *p, int waves_per_cu, int msgs_per_lane, int vari
     p->variant = variant;
     p->tuned = true;
     p->tiles = false;
-    drop_graph(p);
+    for (hb_plan::Graph &g : p->graphs) drop_graph(g);
     return HB_OK;
 }
 
@@ -1279,7 +1304,7 @@ void hb_plan_destroy(hb_plan *p)
     if (!p) return;
     if (p->cap_stream) hipStreamSynchronize(p->cap_stream);
     hipDeviceSynchronize();
-    drop_graph(p);
+    for (hb_plan::Graph &g : p->graphs) drop_graph(g);
     collect_timing(p, true);
     for (auto &e : p->ev_free) { hipEventDestroy(e.first); hipEventDestroy(e.second); }
     if (p->cap_stream) hipStreamDestroy(p->cap_stream);
