@@ -183,10 +183,11 @@ enum {
 
 /*
  * hb_plan_create -- reserve device workspace for batches of up to max_n messages and
- * build the launch plan.  The plan owns its workspace (about 4 bytes per message, a fixed
- * part of about 0.6 MB, and -- unless HB_PLAN_NO_LONG -- a long-chain scratch of
- * HB_LONG_SCRATCH_MB MiB, default 1024) and, with HB_PLAN_GRAPH, a hipGraph captured on
- * the pipeline's first run.  By default a run is hash_batch's tiled launch; when the batch
+ * build the launch plan.  The plan owns its workspace: about 4 bytes per message and a fixed
+ * part of about 0.6 MB, and from the call that first has it take the pipeline (see below;
+ * hb_plan_create or hb_plan_set_config), unless HB_PLAN_NO_LONG, a long-chain scratch of
+ * HB_LONG_SCRATCH_MB MiB (default 1024), the pipeline's streams and, with HB_PLAN_GRAPH,
+ * hipGraphs captured on its first runs.  By default a run is hash_batch's tiled launch; when the batch
  * has more tiles than the GPU holds at once, its longest messages (of at least
  * HB_LONG_MIN_BLOCKS blocks, default 256, and unless HB_PLAN_NO_LONG) are picked out on the
  * device first and started ahead of the tiles.  The pipeline runs instead in plans with
@@ -216,9 +217,11 @@ int hb_plan_create(hb_plan **plan, uint64_t max_n, int flags);
  * nb = floor((L + 8) / 64) + 1; counting sort by (algorithm, nb) descending; work items
  * of one wave each (algorithm-uniform lanes of near-equal nb); items merged by estimated
  * cost, longest first; one persistent launch whose waves pull items from an atomic queue
- * (hb_plan_create says when a run is the pipeline and when the tiled launch).  Per-run pointers and sizes reach the device through a one-thread
- * kernel launched ahead of the pipeline with them as arguments, so a captured graph is
- * replayed unchanged and consecutive runs need no host synchronisation.  Calls on one plan
+ * (hb_plan_create says when a run is the pipeline and when the tiled launch).  Per-run
+ * pointers and sizes reach the device through a one-thread kernel launched ahead of the
+ * pipeline with them as arguments, so a captured graph is replayed unchanged (one of two:
+ * for batches of at most one wave per SIMD, and larger ones) and consecutive runs need no
+ * host synchronisation.  Calls on one plan
  * must be serialised by the caller (a plan is not thread-safe) and one plan's runs must
  * share a stream, since they share the plan's workspace.
  */
@@ -240,7 +243,9 @@ int hb_plan_run(hb_plan *plan, const uint8_t *algos, int algo, const uint8_t *me
 int hb_plan_config(const hb_plan *plan, int *waves_per_cu, int *msgs_per_lane, int *variant);
 
 /* Force launch choices, and so the pipeline (0 keeps the current waves per CU / messages per
- * lane; variant is set as given, 0..4); drops any captured graph.  HB_EINVAL outside those ranges. */
+ * lane; variant is set as given, 0..4); waits for the device and drops any captured graph.
+ * HB_EINVAL outside those ranges; HB_ENOMEM, the plan unchanged, if the pipeline's scratch cannot
+ * be allocated. */
 int hb_plan_set_config(hb_plan *plan, int waves_per_cu, int msgs_per_lane, int variant);
 
 /* Average duration in milliseconds of the hashing launch over the runs without a graph since

@@ -824,6 +824,10 @@ struct hb_plan {
     double kernel_ms_sum = 0.0;
     int kernel_ms_count = 0;
     void *alloc = nullptr;
+    // the pipeline's own: made when the plan first has a launch choice (prepare_pipeline)
+    uint64_t scratch_bytes = 0;     // of schedule words
+    void *scratch = nullptr;
+    bool pipeline_ready = false;
 };
 
 namespace hb {
@@ -834,6 +838,40 @@ static void drop_graph(hb_plan::Graph &g)
     if (g.graph) hipGraphDestroy(g.graph);
     g.exec = nullptr;
     g.graph = nullptr;
+}
+
+// The pipeline's schedule scratch and streams, for a plan that takes it.  Streams only where
+// needed: each stream may take one of the process's few hardware queues, and streams sharing
+// a queue wait behind each other's kernels.
+static int prepare_pipeline(hb_plan *p)
+{
+    if (p->pipeline_ready) return HB_OK;
+    int current = p->device;
+    hipError_t e = hipGetDevice(&current);
+    if (e == hipSuccess && current != p->device) e = hipSetDevice(p->device);
+    // (a capture on some stream does not forbid these calls: nothing of theirs is captured)
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    const bool exchanged = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+    bool memory = true;
+    if (e == hipSuccess && p->scratch_bytes && !p->scratch) memory = hipMalloc(&p->scratch, p->scratch_bytes) == hipSuccess;
+    if (!memory) p->scratch = nullptr;
+    p->ws.sched = static_cast<uint32_t *>(p->scratch);
+    if (memory && e == hipSuccess && (p->flags & HB_PLAN_GRAPH) && !p->cap_stream)
+        e = hipStreamCreateWithFlags(&p->cap_stream, hipStreamNonBlocking);
+    if (memory && e == hipSuccess && p->long_on && !(p->flags & HB_PLAN_LONG_INLINE)) {
+        if (!p->ev_fork) e = hipEventCreateWithFlags(&p->ev_fork, hipEventDisableTiming);
+        if (e == hipSuccess && !p->ev_join) e = hipEventCreateWithFlags(&p->ev_join, hipEventDisableTiming);
+        if (e == hipSuccess && !p->side) e = hipStreamCreateWithFlags(&p->side, hipStreamNonBlocking);
+    }
+    if (exchanged) (void)hipThreadExchangeStreamCaptureMode(&mode);
+    if (current != p->device) (void)hipSetDevice(current);
+    if (!memory) {
+        (void)hipGetLastError();
+        return set_error(HB_ENOMEM, "hb_plan: schedule scratch allocation failed");
+    }
+    if (e != hipSuccess) return hip_error(e, "hb_plan: stream/event");
+    p->pipeline_ready = true;
+    return HB_OK;
 }
 
 static int grid_items(const hb_plan *p) { return p->cus * 4; }
@@ -1184,8 +1222,9 @@ int hb_plan_create(hb_plan **plan, uint64_t max_n, int flags)
         scratch_blocks = p->long_sched ? sched_blocks : 0;
         p->long_min_key = uint32_t(min_blocks);
     }
-    const uint64_t sz_long = up((long_waves + 1) * 4), sz_sched = up(scratch_blocks * kWaveBlockWords * 4);
-    const uint64_t total = sz_desc + sz_meta + sz_lmeta + 3 * sz_bins + sz_sorted + sz_order + sz_long + sz_sched;
+    const uint64_t sz_long = up((long_waves + 1) * 4);
+    p->scratch_bytes = scratch_blocks * kWaveBlockWords * 4;
+    const uint64_t total = sz_desc + sz_meta + sz_lmeta + 3 * sz_bins + sz_sorted + sz_order + sz_long;
     e = hipMalloc(&p->alloc, total);
     if (e != hipSuccess) { delete p; return set_error(HB_ENOMEM, "hb_plan_create: workspace allocation failed"); }
     char *c = static_cast<char *>(p->alloc);
@@ -1197,8 +1236,7 @@ int hb_plan_create(hb_plan **plan, uint64_t max_n, int flags)
     p->ws.bin_start = reinterpret_cast<uint32_t *>(c); c += sz_bins;
     p->ws.sorted = reinterpret_cast<uint32_t *>(c); c += sz_sorted;
     p->ws.order = reinterpret_cast<uint32_t *>(c); c += sz_order;
-    p->ws.wave_base = reinterpret_cast<uint32_t *>(c); c += sz_long;
-    p->ws.sched = reinterpret_cast<uint32_t *>(c);
+    p->ws.wave_base = reinterpret_cast<uint32_t *>(c);
     p->ws.sched_blocks = uint32_t(sched_blocks);
     p->ws.max_long_waves = uint32_t(long_waves);
     p->ws.max_direct_waves = p->long_on ? uint32_t(p->cus) * 4u : 0u;
@@ -1208,22 +1246,17 @@ int hb_plan_create(hb_plan **plan, uint64_t max_n, int flags)
     p->long_ws.start = p->ws.bin_start;
     p->long_ws.sorted = p->ws.sorted;
     p->long_ws.min_key = std::max<uint32_t>(p->long_min_key, 3);  // a chain's first message has a whole block
-    // Streams only where needed: each stream may take one of the process's few hardware
-    // queues, and streams sharing a queue wait behind each other's kernels.
-    e = hipSuccess;
-    if (flags & HB_PLAN_GRAPH) e = hipStreamCreateWithFlags(&p->cap_stream, hipStreamNonBlocking);
-    if (e == hipSuccess && p->long_on && !(flags & HB_PLAN_LONG_INLINE)) {
-        if ((e = hipStreamCreateWithFlags(&p->side, hipStreamNonBlocking)) == hipSuccess &&
-            (e = hipEventCreateWithFlags(&p->ev_fork, hipEventDisableTiming)) == hipSuccess)
-            e = hipEventCreateWithFlags(&p->ev_join, hipEventDisableTiming);
-    }
-    if (e != hipSuccess) {
-        hb_plan_destroy(p);
-        return hip_error(e, "hb_plan_create: stream/event");
-    }
-    if (const char *w = std::getenv("HB_WAVES_PER_CU")) {
+    const char *w = std::getenv("HB_WAVES_PER_CU");
+    if (w) {
         p->waves_per_cu = std::atoi(w) > 0 ? std::atoi(w) : 16;
         p->tiles = false;  // a launch choice, and so the pipeline
+    }
+    if (w || (flags & (HB_PLAN_NO_SORT | HB_PLAN_AUTOTUNE))) {
+        const int rc = prepare_pipeline(p);
+        if (rc != HB_OK) {
+            hb_plan_destroy(p);
+            return rc;
+        }
     }
     *plan = p;
     return HB_OK;
@@ -1279,6 +1312,9 @@ int hb_plan_set_config(hb_plan *p, int waves_per_cu, int msgs_per_lane, int vari
     if (waves_per_cu < 0 || waves_per_cu > 64 || msgs_per_lane < 0 || msgs_per_lane > kMaxMpl || variant < 0 ||
         variant >= kLoadSchemes)
         return set_error(HB_EINVAL, "hb_plan_set_config: out of range");
+    const int rc = prepare_pipeline(p);
+    if (rc != HB_OK) return rc;
+    if (p->graphs[0].exec || p->graphs[1].exec) hipDeviceSynchronize();  // a replay may still run
     if (waves_per_cu) p->waves_per_cu = waves_per_cu;
     if (msgs_per_lane) p->mpl = msgs_per_lane;
     p->variant = variant;
@@ -1312,6 +1348,7 @@ void hb_plan_destroy(hb_plan *p)
     if (p->ev_fork) hipEventDestroy(p->ev_fork);
     if (p->ev_join) hipEventDestroy(p->ev_join);
     if (p->alloc) hipFree(p->alloc);
+    if (p->scratch) hipFree(p->scratch);
     delete p;
 }
 

@@ -838,12 +838,12 @@ int hb_server_create(hb_server **out, int device, uint64_t hbm_budget_bytes, int
     // sharing one with a compute stream stalls every request behind multi-millisecond
     // chains.  So with four queues the loop keeps to three streams (copy, short, long),
     // with eight to five (two copy, two long), and its plans take no side stream.  Each
-    // stream keeps a plan per step
-    // class, since an idle stream also runs the other class's steps: short-chain steps
-    // are plain persistent-kernel plans (nothing in them reaches the long-chain
-    // threshold); long-chain steps take the long-chain path in one launch with the bulk
-    // (HB_PLAN_LONG_INLINE), so their longest chains run rounds-only from precomputed
-    // schedule words beside the bulk -- the chain is what such a step's latency is.
+    // stream keeps a plan per step class, since an idle stream also runs the other class's
+    // steps.  Either's run is the tiled launch, a tile's longest messages by a chain pair;
+    // a long-chain step of more tiles than the chip holds at once also has its longest
+    // messages started first -- the chain is what such a step's latency is -- and nothing
+    // in a short-chain step is long enough (HB_PLAN_NO_LONG).  HB_PLAN_LONG_INLINE counts
+    // where HB_WAVES_PER_CU has the plans take the bucketed pipeline instead.
     // HB_SERVER_LONG_PLAN_FLAGS sets the long-chain plans' flags, HB_SERVER_PLAN_FLAGS
     // every plan's.  Plans launch eagerly.
     if (const char *v = std::getenv("HB_SERVER_MODE")) s->resident = std::strcmp(v, "resident") == 0;
