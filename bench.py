@@ -487,7 +487,7 @@ def _inputs_record(args, name, **arrays):
 
 def bench_uneven(args, steps=5, warmup=2):
     """SM3 over 2^22 messages with lengths uniform on 0..4096 bytes, packed: the bucketed
-    plan (hipGraph) against the plain form (both take the tiled launch by default; the
+    plan against the plain form (both take the tiled launch by default; the
     autotuner may choose the plan's bucketed pipeline)."""
     import torch
 
@@ -501,9 +501,12 @@ def bench_uneven(args, steps=5, warmup=2):
     plan = hb.Plan(b.n, flags=hb.PLAN_GRAPH | hb.PLAN_AUTOTUNE)
     st_plan = _time_stats(lambda: plan.run(b.messages, offs, lens, algo=2, out=out), steps, warmup, stream)
     t_plan = st_plan["mean"]
+    # an eager plan of the same form (the tiled launch, or the pipeline at the tuned choices), for
+    # the hashing launch's own time
     plan_e = hb.Plan(b.n, flags=0)
-    cfg = plan.config()
-    plan_e.set_config(cfg["waves_per_cu"], cfg["msgs_per_lane"], cfg["variant"])
+    tiled, cfg = plan.tiled(), plan.config()
+    if not tiled:
+        plan_e.set_config(cfg["waves_per_cu"], cfg["msgs_per_lane"], cfg["variant"])
     _time_ms(lambda: plan_e.run(b.messages, offs, lens, algo=2, out=out_d), steps, 1, stream)
     same_eager = bool(torch.equal(out_d, out))
     k_ms = plan_e.kernel_ms()
@@ -534,11 +537,13 @@ def bench_uneven(args, steps=5, warmup=2):
         "alu_frac_plain": round(ops / (t_plain / 1e3) / 1e12 / ALU_PEAK_CO_ISSUE_TOPS["sm3"], 4),
         "alu_frac_batched_kernel_one_op_per_lane_clock": round(ops / (k_ms / 1e3) / 1e12 / ALU_PEAK_TOPS, 4),
         "critical_path_ms_bound": round(_critical_path_ms(b.lengths, None, 2), 3),
+        "plan_form": "tiled launch" if tiled else "pipeline",
         "plan_config": cfg,
         "plan_config_note": "autotuned: waves per CU x messages per lane x load scheme (variant 0 default "
                             "bursts, 1 next-block prefetch, 2 one block per load, 3 two-block and 4 "
                             "four-block bursts), timed on this batch against the tiled launch, which "
-                            "an untuned plan runs",
+                            "an untuned plan runs; plan_form is the faster, which batched_* and "
+                            "alu_frac_batched_kernel are of (the tiled launch uses no plan_config)",
         "untuned_config": default_cfg, "untuned_ms": round(t_default, 3),
         "autotune_gain": round(t_default / t_plan, 3),
         "digests_equal_plain": same_plain,
@@ -553,8 +558,8 @@ def bench_uneven(args, steps=5, warmup=2):
 
 def bench_mixed(args, steps=3, warmup=1):
     """8 GiB, algorithm uniform per message, log-normal lengths (median 512 B, sigma 1.5,
-    cap 1 MiB): the plan in a hipGraph against the plain form, the tiled launch with chain
-    groups for the longest messages in both."""
+    cap 1 MiB): the plan, whose tiled launch starts the longest messages of the batch first,
+    against the plain form, whose tiles take them as they come."""
     import torch
 
     from paper_2407_09333_amd import hb, workloads

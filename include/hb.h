@@ -242,6 +242,11 @@ int hb_plan_run(hb_plan *plan, const uint8_t *algos, int algo, const uint8_t *me
  * plan's histogram); HB_TUNE_CACHE names a file that keeps the cache across processes. */
 int hb_plan_config(const hb_plan *plan, int *waves_per_cu, int *msgs_per_lane, int *variant);
 
+/* 1 where the plan's runs are the tiled launch (its launch choices then go unused, and
+ * hb_plan_set_config with them would have it take the pipeline), 0 where they are the pipeline;
+ * settled by the first run with HB_PLAN_AUTOTUNE. */
+int hb_plan_tiled(const hb_plan *plan);
+
 /* Force launch choices, and so the pipeline (0 keeps the current waves per CU / messages per
  * lane; variant is set as given, 0..4); waits for the device and drops any captured graph.
  * HB_EINVAL outside those ranges; HB_ENOMEM, the plan unchanged, if the pipeline's scratch cannot

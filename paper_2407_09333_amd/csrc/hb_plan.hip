@@ -1009,9 +1009,12 @@ static hipError_t enqueue_pipeline(hb_plan *p, bool many, hipStream_t s, bool ti
 
 static hipError_t enqueue_tiles(hb_plan *p, const PlanDesc &d, hipStream_t s, bool timed);
 
+// Runs are the tiled launch rather than the pipeline.
+static bool runs_tiles(const hb_plan *p) { return p->tiles && !(p->flags & HB_PLAN_NO_SORT); }
+
 static int launch_run(hb_plan *p, const PlanDesc &d, hipStream_t s)
 {
-    if (p->tiles && d.sort) {
+    if (runs_tiles(p)) {
         const hipError_t te = enqueue_tiles(p, d, s, (p->flags & HB_PLAN_GRAPH) == 0);
         return te == hipSuccess ? HB_OK : hip_error(te, "hb_plan_run: launch");
     }
@@ -1305,6 +1308,8 @@ int hb_plan_config(const hb_plan *p, int *waves_per_cu, int *msgs_per_lane, int 
     if (variant) *variant = p->variant;
     return HB_OK;
 }
+
+int hb_plan_tiled(const hb_plan *p) { return p && runs_tiles(p) ? 1 : 0; }
 
 int hb_plan_set_config(hb_plan *p, int waves_per_cu, int msgs_per_lane, int variant)
 {

@@ -64,6 +64,7 @@ def lib() -> ctypes.CDLL:
             L.hb_plan_run.argtypes = [_vp, _vp, _i, _vp, _vp, _vp, _u64, _vp, _vp]
             L.hb_plan_config.argtypes = [_vp, ctypes.POINTER(_i), ctypes.POINTER(_i), ctypes.POINTER(_i)]
             L.hb_plan_set_config.argtypes = [_vp, _i, _i, _i]
+            L.hb_plan_tiled.argtypes = [_vp]
             L.hb_plan_kernel_ms.argtypes = [_vp]
             L.hb_plan_kernel_ms.restype = ctypes.c_double
             L.hb_plan_destroy.argtypes = [_vp]
@@ -264,7 +265,8 @@ def hash_final(algo, states, messages, offsets, lengths, out=None, stream=None):
 
 
 class Plan:
-    """Batched form: bucketed, longest-first persistent launch captured in a hipGraph."""
+    """Batched form: the tiled launch, or (with a launch choice) the bucketed, longest-first
+    persistent pipeline, captured in a hipGraph with PLAN_GRAPH."""
 
     def __init__(self, max_n: int, flags: int = PLAN_GRAPH):
         self._h = _vp()
@@ -288,6 +290,11 @@ class Plan:
         w, m, v = _i(), _i(), _i()
         check(lib().hb_plan_config(self._h, ctypes.byref(w), ctypes.byref(m), ctypes.byref(v)))
         return {"waves_per_cu": w.value, "msgs_per_lane": m.value, "variant": v.value}
+
+    def tiled(self) -> bool:
+        """Whether runs are the tiled launch, which has no launch choices, rather than the
+        pipeline with those of config()."""
+        return bool(lib().hb_plan_tiled(self._h))
 
     def set_config(self, waves_per_cu: int = 0, msgs_per_lane: int = 0, variant: int = 0):
         check(lib().hb_plan_set_config(self._h, waves_per_cu, msgs_per_lane, variant))

@@ -139,3 +139,29 @@ def test_both_sides_of_one_wave_per_simd(hb, variant):
                 got = run_guarded(plan, n, oracle.DIGEST_SIZE[algo], b.messages, b.offsets, b.lengths, algo=algo)
                 assert_same(got, want, f"few {variant} {flags}")
                 plan.close()
+
+
+def test_the_form_that_runs_is_reported(hb):
+    """A plan says whether it runs the tiled launch; launch choices and unsorted plans have it
+    run the pipeline; an autotuned one settles it with its first run, after which a plan set up
+    as it reports has the same form."""
+    b = workloads.uniform_lengths_batch(2, 3_000, 2048, seed=81)
+    want = oracle.hash_batch(2, b.messages, b.offsets, b.lengths)
+    plan = hb.Plan(b.n)
+    assert plan.tiled()
+    plan.set_config(waves_per_cu=8)
+    assert not plan.tiled()
+    plan.close()
+    plan = hb.Plan(b.n, flags=hb.PLAN_NO_SORT)
+    assert not plan.tiled()
+    plan.close()
+    plan = hb.Plan(b.n, flags=hb.PLAN_AUTOTUNE)
+    assert_same(plan.run(b.messages, b.offsets, b.lengths, algo=2).cpu().numpy(), want, "autotuned")
+    twin = hb.Plan(b.n, flags=0)
+    if not plan.tiled():
+        twin.set_config(**plan.config())
+    assert twin.tiled() == plan.tiled()
+    assert_same(twin.run(b.messages, b.offsets, b.lengths, algo=2).cpu().numpy(), want, "twin")
+    assert twin.kernel_ms() > 0
+    plan.close()
+    twin.close()
