@@ -237,9 +237,10 @@ int hb_plan_run(hb_plan *plan, const uint8_t *algos, int algo, const uint8_t *me
  *   3  bursts of two whole blocks for every algorithm
  *   4  bursts of four whole blocks for every algorithm
  * With HB_PLAN_AUTOTUNE the first run times waves per CU {8, 16, 32} x messages per lane
- * {1, 2} x the five schemes and the tiled launch on its own input and keeps the fastest, cached per device, CU
- * count, algorithm mix and length bucket (mean block count and spread, read from the
- * plan's histogram); HB_TUNE_CACHE names a file that keeps the cache across processes. */
+ * {1, 2} x the five schemes and the tiled launch on its own input and keeps the fastest, cached
+ * per device, CU count, algorithm mix, length bucket (mean block count and spread, read from
+ * the plan's histogram), the plan's flags where they matter, and whether the batch's tiles fit
+ * the GPU at once; HB_TUNE_CACHE names a file that keeps the cache across processes. */
 int hb_plan_config(const hb_plan *plan, int *waves_per_cu, int *msgs_per_lane, int *variant);
 
 /* 1 where the plan's runs are the tiled launch (its launch choices then go unused, and

@@ -16,6 +16,7 @@
 #include <map>
 #include <mutex>
 #include <string>
+#include <tuple>
 #include <vector>
 
 #include "../../include/hb.h"
@@ -736,14 +737,14 @@ struct TuneKey {
     int cus;
     int algo_mask;
     int len_bucket;
+    int form;  // what else the choice depends on (tune_form); kAnyForm: not known
     bool operator<(const TuneKey &o) const
     {
-        if (arch != o.arch) return arch < o.arch;
-        if (cus != o.cus) return cus < o.cus;
-        if (algo_mask != o.algo_mask) return algo_mask < o.algo_mask;
-        return len_bucket < o.len_bucket;
+        return std::tie(arch, cus, algo_mask, len_bucket, form) < std::tie(o.arch, o.cus, o.algo_mask, o.len_bucket, o.form);
     }
 };
+
+constexpr int kAnyForm = -1;
 
 struct TuneChoice {
     int waves_per_cu;
@@ -757,8 +758,9 @@ static std::map<TuneKey, TuneChoice> g_tune_cache;
 static bool g_tune_loaded = false;
 
 // Optional persistence: HB_TUNE_CACHE names a text file of lines
-// "arch cus algo_mask length_bucket waves_per_cu msgs_per_lane variant tiles"; a line without
-// the last number names the pipeline.
+// "arch cus algo_mask length_bucket waves_per_cu msgs_per_lane variant tiles form".  Lines without
+// the last number or two were written when nothing said what plans and batches they are for: of
+// such a line the pipeline's choices are taken over, and timed against the tiled launch.
 static void load_tune_cache()
 {
     std::lock_guard<std::mutex> g(g_tune_mu);
@@ -769,12 +771,12 @@ static void load_tune_cache()
     FILE *f = std::fopen(path, "r");
     if (!f) return;
     char arch[64], line[256];
-    int cus, mask, bucket, w, m, v, t;
+    int cus, mask, bucket, w, m, v, t, form;
     while (std::fgets(line, sizeof(line), f)) {
         t = 0;
-        if (std::sscanf(line, "%63s %d %d %d %d %d %d %d", arch, &cus, &mask, &bucket, &w, &m, &v, &t) >= 7 && w > 0 &&
-            w <= 64 && m > 0 && m <= kMaxMpl && v >= 0 && v < kLoadSchemes)
-            g_tune_cache[TuneKey{arch, cus, mask, bucket}] = TuneChoice{w, m, v, t == 1};
+        const int got = std::sscanf(line, "%63s %d %d %d %d %d %d %d %d", arch, &cus, &mask, &bucket, &w, &m, &v, &t, &form);
+        if (got >= 7 && w > 0 && w <= 64 && m > 0 && m <= kMaxMpl && v >= 0 && v < kLoadSchemes)
+            g_tune_cache[TuneKey{arch, cus, mask, bucket, got == 9 && form >= 0 ? form : kAnyForm}] = TuneChoice{w, m, v, t == 1};
     }
     std::fclose(f);
 }
@@ -786,9 +788,12 @@ static void save_tune_cache()
     std::lock_guard<std::mutex> g(g_tune_mu);
     FILE *f = std::fopen(path, "w");
     if (!f) return;
-    for (auto &kv : g_tune_cache)
-        std::fprintf(f, "%s %d %d %d %d %d %d %d\n", kv.first.arch.c_str(), kv.first.cus, kv.first.algo_mask,
+    for (auto &kv : g_tune_cache) {
+        std::fprintf(f, "%s %d %d %d %d %d %d %d", kv.first.arch.c_str(), kv.first.cus, kv.first.algo_mask,
                      kv.first.len_bucket, kv.second.waves_per_cu, kv.second.mpl, kv.second.variant, int(kv.second.tiles));
+        if (kv.first.form == kAnyForm) std::fprintf(f, "\n");
+        else std::fprintf(f, " %d\n", kv.first.form);
+    }
     std::fclose(f);
 }
 
@@ -1090,92 +1095,101 @@ static int length_bucket(const hb_plan *p, hipStream_t s, int &bucket)
     return HB_OK;
 }
 
+// What else the faster choice depends on: which long-chain path the pipeline has, whether
+// the tiled launch may run at all, and whether the batch's tiles fill the chip more than once
+// (only then are its longest messages picked out first).
+static int tune_form(const hb_plan *p, const PlanDesc &d)
+{
+    return (d.sort ? 1 : 0) | (p->long_on ? 2 : 0) | (p->flags & HB_PLAN_LONG_INLINE ? 4 : 0) |
+           (ragged_in_one_round(d.n, d.algos != nullptr) ? 8 : 0);
+}
+
 // Time each launch choice on this run's input and keep the fastest, cached per device,
-// algorithm mix and length bucket: waves per CU, messages per lane and the message-load
-// scheme (bursts of 1, 2 or 4 whole blocks, or next-block prefetch; kLoadSchemes).
+// algorithm mix, length bucket and tune_form: waves per CU, messages per lane and the
+// message-load scheme (bursts of 1, 2 or 4 whole blocks, or next-block prefetch;
+// kLoadSchemes), and the tiled launch.
 static int autotune(hb_plan *p, const PlanDesc &d0, hipStream_t s, int algo_mask)
 {
     const int flags_saved = p->flags;
+    const TuneChoice before{p->waves_per_cu, p->mpl, p->variant, p->tiles};
+    auto choose = [&](const TuneChoice &c) {
+        p->waves_per_cu = c.waves_per_cu;
+        p->mpl = c.mpl;
+        p->variant = c.variant;
+        p->tiles = c.tiles;
+    };
+    auto settle = [&](const TuneChoice &c, int status) {
+        choose(c);
+        p->flags = flags_saved;
+        return status;
+    };
     p->flags &= ~HB_PLAN_GRAPH;
     p->tiles = false;
     // one run with the current choice fills the histogram that names the length bucket
     PlanDesc d = d0;
     d.mpl = p->mpl;
     int rc = launch_run(p, d, s);
-    TuneKey key{p->arch, p->cus, algo_mask, 0};
+    TuneKey key{p->arch, p->cus, algo_mask, 0, tune_form(p, d)};
     if (rc == HB_OK) rc = length_bucket(p, s, key.len_bucket);
-    if (rc != HB_OK) { p->flags = flags_saved; return rc; }
+    if (rc != HB_OK) return settle(before, rc);
     load_tune_cache();
+    std::vector<TuneChoice> choices;
     {
         std::lock_guard<std::mutex> g(g_tune_mu);
         auto it = g_tune_cache.find(key);
         if (it != g_tune_cache.end()) {
-            p->waves_per_cu = it->second.waves_per_cu;
-            p->mpl = it->second.mpl;
-            p->variant = it->second.variant;
-            p->tiles = it->second.tiles;
-            p->flags = flags_saved;
             p->tune_bucket = key.len_bucket;
-            return HB_OK;
+            return settle(it->second, HB_OK);
         }
+        TuneKey any = key;
+        any.form = kAnyForm;
+        it = g_tune_cache.find(any);
+        if (it != g_tune_cache.end()) choices.push_back(TuneChoice{it->second.waves_per_cu, it->second.mpl, it->second.variant, false});
     }
-    float best = 1e30f;
-    TuneChoice bestc{p->waves_per_cu, p->mpl, p->variant, false};
-    const int wpcs[] = {8, 16, 32};
-    const int mpls[] = {1, 2};
+    if (choices.empty())
+        for (int var = 0; var < kLoadSchemes; ++var)
+            for (int mpl : {1, 2})
+                for (int w : {8, 16, 32}) choices.push_back(TuneChoice{w, mpl, var, false});
+    if (d.sort) choices.push_back(TuneChoice{before.waves_per_cu, before.mpl, before.variant, true});
     hipEvent_t a = nullptr, b = nullptr;
     hipError_t e = hipEventCreate(&a);
     if (e == hipSuccess) e = hipEventCreate(&b);
-    if (e != hipSuccess) { p->flags = flags_saved; return hip_error(e, "hb_plan_run: autotune events"); }
-    for (int var = 0; var < kLoadSchemes && rc == HB_OK; ++var)
-        for (int mpl : mpls)
-            for (int w : wpcs) {
-                p->waves_per_cu = w;
-                p->variant = var;
-                p->mpl = mpl;
-                d.mpl = mpl;
-                float tot = 0.f;
-                for (int rep = 0; rep < 2 && rc == HB_OK; ++rep) {
-                    hipEventRecord(a, s);
-                    rc = launch_run(p, d, s);
-                    hipEventRecord(b, s);
-                    hipEventSynchronize(b);
-                    float ms = 0.f;
-                    hipEventElapsedTime(&ms, a, b);
-                    if (rep) tot += ms;  // first repetition is a warm-up
-                }
-                if (rc == HB_OK && tot < best) { best = tot; bestc = TuneChoice{w, mpl, var, false}; }
-            }
-    if (d.sort) {  // and the tiled launch
-        p->tiles = true;
-        float tot = 0.f;
-        for (int rep = 0; rep < 2 && rc == HB_OK; ++rep) {
+    if (e != hipSuccess) {
+        if (a) hipEventDestroy(a);
+        return settle(before, hip_error(e, "hb_plan_run: autotune events"));
+    }
+    float best = 1e30f;
+    TuneChoice bestc = choices.front();
+    for (const TuneChoice &c : choices) {
+        choose(c);
+        d.mpl = c.mpl;
+        float ms = 0.f;
+        for (int rep = 0; rep < 2 && rc == HB_OK; ++rep) {  // the first is a warm-up
             hipEventRecord(a, s);
             rc = launch_run(p, d, s);
             hipEventRecord(b, s);
             hipEventSynchronize(b);
-            hipEventElapsedTime(&tot, a, b);
+            hipEventElapsedTime(&ms, a, b);
         }
-        bestc.tiles = rc == HB_OK && tot < best;
+        if (rc != HB_OK) break;
+        if (ms >= best) continue;
+        best = ms;
+        if (c.tiles) bestc.tiles = true;  // the last; the best of the pipeline's choices stay for config()
+        else bestc = c;
     }
     hipEventDestroy(a);
     hipEventDestroy(b);
     collect_timing(p, true);
     p->kernel_ms_sum = 0.0;
     p->kernel_ms_count = 0;
-    p->flags = flags_saved;
-    p->waves_per_cu = bestc.waves_per_cu;
-    p->mpl = bestc.mpl;
-    p->variant = bestc.variant;
-    p->tiles = bestc.tiles;
+    if (rc != HB_OK) return settle(before, rc);
     p->tune_bucket = key.len_bucket;
-    if (rc != HB_OK) return rc;
     {
         std::lock_guard<std::mutex> g(g_tune_mu);
         g_tune_cache[key] = bestc;
     }
     save_tune_cache();
-    return HB_OK;
+    return settle(bestc, HB_OK);
 }
 
 constexpr uint64_t kNoallocMaxN = 1ull << 20;
