@@ -1,7 +1,9 @@
 // hb_kernels.hip -- fixed-length batch-hashing kernels: one lane per message, in index order.
 #include <algorithm>
 #include <atomic>
+#include <cstddef>
 #include <cstdlib>
+#include <type_traits>
 
 #include "hb_device.hpp"
 #include "hb_internal.hpp"
@@ -103,7 +105,7 @@ __device__ __forceinline__ void plain_lds_wave(const uint8_t *__restrict__ msgs,
     // The two staged blocks of this lane's message.  MD5 and SHA-1 read both blocks' words
     // from LDS up front, so the second block's reads complete under the first block's
     // compression (16 more registers; SM3, with more state live, reads one block at a time
-    // to stay within four waves per SIMD).
+    // to stay within the registers of five waves per SIMD).
     constexpr bool kReadAhead = A != SM3;
     auto words = [&](int h, uint32_t *w) {
 #pragma unroll
@@ -188,12 +190,24 @@ k_plain_lds(const uint8_t *__restrict__ msgs, uint64_t n, uint64_t len, uint8_t 
 // As k_plain_lds for lengths divisible by 64: the last block's words come formed from the host
 // (compress_uniform).  2^22 x 256 bytes, a fifth of whose blocks are such: SM3 602 us with the
 // schedule expanded by every lane, 565 so, SHA-1 330 and 310; 300,007 x 64 SM3 21.5 and 20.4.
+//
+// The kernel's arguments, laid out as a struct's members are: where the words are.
+template <int A> struct PadArgs {
+    const uint8_t *msgs;
+    uint64_t n, len;
+    uint8_t *out;
+    UniformWords<A> pad;
+};
+
 template <int A>
 __global__ __launch_bounds__(kPlainBlock) __attribute__((amdgpu_waves_per_eu(A == MD5 ? 5 : 4))) void
 k_plain_lds_pad(const uint8_t *__restrict__ msgs, uint64_t n, uint64_t len, uint8_t *__restrict__ out, UniformWords<A>)
 {
-    // the words where they are in the kernel's arguments, after four of eight bytes
-    const HB_CONSTANT uint32_t *pad = (const HB_CONSTANT uint32_t *)__builtin_amdgcn_kernarg_segment_ptr() + 8;
+    static_assert(std::is_same_v<decltype(&k_plain_lds_pad<A>),
+                                 void (*)(decltype(PadArgs<A>::msgs), decltype(PadArgs<A>::n), decltype(PadArgs<A>::len),
+                                          decltype(PadArgs<A>::out), decltype(PadArgs<A>::pad))>);
+    const HB_CONSTANT uint32_t *pad =
+        (const HB_CONSTANT uint32_t *)__builtin_amdgcn_kernarg_segment_ptr() + offsetof(PadArgs<A>, pad) / sizeof(uint32_t);
     plain_lds_wave<A, true, true>(msgs, n, len, out, pad);
 }
 
