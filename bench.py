@@ -270,9 +270,10 @@ def bench_valu_probe():
     """The integer-VALU issue rates the roofline's peak rests on (hb_probe_valu): SIMD cycles
     per wave instruction for each instruction kind and two mixes, and per wave and 64-byte
     block for each algorithm's compression from registers, at 1, 4 and 8 waves per SIMD (one
-    wave alone shows a lone chain's issue limit); beside them the cycles of the two issue
-    models (every op at its own kind's rate; both VALU places kept busy) and the fraction of
-    each that the compressions as compiled from C++ reach."""
+    wave alone shows a lone chain's issue limit), the compressions in both their forms
+    (*_shared: for SIMDs that waves share); beside them the cycles of the two issue models
+    (every op at its own kind's rate; both VALU places kept busy) and the fractions of them
+    that the compressions reach."""
     from paper_2407_09333_amd import hb
 
     out = {"unit": "SIMD cycles per wave instruction (md5/sha1/sm3: per wave and 64-byte block)"}
@@ -288,6 +289,8 @@ def bench_valu_probe():
     out["co_issue_cycles_per_block"] = {a: round(co_issue_cycles(a), 1) for a in ALGO_NAMES}
     out["compression_frac_of_co_issue_peak_at_4_waves"] = {
         a: round(co_issue_cycles(a) / out["waves_per_simd_4"][a]["cycles"], 3) for a in ALGO_NAMES}
+    out["shared_compression_frac_of_co_issue_peak_at_4_waves"] = {
+        a: round(co_issue_cycles(a) / out["waves_per_simd_4"][a + "_shared"]["cycles"], 3) for a in ALGO_NAMES}
     return out
 
 

@@ -60,7 +60,10 @@ int hb_device_info(int *cu_count, int *wave_size, int *clock_khz, char *arch_nam
  *   kind            HB_PROBE_*: ADD3 v_add3_u32, ALIGNBIT v_alignbit_b32, BITOP3
  *                   v_bitop3_b32, ADD v_add_u32 (VOP2), XOR v_xor_b32 (VOP2), XAD v_xad_u32,
  *                   PERM v_perm_b32, MIX_ALT bitop3 and alignbit alternating, MIX_2_1 two
- *                   bitop3 to one alignbit, MD5 / SHA1 / SM3 compressions
+ *                   bitop3 to one alignbit, MD5 / SHA1 / SM3 compressions as a wave alone on
+ *                   its SIMD runs them; MIX_3_1 three bitop3 to one alignbit, MIX_3_1_RUNS the
+ *                   same in runs of 24 and 8, the latter at raised wave priority, MD5_SHARED /
+ *                   SHA1_SHARED / SM3_SHARED the compressions for SIMDs that waves share
  *   waves_per_simd  1..8
  *   cycles_out      host: SIMD cycles per wave instruction (instruction kinds) or per wave
  *                   and 64-byte block (compression kinds), best of three launches
@@ -71,7 +74,8 @@ int hb_device_info(int *cu_count, int *wave_size, int *clock_khz, char *arch_nam
  */
 enum { HB_PROBE_ADD3 = 0, HB_PROBE_ALIGNBIT = 1, HB_PROBE_BITOP3 = 2, HB_PROBE_ADD = 3, HB_PROBE_XOR = 4,
        HB_PROBE_XAD = 5, HB_PROBE_PERM = 6, HB_PROBE_MIX_ALT = 7, HB_PROBE_MIX_2_1 = 8, HB_PROBE_MD5 = 9,
-       HB_PROBE_SHA1 = 10, HB_PROBE_SM3 = 11, HB_PROBE_KINDS = 12 };
+       HB_PROBE_SHA1 = 10, HB_PROBE_SM3 = 11, HB_PROBE_MIX_3_1 = 12, HB_PROBE_MIX_3_1_RUNS = 13,
+       HB_PROBE_MD5_SHARED = 14, HB_PROBE_SHA1_SHARED = 15, HB_PROBE_SM3_SHARED = 16, HB_PROBE_KINDS = 17 };
 int hb_probe_valu(int kind, int waves_per_simd, double *cycles_out, double *clock_ghz_out);
 
 /*

@@ -7,25 +7,25 @@
 // waves can therefore run two instructions at a time, one of them plain, and the least a
 // block can take is max(4 wide, 2 (plain + wide)) cycles.  Left to itself the oldest wave
 // issues whenever it can, with its plain instructions too, and every other wave ends up
-// stopped at its next wide instruction: three plain to one wide, four waves, took 3.92
+// stopped at its next wide instruction: three plain to one wide, four waves, take 3.3
 // cycles an instruction where 2.0 are possible, and the compiler's order of MD5 / SHA-1 /
-// SM3 1,161 / 2,392 / 5,178 cycles per wave and block.
+// SM3 1,319 / 2,403 / 5,294 cycles per wave and block (hb_probe_valu, from registers).
 //
 // So each round is written as one run of plain instructions and one of wide ones, and a
 // wave raises its priority for the wide run: a wave waiting for the wide place then goes
-// before the waves that could use the other.  The same three-to-one pattern takes 2.54
-// cycles an instruction, and the compressions, from registers at four waves per SIMD, take
-// 801 (MD5), 1,688 (SHA-1) and 3,613 (SM3) cycles -- 1.45, 1.42 and 1.43 times as fast; at
-// eight waves 750, 1,573 and 3,410 (the least possible: 648, about 1,350 and 2,900).  Two
+// before the waves that could use the other.  The three-to-one pattern so takes 2.44
+// cycles an instruction, and the compressions, from registers at four waves per SIMD,
+// 804 (MD5), 1,712 (SHA-1) and 3,704 (SM3) cycles -- 1.64, 1.40 and 1.43 times as fast; at
+// eight waves 764, 1,603 and 3,523 (the least possible: 648, about 1,350 and 2,950).  Two
 // places working also draw more power: over milliseconds the engine clock falls from 2.37
-// to 2.05-2.15 GHz, so the time per block at five waves falls by less, MD5 482 to 397 ns,
-// SHA-1 1,002 to 813, SM3 2,152 to 1,729.
+// to 2.05-2.15 GHz, so kernels gain less than the cycles say.
 //
 // The choice of instructions follows from the same two bounds: of the sums that could be
 // one wide v_add3_u32 / v_xad_u32 or two plain instructions, each round takes as many wide
 // ones as keep 4 wide <= 2 (plain + wide): MD5 one (3 plain + 2 wide a step), SHA-1 one of
-// two (5 + 4 a round), SM3 two of four (12 + 12 a round with its expansion).  Measured the
-// other way: MD5 without v_add3_u32 995, SHA-1 without 1,888, SM3 without v_xad_u32 3,924.
+// two (5 + 4 a round), SM3 two of four (12 + 12 a round with its expansion).  Written the
+// other way they were slower by, MD5 without v_add3_u32 24 %, SHA-1 without 12, SM3 without
+// v_xad_u32 9.
 //
 // What a kernel does between two blocks -- loads, realignment and byte reversal, v_perm_b32
 // being wide -- runs at the raised priority too, so that a wave gets its next loads out: each
@@ -33,7 +33,7 @@
 // 4,096 bytes: 4,849 us when it ended at the plain one, 4,688 so).
 //
 // A wave alone on its SIMD issues one instruction per four cycles or slower whatever its
-// kind, so there the two priority changes a round only cost (MD5 1,886 against 1,208
+// kind, so there the two priority changes a round only cost (MD5 1,896 against 1,385
 // cycles): launches of at most one wave per SIMD take compress<A> instead.
 //
 // Each function is one asm block: the order is the point, and the compiler neither keeps
@@ -313,8 +313,8 @@ __device__ __forceinline__ void sm3_compress_many(uint32_t s8[8], const uint32_t
     for (int t = 0; t < 16; ++t) W[t] = M[t];
     uint32_t a = s8[0], b = s8[1], c = s8[2], d = s8[3], e = s8[4], f = s8[5], g = s8[6], h = s8[7];
     uint32_t p, q, r, s, x0, x1, y0, y1;
-    // the 48 distinct round constants as scalar operands: 4-byte adds (3,613 against 3,690
-    // cycles with 8-byte literals)
+    // the 48 distinct round constants as scalar operands: 4-byte adds (8-byte literals took 2 %
+    // longer)
     asm volatile(
         HB_SM3_H2(a) HB_PLAIN
         HB_SM3_F(a, b, c, d, e, f, g, h, w0, w4, k0, HB_TT_XOR3, HB_TT_XOR3) HB_SM3_H0 HB_SM3_H1(b, d, f, h) HB_SM3_H2(d) HB_SM3_E(h)

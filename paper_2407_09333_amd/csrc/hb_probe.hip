@@ -3,7 +3,8 @@
 // Every CU is filled with `wps` workgroups of four waves (wps waves per SIMD).  An
 // instruction kind runs as long unrolled chains over eight independent accumulators per
 // lane, so no instruction waits for the one before it; a compression kind runs the
-// library's own compress<A> on register data with no memory traffic.  Each workgroup's
+// library's own compress<A> or (shared) compress_many<A> on register data with no memory
+// traffic.  Each workgroup's
 // first lane records s_memtime (engine cycles) and s_memrealtime (100 MHz) around its loop;
 // the host turns the span of all workgroups into SIMD cycles per wave instruction (or per
 // wave and 64-byte block).  Writes go only to the timestamp buffer (four words per
@@ -42,6 +43,11 @@ constexpr int kProbeBlocks = 256;   // compressions per lane
 #define HB_PR_TWO_ONE HB_PR_BITOP3(0) HB_PR_BITOP3(1) HB_PR_ALIGNBIT(2) HB_PR_BITOP3(3) \
                       HB_PR_BITOP3(4) HB_PR_ALIGNBIT(5) HB_PR_BITOP3(6) HB_PR_BITOP3(7) \
                       HB_PR_ALIGNBIT(0) HB_PR_BITOP3(1) HB_PR_BITOP3(2) HB_PR_ALIGNBIT(3)
+// three bitop3 to one alignbit, mixed and in runs (24 and 8) at two priorities
+#define HB_PR_THREE_ONE HB_PR_BITOP3(0) HB_PR_BITOP3(1) HB_PR_BITOP3(2) HB_PR_ALIGNBIT(3) \
+                        HB_PR_BITOP3(4) HB_PR_BITOP3(5) HB_PR_BITOP3(6) HB_PR_ALIGNBIT(7)
+#define HB_PR_RUNS HB_PR_8(HB_PR_BITOP3) HB_PR_8(HB_PR_BITOP3) HB_PR_8(HB_PR_BITOP3) \
+                   "s_setprio 1\n\t" HB_PR_8(HB_PR_ALIGNBIT) "s_setprio 0\n\t"
 #define HB_PR_ASM(BODY, REPT)                                                                      \
     asm volatile(".rept " #REPT "\n\t" BODY ".endr"                                              \
                  : "+v"(a[0]), "+v"(a[1]), "+v"(a[2]), "+v"(a[3]), "+v"(a[4]), "+v"(a[5]),      \
@@ -59,7 +65,9 @@ template <int K> __device__ __forceinline__ void probe_chunk(uint32_t *a, uint32
     else if constexpr (K == HB_PROBE_XAD) HB_PR_ASM(HB_PR_8(HB_PR_XAD), 8);
     else if constexpr (K == HB_PROBE_PERM) HB_PR_ASM(HB_PR_8(HB_PR_PERM), 8);
     else if constexpr (K == HB_PROBE_MIX_ALT) HB_PR_ASM(HB_PR_ALT, 8);
-    else HB_PR_ASM(HB_PR_TWO_ONE, 5);
+    else if constexpr (K == HB_PROBE_MIX_2_1) HB_PR_ASM(HB_PR_TWO_ONE, 5);
+    else if constexpr (K == HB_PROBE_MIX_3_1) HB_PR_ASM(HB_PR_THREE_ONE, 8);
+    else HB_PR_ASM(HB_PR_RUNS, 2);
 }
 
 template <int K> constexpr int chunk_instructions() { return K == HB_PROBE_MIX_2_1 ? 60 : 64; }
@@ -92,7 +100,7 @@ template <int K> __global__ __launch_bounds__(kProbeThreads) void k_probe_instr(
 
 // the library's compression on register data; one xor per block feeds the state back into
 // the words so nothing is loop-invariant
-template <int A> __global__ __launch_bounds__(kProbeThreads) void k_probe_compress(uint64_t *ts, uint32_t *sink, uint32_t seed)
+template <int A, bool MANY> __global__ __launch_bounds__(kProbeThreads) void k_probe_compress(uint64_t *ts, uint32_t *sink, uint32_t seed)
 {
     uint32_t w[16], s[8];
 #pragma unroll
@@ -100,7 +108,7 @@ template <int A> __global__ __launch_bounds__(kProbeThreads) void k_probe_compre
     init_state<A>(s);
     const uint64_t t0 = __builtin_amdgcn_s_memtime(), r0 = __builtin_amdgcn_s_memrealtime();
     for (int b = 0; b < kProbeBlocks; ++b) {
-        compress<A>(s, w);
+        compress<A, MANY>(s, w);
         w[b & 15] ^= s[0];
     }
     stamp(ts, t0, r0);
@@ -110,19 +118,23 @@ template <int A> __global__ __launch_bounds__(kProbeThreads) void k_probe_compre
     sink[blockIdx.x * kProbeThreads + threadIdx.x] = z;
 }
 
+constexpr bool is_compression(int k) { return (k >= HB_PROBE_MD5 && k <= HB_PROBE_SM3) || k >= HB_PROBE_MD5_SHARED; }
+
 template <int K> void launch_probe(int blocks, uint64_t *ts, uint32_t *sink, uint32_t seed)
 {
-    if constexpr (K <= HB_PROBE_MIX_2_1)
-        hipLaunchKernelGGL(k_probe_instr<K>, dim3(uint32_t(blocks)), dim3(kProbeThreads), 0, 0, ts, sink, seed);
+    const dim3 grid{uint32_t(blocks), 1, 1}, block{kProbeThreads, 1, 1};
+    if constexpr (!is_compression(K))
+        hipLaunchKernelGGL(k_probe_instr<K>, grid, block, 0, 0, ts, sink, seed);
+    else if constexpr (K >= HB_PROBE_MD5_SHARED)
+        hipLaunchKernelGGL((k_probe_compress<K - HB_PROBE_MD5_SHARED, true>), grid, block, 0, 0, ts, sink, seed);
     else
-        hipLaunchKernelGGL(k_probe_compress<K - HB_PROBE_MD5>, dim3(uint32_t(blocks)), dim3(kProbeThreads), 0, 0, ts,
-                           sink, seed);
+        hipLaunchKernelGGL((k_probe_compress<K - HB_PROBE_MD5, false>), grid, block, 0, 0, ts, sink, seed);
 }
 
 // units (wave instructions or wave-blocks) one wave runs
 template <int K> constexpr double units_per_wave()
 {
-    if constexpr (K <= HB_PROBE_MIX_2_1) return double(kProbeReps) * chunk_instructions<K>();
+    if constexpr (!is_compression(K)) return double(kProbeReps) * chunk_instructions<K>();
     else return double(kProbeBlocks);
 }
 
@@ -193,7 +205,12 @@ extern "C" int hb_probe_valu(int kind, int waves_per_simd, double *cycles_out, d
     case HB_PROBE_MIX_2_1: rc = run_probe<HB_PROBE_MIX_2_1>(blocks, cus, ts, sink, cycles_out, clock_ghz_out); break;
     case HB_PROBE_MD5: rc = run_probe<HB_PROBE_MD5>(blocks, cus, ts, sink, cycles_out, clock_ghz_out); break;
     case HB_PROBE_SHA1: rc = run_probe<HB_PROBE_SHA1>(blocks, cus, ts, sink, cycles_out, clock_ghz_out); break;
-    default: rc = run_probe<HB_PROBE_SM3>(blocks, cus, ts, sink, cycles_out, clock_ghz_out); break;
+    case HB_PROBE_SM3: rc = run_probe<HB_PROBE_SM3>(blocks, cus, ts, sink, cycles_out, clock_ghz_out); break;
+    case HB_PROBE_MIX_3_1: rc = run_probe<HB_PROBE_MIX_3_1>(blocks, cus, ts, sink, cycles_out, clock_ghz_out); break;
+    case HB_PROBE_MIX_3_1_RUNS: rc = run_probe<HB_PROBE_MIX_3_1_RUNS>(blocks, cus, ts, sink, cycles_out, clock_ghz_out); break;
+    case HB_PROBE_MD5_SHARED: rc = run_probe<HB_PROBE_MD5_SHARED>(blocks, cus, ts, sink, cycles_out, clock_ghz_out); break;
+    case HB_PROBE_SHA1_SHARED: rc = run_probe<HB_PROBE_SHA1_SHARED>(blocks, cus, ts, sink, cycles_out, clock_ghz_out); break;
+    default: rc = run_probe<HB_PROBE_SM3_SHARED>(blocks, cus, ts, sink, cycles_out, clock_ghz_out); break;
     }
     (void)hipFree(sink);
     (void)hipFree(ts);

@@ -130,7 +130,8 @@ def device_info() -> dict:
 
 # hb_probe_valu kinds, in the order of include/hb.h
 PROBE_KINDS = ["add3", "alignbit", "bitop3", "add", "xor", "xad", "perm", "mix_bitop3_alignbit_1_1",
-               "mix_bitop3_alignbit_2_1", "md5", "sha1", "sm3"]
+               "mix_bitop3_alignbit_2_1", "md5", "sha1", "sm3", "mix_bitop3_alignbit_3_1",
+               "mix_bitop3_alignbit_3_1_runs", "md5_shared", "sha1_shared", "sm3_shared"]
 
 
 def probe_valu(kind: str, waves_per_simd: int = 4) -> tuple[float, float]:
