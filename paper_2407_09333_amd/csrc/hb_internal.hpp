@@ -18,8 +18,8 @@ hipError_t launch_fixed(int algo, const uint8_t *msgs, uint64_t n, uint64_t fixe
                         hipStream_t stream);
 
 // As launch_fixed for packed digests, by chain pairs (hb_ragged.hip), for the batches that
-// fixed_chain_applies to: few messages.
-bool fixed_chain_applies(int algo, uint64_t n, uint64_t len);
+// fixed_chain_applies to: few messages.  staged: the other way would stage them through LDS.
+bool fixed_chain_applies(int algo, uint64_t n, uint64_t len, bool staged);
 hipError_t launch_fixed_chain(int algo, const uint8_t *msgs, uint64_t n, uint64_t len, uint8_t *out, hipStream_t stream);
 
 int digest_size(int algo);

@@ -411,9 +411,10 @@ hipError_t launch_fixed(int algo, const uint8_t *msgs, uint64_t n, uint64_t fixe
                         hipStream_t stream)
 {
     // few messages: chain pairs, unless HB_PLAIN_LDS asks for one of the kernels here
-    if (!std::getenv("HB_PLAIN_LDS") && stride == uint32_t(digest_size(algo)) && fixed_chain_applies(algo, n, fixed_len))
+    const bool staged = plain_lds_applies(msgs, fixed_len, stride, algo);
+    if (!std::getenv("HB_PLAIN_LDS") && stride == uint32_t(digest_size(algo)) && fixed_chain_applies(algo, n, fixed_len, staged))
         return launch_fixed_chain(algo, msgs, n, fixed_len, out, stream);
-    if (plain_lds_applies(msgs, fixed_len, stride, algo)) {
+    if (staged) {
         switch (algo) {
         case MD5: return launch_lds_a<MD5>(msgs, n, fixed_len, out, stream);
         case SHA1: return launch_lds_a<SHA1>(msgs, n, fixed_len, out, stream);

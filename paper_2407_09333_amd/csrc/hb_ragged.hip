@@ -579,7 +579,7 @@ hipError_t launch_ragged(const uint8_t *algos, int algo, const uint8_t *msgs, co
     return hipGetLastError();
 }
 
-bool fixed_chain_applies(int algo, uint64_t n, uint64_t len)
+bool fixed_chain_applies(int algo, uint64_t n, uint64_t len, bool staged)
 {
     // Where it was measured faster than a lane to a message (us, lane / chain): SM3 from three
     // blocks on (120 bytes: 14.7 / 13.4; 512: 28.3 / 24.9), SHA-1 from four (250 bytes: 13.2 /
@@ -588,7 +588,10 @@ bool fixed_chain_applies(int algo, uint64_t n, uint64_t len)
     // 89 / 79).  MD5, whose schedule is one addition to
     // a word, for its loads: from 64 blocks, up to 32 messages to a pair (144 x 2 KiB 27.2 / 27.0,
     // x 35,664 bytes 562 / 309; 12,000 x 4 KiB 58.8 / 48.1; 20,011 x 4 KiB 50.3 / 51.5).
-    const uint64_t nb = block_count(len), cus = device_simds() / 4u;
+    // The padding-only block of a length divisible by 64 does not count against a lane that has
+    // its words formed on the scalar unit (SM3 of 128 bytes, up to 32,768 messages: 11.1-11.7 us
+    // / 11.9-12.4; of 192 level).
+    const uint64_t nb = block_count(len) - (staged && len % 64u == 0 ? 1u : 0u), cus = device_simds() / 4u;
     if (n > 128u * cus || nb >= 0x80000000u) return false;
     if (algo == MD5) return n <= 64u * cus && nb >= 64;
     return algo == SM3 ? nb >= 3 : algo == SHA1 && nb >= (n <= 64u * cus ? 4u : 32u);
