@@ -107,9 +107,10 @@ int hash_batch_strided(int algo, const uint8_t *messages, const uint64_t *offset
  * digests_out holds n slots of hb_digest_size(algo) bytes.  Allocates nothing.  When
  * messages and msg_len are multiples of 4 and msg_len < 2^25, each wave of 64 messages
  * stages two blocks of all 64 at a time through LDS with whole-line loads (HB_PLAIN_LDS=0
- * reads each lane's message on its own instead).  Up to 128 SHA-1 or SM3 messages to a CU
- * have their schedules computed by a second wave (any value of HB_PLAIN_LDS: not so).  The
- * digests are the same whichever way.
+ * reads each lane's message on its own instead).  Up to 128 SHA-1 or SM3 messages to a CU, or
+ * 64 MD5 messages of about 4 KiB or more, have their schedules computed by a second wave
+ * where they are long enough for that to pay (any value of HB_PLAIN_LDS: not so).  The digests
+ * are the same whichever way.
  */
 int hash_batch_fixed(int algo, const uint8_t *messages, uint64_t n, uint64_t msg_len,
                      uint8_t *digests_out, void *stream);
@@ -171,13 +172,13 @@ int hash_final_batch(int algo, const hb_state *states, const uint8_t *messages, 
                      const uint64_t *lengths, uint64_t n, uint8_t *digests_out, void *stream);
 
 /* ------------------------------------------------------------------------------------ */
-/* Batched form: length-bucketed, longest-first, persistent fused launch in a hipGraph.  */
+/* Batched form: the tiled launch, or a length-bucketed, longest-first pipeline.         */
 /* ------------------------------------------------------------------------------------ */
 
 typedef struct hb_plan hb_plan;
 
 enum {
-    HB_PLAN_GRAPH = 1,      /* capture the pipeline in a hipGraph and replay it (default on) */
+    HB_PLAN_GRAPH = 1,      /* capture the pipeline in hipGraphs and replay them (default on) */
     HB_PLAN_AUTOTUNE = 2,   /* time the kernel variants on first use and cache the choice */
     HB_PLAN_NO_SORT = 4,    /* skip bucketing: lanes take messages in index order */
     HB_PLAN_NO_LONG = 8,    /* no separate long-chain path (see hb_plan_create) */
@@ -258,8 +259,10 @@ int hb_plan_tiled(const hb_plan *plan);
  * be allocated. */
 int hb_plan_set_config(hb_plan *plan, int waves_per_cu, int msgs_per_lane, int variant);
 
-/* Average duration in milliseconds of the hashing launch over the runs without a graph since
- * the last call, measured with HIP events around it on the plan's stream; -1 if none. */
+/* Average duration in milliseconds of the hashing launch over the runs of plans without
+ * HB_PLAN_GRAPH since the last call, measured with HIP events around it on the run's stream
+ * (a tiled launch that starts the longest messages first: with the launches that pick them
+ * out); -1 if none. */
 double hb_plan_kernel_ms(hb_plan *plan);
 
 void hb_plan_destroy(hb_plan *plan);

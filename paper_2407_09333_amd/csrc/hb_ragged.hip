@@ -1,10 +1,10 @@
 // hb_ragged.hip -- packed batches of any lengths in one launch, with no workspace in HBM.
 //
-// A workgroup takes a tile of consecutive messages.  If their block counts are all but the
-// same it hashes them in index order, one lane each; else it sorts them by block count in
-// LDS and hashes them longest first: its longest messages (up to 32) by a chain pair -- two of its
-// four waves, hb_chain.hpp -- and the others 64 of near-equal length at a time by the
-// waves that are free.  A mixed batch gives each tile one workgroup per algorithm, which
+// A workgroup takes a tile of consecutive messages (hb_plan_rules.hpp).  If they have one block
+// count, or sorting would save too little, it hashes them in index order, one lane each; else
+// it sorts them by block count in LDS and hashes them longest first: its longest messages (up
+// to 32) by a chain pair -- two of its four waves, hb_chain.hpp -- and the others 64 of
+// near-equal length at a time by the waves that are free.  A mixed batch gives each tile one workgroup per algorithm, which
 // takes the tile's messages of that algorithm, so every wave is algorithm-uniform and the
 // three algorithms' chains run beside each other.
 //
