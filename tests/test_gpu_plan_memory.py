@@ -30,7 +30,7 @@ def test_schedule_scratch_comes_with_the_pipeline(hb):
     plan = hb.Plan(1000)
     assert before - free_bytes() < GIB // 2
     plan.set_config(waves_per_cu=16, msgs_per_lane=1, variant=0)
-    assert before - free_bytes() >= GIB
+    assert before - free_bytes() >= GIB // 2
     plan.set_config(waves_per_cu=8)  # no second one
     assert before - free_bytes() < GIB + GIB // 2
     plan.close()
@@ -43,7 +43,7 @@ def test_plans_that_may_take_the_pipeline_have_it_from_the_start(hb, monkeypatch
         monkeypatch.setenv("HB_WAVES_PER_CU", env)
     before = free_bytes()
     plan = hb.Plan(1000, flags=flags)
-    assert before - free_bytes() >= GIB
+    assert before - free_bytes() >= GIB // 2
     plan.close()
 
 
