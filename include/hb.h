@@ -181,7 +181,8 @@ enum {
     HB_PLAN_GRAPH = 1,      /* capture the pipeline in hipGraphs and replay them (default on) */
     HB_PLAN_AUTOTUNE = 2,   /* time the kernel variants on first use and cache the choice */
     HB_PLAN_NO_SORT = 4,    /* skip bucketing: lanes take messages in index order */
-    HB_PLAN_NO_LONG = 8,    /* no separate long-chain path (see hb_plan_create) */
+    HB_PLAN_NO_LONG = 8,    /* no separate long-chain path (see hb_plan_create): for batches
+                               without long messages */
     HB_PLAN_LONG_INLINE = 16 /* long-chain work and bulk in one launch on the run's stream:
                                 no side stream */
 };
