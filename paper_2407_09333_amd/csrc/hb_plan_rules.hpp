@@ -50,6 +50,7 @@ HB_HD inline uint64_t wave_region_blocks(LenAt len_at, uint32_t lanes, uint64_t 
 constexpr uint32_t kTileThreads = 256;  // four waves
 constexpr uint32_t kTileMax = 2048;     // messages of a tile, at most
 constexpr uint32_t kTileChains = 32;    // messages that a tile's chain pair takes, at most
+constexpr uint32_t kTileChainsMd5 = 8;  // of MD5 messages of one length (kChainsAlike, hb_ragged.hip)
 
 // How a packed batch is dealt out: messages per tile, tiles, workgroups per tile (one per
 // algorithm), and how many times over its workgroups fill the chip.
@@ -57,16 +58,17 @@ struct Tiling {
     uint64_t tile, tiles, per, rounds;
 };
 
-inline Tiling tiling(uint64_t n, bool mixed, uint64_t cus)
+// chains: kTileChainsMd5 for a batch of MD5 messages, else kTileChains.
+inline Tiling tiling(uint64_t n, bool mixed, uint64_t cus, uint64_t chains = kTileChains)
 {
     const uint64_t per = mixed ? 3u : 1u, wide = mixed ? 2u : 1u, slots = cus * 4u;
     const uint64_t rounds = (n * per + slots * kTileMax - 1) / (slots * kTileMax);
     const uint64_t one = (n + cus - 1) / cus, all = (n * per + slots * rounds - 1) / (slots * rounds);
     uint64_t tile;
-    if (const uint64_t at_once = cus > per ? cus / per : 1u, few = (n + at_once - 1) / at_once; few <= kTileChains * wide) {
-        // One workgroup on each CU takes so few that its chain pair can take them all (of a
-        // mixed tile's 64 each algorithm has about 21): however alike their lengths, none is
-        // left to a lane of its own.  In tiles of 64, half of 64 equal messages or more were:
+    if (const uint64_t at_once = cus > per ? cus / per : 1u, few = (n + at_once - 1) / at_once; few <= chains * wide) {
+        // One workgroup on each CU takes so few that its chain pair takes them all however alike
+        // their lengths, and none is left to a lane of its own (of a mixed tile's 64 each
+        // algorithm has about 21; of MD5's the pair takes eight).  In tiles of 64, half of 64 equal messages or more were:
         // plans of 64 messages of 64 KiB took, MD5 / SHA-1 / SM3, 613 / 1,314 / 2,689 us, and
         // take 564 / 842 / 1,837 so; 1,000 of 16 KiB 155 / 328 / 677 and 151 / 220 / 472.
         tile = few;

@@ -81,6 +81,11 @@ template <int A> constexpr uint32_t kChainLeast = A == MD5 ? 48u : (A == SHA1 ? 
 template <int A> constexpr uint32_t kBlockOps = A == MD5 ? 324u : (A == SHA1 ? 613u : 1348u);
 constexpr uint32_t kSortOps = 700;
 
+// Messages of one block count that a tile's chain pair takes: MD5's chains gain least, and less
+// the more of them a pair runs (of 16 KiB, us, by lanes / by chain pairs: 8 to a pair 160 / 155,
+// 21 165 / 185).
+template <int A> constexpr uint32_t kChainsAlike = A == MD5 ? kTileChainsMd5 : kTileChains;
+
 constexpr uint64_t kNoMessage = ~0ull;
 constexpr uint32_t kNoLong = 0xffffffffu;
 
@@ -203,7 +208,7 @@ __device__ __forceinline__ void ragged_tile(const RaggedArgs &r, uint64_t base, 
     // message (262,144 messages, us with / without: MD5 of 0 to 64 bytes 14.3 / 12.2, 0 to 130
     // 17.7 / 16.8; SHA-1 18.4 / 16.2 and 23.6 / 22.5; MD5 of 0 to 257 20.2 sorted, 22.6 before).
     const bool worth = PER > 1 || (uint64_t(longest) * have - blocks) * kBlockOps<A> > uint64_t(kSortOps) * have;
-    const bool sorted = least == longest ? have <= kChainMessages && chains : chains || least == 0 || (MANY && worth);
+    const bool sorted = least == longest ? have <= kChainsAlike<A> && chains : chains || least == 0 || (MANY && worth);
     // Short messages of one algorithm are sorted within 512 at a time (the last 512 to 1,023 of
     // the tile), each with bins of its own: neighbours in memory share cache lines, and hashed
     // a whole tile apart they were read twice (4,000,000 messages of 0 to 257 / 1,024 bytes,
@@ -544,6 +549,11 @@ __global__ __launch_bounds__(kRaggedThreads) void k_fixed_chain(const uint8_t *_
     }
 }
 
+Tiling ragged_tiling(uint64_t n, bool mixed, int algo)
+{
+    return tiling(n, mixed, device_simds() / 4u, !mixed && algo == MD5 ? kTileChainsMd5 : kTileChains);
+}
+
 // A form each for tiles of one message a thread, two and more: unrolled for eight, the short
 // batches' launches spent a microsecond passing over code they had no messages for (300,007
 // messages of 16 bytes in tiles of 512, MD5 / SHA-1 / SM3, us: 11.2 / 14.0 / 21.5 unrolled for
@@ -561,12 +571,15 @@ template <int A> auto *ragged_form(uint64_t tile, bool few)
 hipError_t launch_ragged(const uint8_t *algos, int algo, const uint8_t *msgs, const uint64_t *offs, const uint64_t *lens,
                          uint64_t n, uint8_t *out, uint32_t stride, hipStream_t stream)
 {
-    const Tiling t = tiling(n, algos != nullptr, device_simds() / 4u);
+    const Tiling t = ragged_tiling(n, algos != nullptr, algo);
     const uint64_t tile = t.tile, tiles = t.tiles, per = t.per;
     if (tiles * per > 0x7fffffffull) return hipErrorInvalidConfiguration;
     const RaggedArgs r{msgs, offs, lens, algos, out, n, stride, uint32_t(tile)};
     const dim3 grid{uint32_t(tiles * per), 1, 1}, block{kRaggedThreads, 1, 1};
-    const bool few = tiles * per <= device_simds() / 4u;  // one wave to a SIMD (see few_waves)
+    // one wave to a SIMD (see few_waves); a mixed batch's workgroups have a third of a tile each
+    // (12,000 / 16,384 messages of 16 KiB, us: 852 / 861 with the form for shared SIMDs, 725 / 728
+    // without)
+    const bool few = tiles * per * ((tile + 64u * per - 1) / (64u * per)) <= device_simds();
     if (algos) {
         hipLaunchKernelGGL((tile > 2u * kRaggedThreads ? k_ragged_mixed<true, kPerThread> : few ? k_ragged_mixed<false, 2> : k_ragged_mixed<true, 2>),
                            grid, block, 0, stream, r, uint32_t(tiles));
@@ -609,12 +622,12 @@ hipError_t launch_fixed_chain(int algo, const uint8_t *msgs, uint64_t n, uint64_
     return hipGetLastError();
 }
 
-bool ragged_in_one_round(uint64_t n, bool mixed) { return tiling(n, mixed, device_simds() / 4u).rounds <= 1; }
+bool ragged_in_one_round(uint64_t n, bool mixed) { return ragged_tiling(n, mixed, SM3).rounds <= 1; }
 
 hipError_t launch_ragged_long(const LongWs &w, const uint8_t *algos, int algo, const uint8_t *msgs, const uint64_t *offs,
                               const uint64_t *lens, uint64_t n, uint8_t *out, uint32_t stride, hipStream_t stream)
 {
-    const Tiling t = tiling(n, algos != nullptr, device_simds() / 4u);
+    const Tiling t = ragged_tiling(n, algos != nullptr, algo);
     if (t.tiles * t.per + kLongGroups > 0x7fffffffull) return hipErrorInvalidConfiguration;
     const RaggedArgs r{msgs, offs, lens, algos, out, n, stride, uint32_t(t.tile)};
     const dim3 block{kRaggedThreads, 1, 1}, sweep{device_simds(), 1, 1}, grid{uint32_t(kLongGroups + t.tiles * t.per), 1, 1};

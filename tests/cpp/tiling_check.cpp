@@ -19,7 +19,9 @@ void fail(const char *what, uint64_t n, bool mixed, uint64_t cus)
 
 void check(uint64_t n, bool mixed, uint64_t cus)
 {
-    const hb::Tiling t = hb::tiling(n, mixed, cus);
+    const hb::Tiling t = hb::tiling(n, mixed, cus), md5 = hb::tiling(n, mixed, cus, hb::kTileChainsMd5);
+    if (!mixed && (n <= hb::kTileChainsMd5 * cus ? md5.tile > hb::kTileChainsMd5 : md5.tile % 64u != 0))
+        fail("MD5", n, mixed, cus);
     if (t.tile == 0 || t.tile > hb::kTileMax || t.per != (mixed ? 3u : 1u)) fail("tile", n, mixed, cus);
     if (t.tiles * t.tile < n || (t.tiles - 1) * t.tile >= n) fail("tiles", n, mixed, cus);
     if (t.tiles * t.per > t.rounds * cus * 4u + t.per) fail("rounds", n, mixed, cus);

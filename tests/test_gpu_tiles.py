@@ -43,11 +43,11 @@ def check_batch(hb, lens, seed, what, mixed=True):
 
 
 @pytest.mark.parametrize("length", [4100, 200])
-@pytest.mark.parametrize("per_cu", [1, 32])
+@pytest.mark.parametrize("per_cu", [1, 8, 32])
 @pytest.mark.parametrize("extra", [-1, 0, 1])
 def test_few_alike_messages(hb, length, per_cu, extra):
     """Messages of one length, on both sides of the counts where every one of a tile runs in
-    its chain pair (32 to a CU; 64 to three CUs where algorithms are mixed)."""
+    its chain pair (32 to a CU, eight of MD5; 64 to three CUs where algorithms are mixed)."""
     cus = hb.device_info()["cu_count"]
     check_batch(hb, np.full(per_cu * cus + extra, length), 3, "few alike", mixed=False)
     n = 2 * per_cu * (cus // 3) + extra
@@ -77,3 +77,18 @@ def test_short_messages_sorted_512_at_a_time(hb, per_cu, longest):
     lens = rng.integers(0, 150, n)
     lens[rng.choice(n, 3 * n // 2000, replace=False)] = 64 * longest - 9   # in most tiles
     check_batch(hb, lens, 7, "short sorted", mixed=per_cu == 2300)
+
+
+def test_mixed_batches_of_one_wave_per_simd(hb):
+    """Mixed batches on both sides of one wave per SIMD: the workgroups have about a third of a
+    tile each."""
+    cus = hb.device_info()["cu_count"]
+    for n in (64 * cus, 128 * cus + 1, 226 * cus, 226 * cus + 1, 256 * cus):
+        print(f"case mixed few n={n}", flush=True)
+        rng = np.random.default_rng(n)
+        lens = rng.integers(0, 700, n).astype(np.uint64)
+        algos = rng.integers(0, 3, n).astype(np.uint8)
+        offs = workloads.packed(lens)
+        msgs = workloads.host_random_bytes(int(lens.sum()) + 1, seed=8)
+        got = hb.hash_batch_mixed(algos, msgs, offs, lens).cpu().numpy()
+        assert_same(got, oracle.hash_batch(algos, msgs, offs, lens), f"mixed few {n}")
